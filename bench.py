@@ -12,7 +12,7 @@ step), the dominant kernel's roofline position (per-kernel time from HIP events 
 library on the launch stream), and the fp64 CPU oracle timed on the host cores as a reported baseline.
 
 --mode headline runs only the step and the self-contained pair (the run the rocprofv3 summaries under
-profiles/ are taken from); --mode streamed the same under DN_OPT_STREAMED_CHUNK_KERNEL.
+profiles/ are taken from).
 """
 from __future__ import annotations
 
@@ -47,17 +47,20 @@ def kernel_flops_per_chunk_head(name: str, d: int, c: int = C) -> float:
         return 2 * c * c * d + (2.0 / 3.0) * c ** 3
     if "k_scan_fwd_save" in name:  # as k_scan_fwd
         return 6 * c * d * d + 8 * c * c * d
-    if "k_scan_bwd" in name:     # T K, K Q^T, P^T dO (3 x 2C^2 d); K dS, Q^T dO, W^T dUt (3 x 2Cd^2)
-        return 6 * c * d * d + 6 * c * c * d
-    if "k_scan_pair" in name:    # recompute scan: T K, T V, W S, K^T Ut; reverse scan: T K, K Q^T, P^T dO, K dS, Q^T dO, W^T dUt
-        return (4 * c * d * d + 4 * c * c * d) + (6 * c * d * d + 6 * c * c * d)
+    if "k_scan_bwd" in name:     # T K, K Q^T, P^T dO, T^T dUt (4 x 2C^2 d); K dS, Q^T dO, W^T dUt (3 x 2Cd^2)
+        return 6 * c * d * d + 8 * c * c * d
+    if "k_scan_pair" in name:    # recompute scan: T K, T V, W S, K^T Ut; reverse scan as above
+        return (4 * c * d * d + 4 * c * c * d) + (6 * c * d * d + 8 * c * c * d)
     if "k_scan_fwd" in name:     # T K, T V, Q K^T, P Ut (4 x 2C^2 d); W S, Q S, K^T Ut (3 x 2Cd^2)
         return 6 * c * d * d + 8 * c * c * d
     if "k_bwd_stream" in name:
         # K S, K dS', dO S^T, Ut dS'^T, dV S^T (5 x 2Cd^2); T R, P^T dO, X^T dUt, dO Ut^T, dUt R^T, Q K^T, dP K, dP^T Q,
         # K K^T, Ah K, Ah^T K (11 x 2C^2 d); dX X^T, X^T M1 (2 x 2C^3)
         return 10 * c * d * d + 22 * c * c * d + 4 * c ** 3
-    if "k_bwd_chunk" in name:
+    if "k_bwd_local" in name:
+        # dO S^T, dV S^T, Ut dS'^T (3 x 2Cd^2); dO Ut^T, dV Ut^T, dP K, dP^T Q, (Ah + Ah^T) K (5 x 2C^2 d)
+        return 6 * c * d * d + 10 * c * c * d
+    if "k_bwd_chunk" in name:    # the form through the inverse that k_bwd_local replaced
         # adjoint of Eq. 8-9: dO S^T, dUt S^T, Ut dS^T (3 x 2Cd^2); dO Ut^T, dP K, dP^T Q (3 x 2C^2 d)
         # adjoint of Eq. 10-11: K K^T, dW K^T, dU V^T, X^T dW, X^T dU, Ah K, Ah^T K (7 x 2C^2 d);
         #                       dX X^T, X^T M1 (2 x 2C^3); forward substitution (2/3 C^3)
@@ -71,18 +74,20 @@ def kernel_bytes_per_chunk_head(name: str, d: int, c: int = C, es: int = 2) -> f
 
     tile = C x d elements, cc = C x C, st = d x d (states leave the scans in the element type)."""
     tile, cc, st, beta = c * d * es, c * c * es, d * d * es, c * es
-    if "k_wy_prep" in name:      # K, beta -> T, X
-        return tile + beta + 2 * cc
+    if "k_wy_prep" in name:      # K, beta -> T
+        return tile + beta + cc
     if "k_scan_fwd_save" in name:  # Q, K, V, T -> O, Ut, S
         return 3 * tile + cc + 2 * tile + st
-    if "k_scan_bwd" in name:     # Q, K, dO, T -> dUt, dS'
+    if "k_scan_bwd" in name:     # Q, K, dO, T -> dV, dS'
         return 3 * tile + cc + tile + st
-    if "k_scan_pair" in name:    # K, V, T -> Ut, S   and   Q, K, dO, T -> dUt, dS'
+    if "k_scan_pair" in name:    # K, V, T -> Ut, S   and   Q, K, dO, T -> dV, dS'
         return (2 * tile + cc + tile + st) + (3 * tile + cc + tile + st)
     if "k_scan_fwd" in name:     # Q, K, V, T -> O
         return 3 * tile + cc + tile
     if "k_bwd_stream" in name:   # dO, K, Q, V, S, dS', X, beta -> dQ, dK, dV, dbeta
         return 4 * tile + 2 * st + cc + beta + 3 * tile + c * 4
+    if "k_bwd_local" in name:    # dO, dV, Ut, K, Q, S, dS', beta -> dQ, dK, dbeta
+        return 5 * tile + 2 * st + beta + 2 * tile + c * 4
     if "k_bwd_chunk" in name:    # dO, Ut, dUt, K, Q, V, S, dS', X, beta -> dQ, dK, dV, dbeta
         return 6 * tile + 2 * st + cc + beta + 3 * tile + c * 4
     return 0.0
@@ -91,7 +96,7 @@ def kernel_bytes_per_chunk_head(name: str, d: int, c: int = C, es: int = 2) -> f
 def kernel_algorithmic_bytes_per_token_head(name: str, d: int, es: int = 2) -> float:
     """What the METHOD obliges a kernel to move per token and head: the layer's own tensors it reads and writes, once
     (forward: q, k, v, beta in, o out = 1026 B at d = 128 in bf16; backward: q, k, v, beta, do in, dq, dk, dv, dbeta out =
-    1798 B).  Intermediates that cross kernels (T, X, Ut, dUt, the chunk states) count for nothing here: they are the
+    1798 B).  Intermediates that cross kernels (T, Ut, the chunk states) count for nothing here: they are the
     price of the decomposition, and the roofline fraction reported against these bytes shows that price."""
     row, b_in, b_out = d * es, es, 4
     if "k_wy_prep" in name:                          # k, beta
@@ -102,6 +107,8 @@ def kernel_algorithmic_bytes_per_token_head(name: str, d: int, es: int = 2) -> f
         return 3 * row
     if "k_scan_pair" in name:                        # q, k, do and (recompute) k, v
         return 5 * row
+    if "k_bwd_local" in name:                        # q, k, beta, do -> dq, dk, dbeta (dv leaves in the reverse scan)
+        return 3 * row + b_in + 2 * row + b_out
     if "k_bwd_chunk" in name or "k_bwd_stream" in name:   # the backward pass: q, k, v, beta, do -> dq, dk, dv, dbeta
         return 4 * row + b_in + 3 * row + b_out
     return 0.0
@@ -134,8 +141,8 @@ def main() -> int:
     ap.add_argument("--steps", type=int, default=50)
     ap.add_argument("--warmup", type=int, default=10)
     ap.add_argument("--no-cpu-baseline", action="store_true")
-    ap.add_argument("--mode", choices=("full", "headline", "streamed"), default="full",
-                    help="headline: only the step and the self-contained pair; streamed: the same under DN_OPT_STREAMED_CHUNK_KERNEL")
+    ap.add_argument("--mode", choices=("full", "headline"), default="full",
+                    help="headline: only the step and the self-contained pair")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run a plain 256 MiB device copy, as the reference dispatch that scales the "
                          "rocprofv3 FETCH_SIZE / WRITE_SIZE counters")
@@ -196,8 +203,6 @@ def main() -> int:
         dn.deltanet_profile_enable(False)
         return {name.strip("()"): (ms, n) for name, (ms, n) in prof.items()}
 
-    if args.mode == "streamed":
-        dn.deltanet_set_option(dn.DN_OPT_STREAMED_CHUNK_KERNEL, 1)
     if args.copy_calibration:
         src = torch.empty(256 << 20, dtype=torch.uint8, device=dev).random_(0, 255)
         dst = torch.empty_like(src)
@@ -277,8 +282,7 @@ def main() -> int:
         "precondition_steps": PRECONDITION_STEPS,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16", "data": "synthetic",
-        "config": {"workload": "configs[2]: bf16 fwd+bwd, B=8, L=2048, H=16, d_k=d_v=128, chunk=64; the forward pass keeps its per-chunk tiles for the backward pass"
-                               + ("; option DN_OPT_STREAMED_CHUNK_KERNEL" if args.mode == "streamed" else ""),
+        "config": {"workload": "configs[2]: bf16 fwd+bwd, B=8, L=2048, H=16, d_k=d_v=128, chunk=64; the forward pass keeps its per-chunk tiles for the backward pass",
                    "tokens_per_step": tokens},
         "ms_per_step_median_of_events": round(statistics.median(step_ms), 4),
         "fwd_ms": round(fw, 4), "bwd_ms": round(bw, 4),
@@ -297,7 +301,7 @@ def main() -> int:
         "roofline": roofline,
     }
 
-    # The self-contained pair on the same workload (the backward pass recomputes T, X, the chunk states and
+    # The self-contained pair on the same workload (the backward pass recomputes T, the chunk states and
     # Ut from the inputs, as the paper's implementation does), with its own per-kernel times.
     rms = wall_ms(recompute_step, args.steps, args.warmup)
     rprof = profile(recompute_step, args.steps)
@@ -305,20 +309,8 @@ def main() -> int:
         "ms_per_step": round(rms, 4), "tokens_per_s": round(tokens / (rms * 1e-3), 1), "steps": args.steps,
         "kernels": {name: {"avg_ms": round(ms / n, 4), "launches_per_step": n // args.steps} for name, (ms, n) in rprof.items()}}
     if args.mode != "full":
-        if args.mode == "streamed":
-            dn.deltanet_set_option(dn.DN_OPT_STREAMED_CHUNK_KERNEL, 0)
         print(json.dumps(out))
         return 0
-
-    # The same step with the chunk kernel that streams S and dS' in column blocks and rebuilds Ut, dUt on chip (the
-    # scans then do not store them): fewer bytes, more barrier intervals.
-    dn.deltanet_set_option(dn.DN_OPT_STREAMED_CHUNK_KERNEL, 1)
-    sms = wall_ms(step, args.steps, args.warmup)
-    sprof = profile(step, args.steps)
-    dn.deltanet_set_option(dn.DN_OPT_STREAMED_CHUNK_KERNEL, 0)
-    out["streamed_chunk_kernel_fwd_bwd"] = {
-        "ms_per_step": round(sms, 4), "tokens_per_s": round(tokens / (sms * 1e-3), 1), "steps": args.steps, "vs_plain": round(sms / ms_per_step, 3),
-        "kernels": {name: {"avg_ms": round(ms / n, 4), "launches_per_step": n // args.steps} for name, (ms, n) in sprof.items()}}
 
     # The same forward in the recurrent (token-serial) form, the baseline the paper times the chunkwise
     # form against; vector-ALU bound: 3 fused multiply-adds per state element per token.
@@ -366,7 +358,7 @@ def main() -> int:
     del wsf, qp, kp, bp
 
     # The same number of tokens and the same model width at head size 256 (H / 2 heads): the scans own 32 state columns
-    # per workgroup and the backward's chunk kernel streams S and dS' in column blocks.
+    # per workgroup.
     H2, d2 = max(1, H // 2), 2 * d
     gen = torch.Generator(device="cpu").manual_seed(7)
     unit2 = lambda: torch.nn.functional.normalize(torch.randn(B, L, H2, d2, generator=gen), dim=-1).bfloat16().to(dev)

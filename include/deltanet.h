@@ -116,7 +116,7 @@ int deltanet_bwd(const dn_shape *shape, const void *q, const void *k, const void
  * results instead of recomputing them (the other side of the trade section 3.2 describes: with
  * hundreds of GB of HBM the chunk states of a layer, d_k * d_v * 2 bytes per 64 tokens and head in
  * bf16, are cheap to keep, and the backward pass then skips the UT transform and the forward scan).
- * deltanet_fwd_save computes what deltanet_fwd computes and leaves T and (I + A)^-1 of Eq. 10, the
+ * deltanet_fwd_save computes what deltanet_fwd computes and leaves T of Eq. 10, the
  * chunk-initial states and U - W S of Eq. 8 in `saved`; deltanet_bwd_saved computes what deltanet_bwd
  * computes from the same q, k, v, beta and that buffer, which it also uses as scratch (afterwards the
  * buffer can serve another deltanet_fwd_save, not another deltanet_bwd_saved).  `saved` is
@@ -243,12 +243,9 @@ int deltanet_profile_collect(dn_kernel_time *out, int max_entries, int *num_entr
 
 /*
  * Process-wide options (each 0 by default).
- *  DN_OPT_STREAMED_CHUNK_KERNEL: the backward pass of the plain delta rule in bf16 (head sizes up to 128) takes the chunk
- *    kernel that reads the chunk states in blocks of 32 state columns and rebuilds U - W S of Eq. 8 and its gradient on
- *    chip instead of reading them back from the scans, which then do not store them: 13 % fewer bytes through HBM per
- *    training step, and on MI355X a slower step (the blocks take more barrier intervals than they save in traffic).
- *    Same results to within rounding.  deltanet_fwd_save and the deltanet_bwd_saved that follows it must run under the
- *    same setting.  Unknown options return DN_ERR_UNSUPPORTED.
+ *  DN_OPT_STREAMED_CHUNK_KERNEL: accepted and without effect.  It chose a chunk kernel that read the chunk states in
+ *    blocks of state columns; the one chunk kernel there is now does that for every rule, type and head size.
+ *    Unknown options return DN_ERR_UNSUPPORTED.
  */
 typedef enum { DN_OPT_STREAMED_CHUNK_KERNEL = 0 } dn_option;
 int deltanet_set_option(int option, int value);

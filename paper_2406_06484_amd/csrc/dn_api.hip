@@ -13,7 +13,6 @@
 namespace dn {
 namespace {
 struct ProfRec { std::string name; hipEvent_t a, b; };
-std::atomic<int> g_opt_streamed{0}; // DN_OPT_STREAMED_CHUNK_KERNEL
 std::mutex g_prof_mu;
 std::atomic<bool> g_prof_on{false};
 std::vector<ProfRec> g_prof;
@@ -45,7 +44,7 @@ constexpr int kChunk = 64;
 
 struct Plan {
     Problem pb;
-    size_t off_coff, off_T, off_X, off_Ut, off_dUt, off_Sc, off_dSc, off_gam, off_zg, off_Qm, off_Km, off_seg, seg_bytes, total;
+    size_t off_coff, off_T, off_Ut, off_Sc, off_dSc, off_gam, off_Qm, off_Km, off_seg, seg_bytes, total;
     size_t esz;
 };
 
@@ -110,15 +109,17 @@ void make_plan(const dn_shape *s, int want_bwd, Plan *pl, bool gated = false, bo
     const size_t tC = up256(tiles * kChunk * kChunk * pl->esz);
     pl->off_T = o; o += tC; // T of Eq. 10
     if (want_bwd) {
-        pl->off_X = o; o += tC; // (I + A)^-1 of Eq. 10, reused by the chunk kernel
+        // (one C x C and one C x d_v tile per chunk and head are unused: the size that callers were told, and may have
+        // stored, for a shape stays what it was)
+        o += tC;
         pl->off_Ut = o; o += tV;
-        pl->off_dUt = o; o += tV;
+        o += tV;
         pl->off_Sc = o; o += tS;
         pl->off_dSc = o; o += tS;
     }
     if (gated) {
         pl->off_gam = o; o += up256(tiles * 2 * kChunk * sizeof(float)); // gamma_i and 1 / gamma_i per chunk row
-        pl->off_zg = o; o += up256(tiles * sizeof(float)); // <dS_C, S_C> per chunk, where the gate gradient takes a second kernel
+        o += up256(tiles * sizeof(float)); // (unused, as above)
     }
     { // forward pass split over segments of the sequence: N, M and the start state per segment
         const int nv = s->d_v / scan_vblock_cols((int)pl->esz, s->d_k, s->d_v);
@@ -141,16 +142,10 @@ void bind_workspace(const Plan &pl, void *ws, Ptrs *p, Problem *pb, bool want_bw
     pb->coff = pb->cu_user ? reinterpret_cast<int32_t *>(b + pl.off_coff) : nullptr;
     pb->cu = pb->cu_user ? pb->coff + 2 * (size_t)pb->N + 1 : nullptr;
     p->Tm = b + pl.off_T;
-    p->want_x = want_bwd;
     if (want_bwd) {
-        p->Xm = b + pl.off_X;
-        p->Ut = b + pl.off_Ut; p->dUt = b + pl.off_dUt; p->Sc = b + pl.off_Sc;
-        p->dSc = b + pl.off_dSc;
+        p->Ut = b + pl.off_Ut; p->Sc = b + pl.off_Sc; p->dSc = b + pl.off_dSc;
     }
-    if (gated) {
-        p->gam = reinterpret_cast<float *>(b + pl.off_gam);
-        p->zg = reinterpret_cast<float *>(b + pl.off_zg);
-    }
+    if (gated) p->gam = reinterpret_cast<float *>(b + pl.off_gam);
     if (prologue) {
         p->Qm = b + pl.off_Qm; p->Km = b + pl.off_Km;
     }
@@ -203,7 +198,6 @@ int fwd_impl(const dn_shape *shape, const void *q, const void *k, const void *v,
     pl.pb.stream = static_cast<hipStream_t>(hip_stream);
     pl.pb.save = save;
     p.pro = prologue;
-    p.streamed = dn::g_opt_streamed.load(std::memory_order_relaxed);
     bind_workspace(pl, workspace, &p, &pl.pb, save, gated, prologue);
     return impl->fwd(pl.pb, p) == 0 ? DN_OK : DN_ERR_LAUNCH;
 }
@@ -231,7 +225,6 @@ int bwd_impl(const dn_shape *shape, const void *q, const void *k, const void *v,
     pl.pb.stream = static_cast<hipStream_t>(hip_stream);
     pl.pb.save = saved;
     p.pro = prologue;
-    p.streamed = dn::g_opt_streamed.load(std::memory_order_relaxed);
     bind_workspace(pl, workspace, &p, &pl.pb, true, gated, prologue);
     return impl->bwd(pl.pb, p) == 0 ? DN_OK : DN_ERR_LAUNCH;
 }
@@ -391,9 +384,8 @@ int deltanet_gated_recurrent_fwd(const dn_shape *shape, const void *q, const voi
 }
 
 int deltanet_set_option(int option, int value) {
-    if (option != DN_OPT_STREAMED_CHUNK_KERNEL) return DN_ERR_UNSUPPORTED;
-    dn::g_opt_streamed.store(value != 0, std::memory_order_relaxed);
-    return DN_OK;
+    (void)value;
+    return option == DN_OPT_STREAMED_CHUNK_KERNEL ? DN_OK : DN_ERR_UNSUPPORTED;
 }
 
 int deltanet_profile_enable(int on) {

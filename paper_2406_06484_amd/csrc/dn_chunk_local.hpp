@@ -1,0 +1,463 @@
+// The chunk-parallel backward kernel: everything of the backward pass that is local to one chunk, given the chunk-initial
+// state S, the gradient dS' with respect to the state after the chunk, Ut (Eq. 8) and dV from the two scans.
+//
+// Inside a chunk Ut solves (I + A) Ut = diag(beta) (V - K S) with A = diag(beta) tril(K K^T, -1) (Eq. 10-11), so with dUt =
+// P^T dO + K dS' the adjoint of the solve is G = (I + A)^-T dUt, and everything follows from G and Ut:
+//     dV = diag(beta) G  (that is T^T dUt: the reverse scan forms it and stores it),    dA = -tril(G Ut^T, -1).
+// The inverse of Eq. 10 and the gradients with respect to W and T never have to exist here.  Per chunk:
+//     dP = tril(dO Ut^T)                  Ah = diag(beta) dA = -tril(dV Ut^T, -1)
+//     dQ = dO S^T + dP K                  dK = Ut dS'^T - dV S^T + dP^T Q + (Ah + Ah^T) K
+//     dbeta_i = G_i . (v_i - S_{i-1}^T k_i) = dV_i . Ut_i / beta_i^2,   the diagonal of dV Ut^T
+// (rows whose beta is zero, or so small that the quotient could leave the range of fp32, take dbeta from G and the
+// prediction error themselves: rare_dbeta below).
+//
+// The operands with a d_v axis (S, dS', dO, dV, Ut) are walked in blocks of BVB state columns, each read from global memory
+// once; K and Q stay in LDS for the chunk.  Every block waits in registers from the moment it is requested; as soon as it has
+// moved to LDS the same registers request the block NS blocks on (of the workgroup's next chunk, at the end), so about one
+// chunk's worth of loads (d = 128; NS blocks at d = 256) is in flight at any time.
+// Bound by HBM: per chunk and head 176 KB at d = 128 in bf16 (read q, k, dO, dV, Ut, S, dS'; write dq, dk), with a third of the
+// matrix and LDS work of the form that goes through the inverse (which read X, V and dUt and wrote dV as well, 216 KB, in
+// eleven barrier intervals; here six).  Measured, 16 384 tokens of width 2048, kernel time before and now: d = 128 185 -> 138 us
+// (5.2 TB/s, what a copy reaches), d = 64 223 -> 115 us, d = 256 247 -> 195 us, gated 223 -> 191 us, prologue 229 -> 190 us.
+#pragma once
+#include <type_traits>
+
+#include "dn_kernels.hpp"
+
+namespace dn {
+
+template <typename T, int DK, int DV> struct LocalSmem {
+    static constexpr int BVB0 = sizeof(T) == 2 ? (DK > 128 ? 32 : 64) : (DK > 32 ? 32 : 64);
+    static constexpr int BVB = DV < BVB0 ? DV : BVB0, NB = DV / BVB; // state columns per block, blocks per chunk
+    static constexpr int NS = NB < 2 ? 1 : 2;                        // register sets for the blocks in flight
+    static_assert(NB % NS == 0, "blocks alternate between the register sets");
+    // (d_k = 64: rows padded by 8, so that two workgroups fit the LDS of a CU)
+    static constexpr int LK = (sizeof(T) == 2 && DK == 64) ? ldc<T>(DK) : ldn<T>(DK);
+    static constexpr int LB = ldc<T>(BVB), LU = ldc<T>(C), LT = ldn<T>(C), LQO = ldc<T>(DK);
+    static constexpr size_t oK = 0;
+    static constexpr size_t oQ = oK + align16(sizeof(T) * C * LK);
+    static constexpr size_t oBeta = oQ + align16(sizeof(T) * C * LK);
+    static constexpr size_t oDg = oBeta + sizeof(float) * C;           // diagonal of dV Ut^T
+    static constexpr size_t oGam = oDg + sizeof(float) * C;            // gated: gamma_i
+    static constexpr size_t oZ = oGam + sizeof(float) * C;             // gated: per-wave shares of <dS_C, S_C> and <dS_0, S_0>
+    static constexpr size_t oCq = oZ + sizeof(float) * 2 * NWC;          // gated: q_i . dq_i per column block of d_k
+    static constexpr size_t oCv = oCq + sizeof(float) * (DK / 32) * C; // gated: v_i . dv_i
+    static constexpr size_t oMask = align16(oCv + sizeof(float) * C);
+    // the current block ...
+    static constexpr size_t oS = oMask + 16;
+    static constexpr size_t oDS = oS + align16(sizeof(T) * BVB * LK);
+    static constexpr size_t oDO = oDS + align16(sizeof(T) * BVB * LK);
+    static constexpr size_t oDV = oDO + align16(sizeof(T) * C * LB);
+    static constexpr size_t oUt = oDV + align16(sizeof(T) * C * LB);
+    static constexpr size_t endB = oUt + align16(sizeof(T) * BVB * LU);
+    // ... and over its bytes, after the last one: dP and Ah + Ah^T, the staging tiles of the waves that own C x d_k tiles
+    // (prologue variant: dq and dk as C x d_k matrices instead)
+    static constexpr int TILES = 2 * (DK / 32), NSTG = TILES < NWC ? TILES : NWC;
+    static constexpr size_t oDP = oS, oBm = oDP + align16(sizeof(T) * C * LT);
+    static constexpr size_t oStage = oBm + align16(sizeof(T) * C * LT);
+    static constexpr size_t endS = oStage + NSTG * sizeof(T) * Stage<T>::ELEMS;
+    static constexpr size_t oDQm = oStage, oDKm = oDQm + align16(sizeof(T) * C * LQO), endP = oDKm + align16(sizeof(T) * C * LQO);
+    // rare_dbeta: a C x C matrix and a block of 32 columns
+    static constexpr size_t oL = oS, oRS = oL + align16(sizeof(T) * C * LT), endR = oRS + sizeof(T) * (64 * LK + 2 * C * ldc<T>(32) + 32 * LU);
+    static constexpr size_t bytes = cmax(cmax(endB, endS), endR), bytes_pro = cmax(cmax(endB, endP), endR);
+    // d_k, d_v <= 64 in bf16: two workgroups per CU
+    static constexpr int WPC = (bytes <= 80 * 1024 && bytes_pro <= 80 * 1024 && sizeof(T) == 2 && DK <= 64 && DV <= 64) ? 2 : 1;
+};
+
+struct NoTile {};
+
+// beta below this: dbeta is not taken from the quotient (its square, and products of its size, stay far inside fp32 above it)
+constexpr float kTinyBeta = 0x1p-40f;
+
+// dbeta of the rows whose beta is zero (or tiny), formed from G and the prediction error
+//     e = V - K S - tril(K K^T, -1) Ut,   G = P^T dO + K dS' - tril(K K^T, -1)^T dV,   dbeta_i = G_i . e_i,
+// in a second walk over the workgroup's tiles that every workgroup makes which met such a row, in blocks of 32 state columns.
+// Waves 0 and 1 own rows 0..31 and 32..63 of e and G.  (Masked tokens are the case in real use: beta = 0 leaves the state alone.)
+template <typename T, int DK, int DV, int VAR>
+__device__ inline void rare_dbeta(const SeqMap &sm, int H, const Ptrs &p, int chunks_total, unsigned char *smem) {
+    using SM = LocalSmem<T, DK, DV>;
+    constexpr int MB = 2, LB = ldc<T>(32);
+    T *sK = reinterpret_cast<T *>(smem + SM::oK), *sQ = reinterpret_cast<T *>(smem + SM::oQ);
+    T *sL = reinterpret_cast<T *>(smem + SM::oL), *sS = reinterpret_cast<T *>(smem + SM::oRS);
+    T *sDS = sS + 32 * SM::LK, *sDO = sDS + 32 * SM::LK, *sDV = sDO + C * LB, *sUt = sDV + C * LB;
+    int tx = threadIdx.x, wave;
+    auto fresh = [&]() __attribute__((always_inline)) { tx = threadIdx.x; asm volatile("" : "+v"(tx)); wave = tx >> 6; }; // see k_bwd_local
+    auto cc_tile = [&](const T *A, bool strict) __attribute__((always_inline)) { // tril(A K^T) to sL
+        if (wave < 4) {
+            const int mi = wave >> 1, ni = wave & 1;
+            f32x16 t = zero16();
+            if (mi >= ni) mma<DK, false, false, T, true, MB>(t, A + 32 * mi * SM::LK, SM::LK, sK + 32 * ni * SM::LK, SM::LK, tx);
+            acc_each(t, [&](int rr, int c, float &val) { const int i = 32 * mi + rr, j = 32 * ni + c; if (j > i || (strict && j == i)) val = 0.f; }, tx);
+            acc_to_lds<T>(sL, SM::LT, 32 * mi, 32 * ni, t, tx);
+        }
+    };
+#pragma unroll 1
+    for (TileIter it(chunks_total, H); it.valid(); it.next()) {
+        const TilePos tp = tile_pos(sm, H, it.gid(), it.head());
+        if (!tp.ok) break;
+        fresh();
+        float b = 1.f; // beta of row tx & 63, in every wave
+        if ((tx & 63) < tp.nvalid) b = to_f32(((const T *)p.beta)[(tp.row0 + (tx & 63)) * H + tp.h]);
+        if (VAR == VAR_PROLOGUE && (tx & 63) < tp.nvalid) b = sigmoid_f32(b);
+        const unsigned long long mask = __ballot(fabsf(b) < kTinyBeta);
+        if (!mask) continue;
+#pragma unroll 1
+        for (int e = tx; e < C * DK; e += NTC) {
+            const int i = e / DK, k = e % DK;
+            const long at = ((tp.row0 + i) * H + tp.h) * DK + k;
+            sK[i * SM::LK + k] = i < tp.nvalid ? ((const T *)(VAR == VAR_PROLOGUE ? p.Km : p.k))[at] : from_f32<T>(0.f);
+            sQ[i * SM::LK + k] = i < tp.nvalid ? ((const T *)(VAR == VAR_PROLOGUE ? p.Qm : p.q))[at] : from_f32<T>(0.f);
+        }
+        f32x16 sum = zero16();
+#pragma unroll 1
+        for (int v0 = 0; v0 < DV; v0 += 32) {
+#pragma unroll 1
+            for (int e = tx; e < 32 * DK; e += NTC) {
+                const int v = e / DK, k = e % DK;
+                sS[v * SM::LK + k] = ((const T *)p.Sc)[(tp.tile * DV + v0 + v) * DK + k];
+                sDS[v * SM::LK + k] = ((const T *)p.dSc)[(tp.tile * DV + v0 + v) * DK + k];
+            }
+#pragma unroll 1
+            for (int e = tx; e < C * 32; e += NTC) {
+                const int i = e >> 5, v = e & 31;
+                const long at = ((tp.row0 + i) * H + tp.h) * DV + v0 + v;
+                const float g = VAR == VAR_GATED ? p.gam[tp.tile * 2 * C + i] : 1.f;
+                sDO[i * LB + v] = i < tp.nvalid ? from_f32<T>(to_f32(((const T *)p.d_o)[at]) * g) : from_f32<T>(0.f);
+                sDV[i * LB + v] = i < tp.nvalid ? from_f32<T>(-to_f32(((const T *)p.dv)[at]) * g) : from_f32<T>(0.f);
+                sUt[(e >> 6) * SM::LU + (e & 63)] = ((const T *)p.Ut)[(tp.tile * DV + v0 + (e >> 6)) * C + (e & 63)];
+            }
+            lds_barrier(); fresh();
+            cc_tile(sK, true);
+            lds_barrier(); fresh();
+            f32x16 g = zero16(), e = zero16();
+            if (wave < 2) {
+                mma<DK, false, false, T, true, MB>(e, sK + 32 * wave * SM::LK, SM::LK, sS, SM::LK, tx);
+                mma<C, false, false, T, true, MB>(e, sL + 32 * wave * SM::LT, SM::LT, sUt, SM::LU, tx);
+                mma<DK, false, false, T, true, MB>(g, sK + 32 * wave * SM::LK, SM::LK, sDS, SM::LK, tx);
+                mma<C, true, true, T, true, MB>(g, sL + 32 * wave, SM::LT, sDV, LB, tx);
+            }
+            lds_barrier(); fresh();
+            cc_tile(sQ, false);
+            lds_barrier(); fresh();
+            if (wave < 2) {
+                mma<C, true, true, T, true, MB>(g, sL + 32 * wave, SM::LT, sDO, LB, tx);
+                const int l31 = tx & 31, hh = (tx & 63) >> 5;
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const int i = 32 * wave + 8 * (u >> 2) + 4 * hh + (u & 3);
+                    float v = i < tp.nvalid ? to_f32(((const T *)p.v)[((tp.row0 + i) * H + tp.h) * DV + v0 + l31]) : 0.f;
+                    if (VAR == VAR_GATED) v *= p.gam[tp.tile * 2 * C + C + i];
+                    sum[u] += g[u] * (v - e[u]);
+                }
+            }
+            lds_barrier(); fresh();
+        }
+        const int l31 = tx & 31, hh = (tx & 63) >> 5;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int i = (32 * wave + 8 * (u >> 2) + 4 * hh + (u & 3)) & (C - 1);
+            float db = sum[u];
+#pragma unroll
+            for (int d = 1; d < 32; d <<= 1) db += __shfl_xor(db, d);
+            if (VAR == VAR_PROLOGUE) { // through the sigmoid
+                const float bi = __shfl(b, i);
+                db *= bi * (1.f - bi);
+            }
+            if (wave < 2 && l31 == 0 && ((mask >> i) & 1)) p.dbeta[(tp.row0 + i) * H + tp.h] = db;
+        }
+    }
+}
+
+template <typename T, int DK, int DV, int VAR>
+__global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSmem<T, DK, DV>::WPC))) void k_bwd_local(SeqMap sm, int H, Ptrs p, int chunks_total) {
+    using SM = LocalSmem<T, DK, DV>;
+    constexpr bool GATED = VAR == VAR_GATED, PRO = VAR == VAR_PROLOGUE;
+    constexpr int BVB = SM::BVB, NB = SM::NB;
+    constexpr int NS = GATED ? 1 : SM::NS; // (the gated kernels have no registers for a second set)
+    constexpr int KT = SM::TILES, KW = (KT + NWC - 1) / NWC; // 32 x 32 tiles of a C x d_k matrix, and per wave
+    // operand fragments per request batch (one where registers are short: two workgroups per CU, the gated kernels)
+    constexpr int MB = (SM::WPC == 2 || (GATED && sizeof(T) == 2)) ? 1 : 2;
+    // a C x BVB tile of dO, dV: 512 pieces of 16 bytes, or 256 (then each half of the workgroup fetches one of the two)
+    constexpr bool HALF = C * BVB / El<T>::VEC < NTC;
+    extern __shared__ __align__(16) unsigned char smem[];
+    T *sK = reinterpret_cast<T *>(smem + SM::oK), *sQ = reinterpret_cast<T *>(smem + SM::oQ);
+    T *sS = reinterpret_cast<T *>(smem + SM::oS), *sDS = reinterpret_cast<T *>(smem + SM::oDS);
+    T *sDO = reinterpret_cast<T *>(smem + SM::oDO), *sDV = reinterpret_cast<T *>(smem + SM::oDV); // sDV holds -dV
+    T *sUt = reinterpret_cast<T *>(smem + SM::oUt);
+    T *sDP = reinterpret_cast<T *>(smem + SM::oDP), *sBm = reinterpret_cast<T *>(smem + SM::oBm);
+    T *sDQm = reinterpret_cast<T *>(smem + SM::oDQm), *sDKm = reinterpret_cast<T *>(smem + SM::oDKm);
+    float *sBeta = reinterpret_cast<float *>(smem + SM::oBeta), *sDg = reinterpret_cast<float *>(smem + SM::oDg);
+    float *sGam = reinterpret_cast<float *>(smem + SM::oGam);
+    float *sZ = reinterpret_cast<float *>(smem + SM::oZ), *sCq = reinterpret_cast<float *>(smem + SM::oCq), *sCv = reinterpret_cast<float *>(smem + SM::oCv);
+    unsigned long long *sMask = reinterpret_cast<unsigned long long *>(smem + SM::oMask);
+    // The thread index as the helpers see it, re-read through an empty asm in every barrier interval: the per-lane offsets
+    // derived from it are then formed where they are used instead of being carried through the whole tile loop.
+    int tq = threadIdx.x;
+    auto fresh = [&]() __attribute__((always_inline)) { tq = threadIdx.x; asm volatile("" : "+v"(tq)); };
+    int wave = threadIdx.x >> 6;
+    const bool first_half = __builtin_amdgcn_readfirstlane((int)(threadIdx.x < 256)) != 0;
+    // tile number sI of this wave in a C x d_k matrix: row block ka, column block kb (with at most four such tiles they go to
+    // waves 4..7: the first four waves own the C x C tiles; at d_k = 256 a wave owns both row blocks of one column block)
+    constexpr int TSHIFT = KT <= 4 ? 4 : 0;
+    auto kt = [&](int sI) __attribute__((always_inline)) { return TSHIFT ? ((wave + TSHIFT) & (NWC - 1)) + sI * NWC : wave + sI * NWC; };
+    auto ka = [&](int sI) __attribute__((always_inline)) { return kt(sI) / (DK / 32); };
+    auto kb = [&](int sI) __attribute__((always_inline)) { return kt(sI) % (DK / 32); };
+
+    typedef TileRegs<T, C, BVB, HALF ? 256 : NTC> TokTile; // a block of dO, dV or V
+    static_assert(TokTile::NIT == 1 || sizeof(T) == 4 || !HALF, "one row per thread");
+    struct Blk {
+        TileRegs<T, BVB, DK, NTC> s, ds;
+        TokTile a;                                            // dO (HALF: first half dO, second half dV)
+        std::conditional_t<HALF, NoTile, TokTile> b;          // dV
+        TileRegs<T, BVB, C, HALF ? 256 : NTC> ut;             // (HALF: both halves hold a copy, the first one stores it)
+        std::conditional_t<GATED, TokTile, NoTile> v;         // gated: V, for v_i . dv_i (HALF: used by the second half)
+        float gr[TokTile::NIT];                               // gated: gamma of this thread's rows
+    } r[NS];
+    struct Head {
+        TileRegs<T, C, DK, NTC> k, q;
+        T beta; // kept in storage format: converting here would wait for the whole prefetch
+        float gm;
+    } rh;
+    std::conditional_t<PRO, TileRegs<T, C, DK, NTC>, NoTile> rawq, rawk;
+    // (`live` = 0 masks every row of a request: the instruction is issued, no memory is touched; no branch stands around a
+    // request, so the compiler knows how many are in flight and waits for exactly the one it needs)
+    auto fetch_blk = [&](Blk &x, const TilePos &tp, int vb, int live) __attribute__((always_inline)) {
+        const int v0 = vb * BVB, tt = HALF ? (tq & 255) : tq;
+        const long row = (tp.row0 * H + tp.h) * DV + v0, tv = tp.tile * DV + v0;
+        x.s.load_once((const T *)p.Sc + tv * DK, DK, BVB * live, tq);
+        x.ds.load_once((const T *)p.dSc + tv * DK, DK, BVB * live, tq);
+        if constexpr (HALF) x.a.load_once((first_half ? (const T *)p.d_o : (const T *)p.dv) + row, (long)H * DV, tp.nvalid * live, tt);
+        else {
+            x.a.load_once((const T *)p.d_o + row, (long)H * DV, tp.nvalid * live, tq);
+            x.b.load_once((const T *)p.dv + row, (long)H * DV, tp.nvalid * live, tq);
+        }
+        x.ut.load_once((const T *)p.Ut + tv * C, C, BVB * live, tt);
+        if constexpr (GATED) {
+            x.v.load_once((const T *)p.v + row, (long)H * DV, tp.nvalid * live, tt);
+            x.a.load_row_factors(x.gr, p.gam + tp.tile * 2 * C, tt);
+        }
+    };
+    auto fetch_head = [&](const TilePos &tp, int live) __attribute__((always_inline)) {
+        // (prologue variant: the q and k that k_wy_prep mapped and left in the workspace, in the layout of q and k)
+        rh.k.load_once((const T *)(PRO ? p.Km : p.k) + (tp.row0 * H + tp.h) * DK, (long)H * DK, tp.nvalid * live, tq);
+        rh.q.load_once((const T *)(PRO ? p.Qm : p.q) + (tp.row0 * H + tp.h) * DK, (long)H * DK, tp.nvalid * live, tq);
+        if (tq < C) rh.beta = ((const T *)p.beta)[(tp.row0 + min(tq, tp.nvalid - 1)) * H + tp.h];
+        if (GATED && tq < C) rh.gm = p.gam[tp.tile * 2 * C + tq];
+    };
+    auto pos_of = [&](const TileIter &it) __attribute__((always_inline)) { return it.valid() ? tile_pos(sm, H, it.gid(), it.head()) : TilePos{0, 0, 0, 0, false}; };
+
+    TileIter it(chunks_total, H);
+    TilePos cur = pos_of(it);
+    if (cur.ok) {
+        fetch_head(cur, 1);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) fetch_blk(r[s], cur, s, 1);
+    }
+    unsigned long long any_tiny = 0;
+    while (cur.ok) { // packed layout: the first chunk past the last real one ends the walk (so would every later one)
+        TileIter nx = it;
+        nx.next();
+        const TilePos np = pos_of(nx);
+        const TilePos nf = np.ok ? np : cur; // what the freed registers request at the end (masked where there is no next chunk)
+        const int nl = np.ok ? 1 : 0;
+        asm volatile("" : "+v"(wave)); // opaque: the tile offsets derived from it are not hoisted out of the loop
+        const int mi = (wave >> 1) & 1, ni = wave & 1; // tile of every C x C matrix, for the first four waves
+        const bool cc = wave < 4, upper = (mi == 0 && ni == 1);
+        T *stg = reinterpret_cast<T *>(smem + SM::oStage) + (wave % SM::NSTG) * Stage<T>::ELEMS;
+        const int nvalid = cur.nvalid, h = cur.h;
+        const long row0 = cur.row0;
+
+        rh.k.store(sK, SM::LK, tq); rh.q.store(sQ, SM::LK, tq);
+        if (tq < C) {
+            float b = tq < nvalid ? to_f32(rh.beta) : 0.f;
+            if (PRO) b = tq < nvalid ? sigmoid_f32(b) : 0.f; // beta = sigmoid(logit), section 2.2
+            sBeta[tq] = b;
+            const unsigned long long m = __ballot(tq < nvalid && fabsf(b) < kTinyBeta);
+            if (tq == 0) *sMask = m;
+            if (GATED) sGam[tq] = rh.gm;
+        }
+        // prologue variant: the pre-activations, for the way back through the map at the end of the chunk (at d_k = 256 they are
+        // requested after the last block: there are no registers to hold them longer)
+        auto fetch_raw = [&]() __attribute__((always_inline)) {
+            if constexpr (PRO) {
+                rawq.load_once((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid, tq);
+                rawk.load_once((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, tq);
+            }
+        };
+        if (DK <= 128) fetch_raw();
+        if (DK <= 128 || VAR == VAR_PLAIN) fetch_head(nf, nl);
+        // gated: this thread's shares of <dS~', S_0> and <K, Ut dS~'^T>
+        float zs = 0.f, zk = 0.f;
+        f32x16 dpc = zero16(), ahc = zero16(), dq[KW], dk[KW];
+        // (where the C x C tiles and the C x d_k tiles are on different waves, they share registers)
+        f32x16 &dp = TSHIFT ? dq[0] : dpc, &ah = TSHIFT ? dk[0] : ahc;
+#pragma unroll
+        for (int sI = 0; sI < KW; ++sI) { dq[sI] = zero16(); dk[sI] = zero16(); }
+
+        auto block = [&](Blk &x, int vb) __attribute__((always_inline)) {
+            // gated: the chunk is the plain rule on v_i / gamma_i with outputs gamma_i o~_i, so dO and dV rows come in scaled by gamma_i
+            if constexpr (GATED) {
+                zs += x.ds.dot(x.s);
+                // v_i . dv_i over this block's columns: the lanes that hold a row are adjacent
+                const int tt = HALF ? (tq & 255) : tq;
+#pragma unroll
+                for (int i = 0; i < TokTile::NIT; ++i) {
+                    float s;
+                    if constexpr (HALF) s = x.a.dot_row(x.v, i);
+                    else s = x.b.dot_row(x.v, i);
+#pragma unroll
+                    for (int d = 1; d < TokTile::TPR; d <<= 1) s += __shfl_xor(s, d);
+                    if (tt % TokTile::TPR == 0 && (!HALF || !first_half)) {
+                        float *to = sCv + i * TokTile::RPI + tt / TokTile::TPR;
+                        *to = vb == 0 ? s : *to + s;
+                    }
+                }
+                x.a.scale_rows(x.gr);
+                if constexpr (!HALF) x.b.scale_rows(x.gr);
+            }
+            x.s.store(sS, SM::LK, tq); x.ds.store(sDS, SM::LK, tq);
+            if constexpr (HALF) {
+                if (first_half) { x.a.store(sDO, SM::LB, tq & 255); x.ut.store(sUt, SM::LU, tq & 255); }
+                else x.a.store_neg(sDV, SM::LB, tq & 255);
+            } else {
+                x.a.store(sDO, SM::LB, tq); x.b.store_neg(sDV, SM::LB, tq);
+                x.ut.store(sUt, SM::LU, tq);
+            }
+            // this set's registers are free again
+            const bool wrap = vb + NS >= NB;
+            fetch_blk(x, wrap ? nf : cur, wrap ? vb + NS - NB : vb + NS, wrap ? nl : 1);
+            lds_barrier(); fresh();
+            if (cc && !upper) // dO Ut^T, -dV Ut^T: the fragments of Ut are read once for both
+                mma_shared_b<BVB, false, false, true, T, MB>(dp, ah, sDO + 32 * mi * SM::LB, SM::LB, sDV + 32 * mi * SM::LB, SM::LB, sUt + 32 * ni, SM::LU, tq);
+#pragma unroll
+            for (int sI = 0; sI < KW; ++sI) if (kt(sI) < KT) {
+                // dO S^T, -dV S^T
+                mma_shared_b<BVB, false, false, true, T, MB>(dq[sI], dk[sI], sDO + 32 * ka(sI) * SM::LB, SM::LB, sDV + 32 * ka(sI) * SM::LB, SM::LB,
+                                                             sS + 32 * kb(sI), SM::LK, tq);
+                if (GATED) { // Ut dS~'^T on its own, for <K, Ut dS~'^T>
+                    f32x16 t = zero16();
+                    mma<BVB, true, true, T, true, MB>(t, sUt + 32 * ka(sI), SM::LU, sDS + 32 * kb(sI), SM::LK, tq);
+                    acc_each(t, [&](int rr, int c, float &val) { zk += val * to_f32(sK[(32 * ka(sI) + rr) * SM::LK + 32 * kb(sI) + c]); }, tq);
+                    __builtin_amdgcn_sched_barrier(0);
+                    dk[sI] += t;
+                } else {
+                    mma<BVB, true, true, T, true, MB>(dk[sI], sUt + 32 * ka(sI), SM::LU, sDS + 32 * kb(sI), SM::LK, tq);
+                }
+            }
+            lds_barrier(); fresh(); // the block's bytes are free
+        };
+        if constexpr (NB == NS) {
+#pragma unroll
+            for (int vb = 0; vb < NB; ++vb) block(r[vb], vb);
+        } else {
+#pragma unroll 1
+            for (int vb = 0; vb < NB; vb += NS) {
+                block(r[0], vb);
+                if (NS == 2) block(r[NS - 1], vb + 1);
+            }
+        }
+        if (DK > 128) fetch_raw();
+        if (DK > 128 && VAR != VAR_PLAIN) fetch_head(nf, nl); // (no registers to hold it longer)
+
+        float z0 = 0.f; // gated: this thread's share of <Q, dO S^T> + <K, Ut dS~'^T - dV S^T>
+        if (GATED) {
+#pragma unroll
+            for (int sI = 0; sI < KW; ++sI) if (kt(sI) < KT) {
+                acc_each(dq[sI], [&](int rr, int c, float &val) { z0 += val * to_f32(sQ[(32 * ka(sI) + rr) * SM::LK + 32 * kb(sI) + c]); }, tq);
+                __builtin_amdgcn_sched_barrier(0);
+                acc_each(dk[sI], [&](int rr, int c, float &val) { z0 += val * to_f32(sK[(32 * ka(sI) + rr) * SM::LK + 32 * kb(sI) + c]); }, tq);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (cc) {
+            // dP = tril(dO Ut^T); Bm = Ah + Ah^T with Ah = -tril(dV Ut^T, -1); the diagonal of -dV Ut^T for dbeta
+            if (mi == ni) {
+                const int lane = tq & 63, c = lane & 31, hh = lane >> 5;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int rr = 8 * (e >> 2) + 4 * hh + (e & 3), i = 32 * mi + rr, j = 32 * mi + c;
+                    if (rr == c) sDg[i] = -ah[e];
+                    if (rr >= c) {
+                        const T x = from_f32<T>(rr == c ? 0.f : ah[e]);
+                        sBm[i * SM::LT + j] = x;
+                        sBm[j * SM::LT + i] = x;
+                    }
+                    dp[e] = rr >= c ? dp[e] : 0.f;
+                }
+            } else if (mi == 1) {
+                acc_to_lds<T>(sBm, SM::LT, 32, 0, ah, tq);
+                acc_to_lds_t<T>(sBm, SM::LT, 32, 0, ah, tq);
+            }
+            acc_to_lds<T>(sDP, SM::LT, 32 * mi, 32 * ni, dp, tq); // (the upper tile: zero)
+        }
+        lds_barrier(); fresh();
+#pragma unroll
+        for (int sI = 0; sI < KW; ++sI) if (kt(sI) < KT) {
+            // dQ += dP K, dK += Bm K (shared fragments of K), dK += dP^T Q (dP is lower triangular)
+            mma_shared_b<C, false, false, true, T, MB>(dq[sI], dk[sI], sDP + 32 * ka(sI) * SM::LT, SM::LT, sBm + 32 * ka(sI) * SM::LT, SM::LT,
+                                                       sK + 32 * kb(sI), SM::LK, tq);
+            if (ka(sI) == 1) mma<32, true, true, T, true, MB>(dk[sI], sDP + 32 * SM::LT + 32, SM::LT, sQ + 32 * SM::LK + 32 * kb(sI), SM::LK, tq);
+            else mma<C, true, true, T, true, MB>(dk[sI], sDP, SM::LT, sQ + 32 * kb(sI), SM::LK, tq);
+            if (PRO) {
+                acc_to_lds<T>(sDQm, SM::LQO, 32 * ka(sI), 32 * kb(sI), dq[sI], tq);
+                acc_to_lds<T>(sDKm, SM::LQO, 32 * ka(sI), 32 * kb(sI), dk[sI], tq);
+            } else {
+                if (GATED) { // also q_i . dq_i over this tile's columns, for the gate gradient
+                    acc_to_lds<T>(stg, Stage<T>::LD, 0, 0, dq[sI], tq);
+                    stage_flush_dot<T>(stg, (T *)p.dq + (row0 * H + h) * DK, (long)H * DK, 32 * ka(sI), 32 * kb(sI), nvalid, sQ, SM::LK,
+                                       sCq + kb(sI) * C);
+                } else {
+                    acc_store<T, true>(stg, (T *)p.dq + (row0 * H + h) * DK, (long)H * DK, 32 * ka(sI), 32 * kb(sI), nvalid, dq[sI], tq);
+                }
+                acc_store<T, true>(stg, (T *)p.dk + (row0 * H + h) * DK, (long)H * DK, 32 * ka(sI), 32 * kb(sI), nvalid, dk[sI], tq);
+            }
+        }
+        any_tiny |= *sMask;
+        if (tq < nvalid) { // (nvalid <= C) dbeta, from the diagonal of dV Ut^T
+            const float b = sBeta[tq], ib = 1.f / b;
+            float db = sDg[tq] * ib * ib;
+            if (PRO) db *= b * (1.f - b); // through the sigmoid
+            if (!((*sMask >> tq) & 1)) p.dbeta[(row0 + tq) * H + h] = db;
+        }
+        if (GATED) { // this wave's shares of <dS_C, S_C> and <dS_0, S_0>, summed in a fixed order after the barrier
+            float zc = zs + zk, zb = zs - zk + z0;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) { zc += __shfl_xor(zc, d); zb += __shfl_xor(zb, d); }
+            if ((tq & 63) == 0) { sZ[wave] = zc; sZ[NWC + wave] = zb; }
+        }
+        lds_barrier(); fresh();
+        if constexpr (PRO) { // dq, dk are assembled: gradient through the feature map, dx = SiLU'(x) (dy - y (y . dy)) / ||SiLU(x)||
+            rawq.feature_map_bwd_store(sDQm, SM::LQO, (T *)p.dq + (row0 * H + h) * DK, (long)H * DK, nvalid, tq);
+            rawk.feature_map_bwd_store(sDKm, SM::LQO, (T *)p.dk + (row0 * H + h) * DK, (long)H * DK, nvalid, tq);
+            lds_barrier(); fresh();
+        }
+        if (GATED && tq < C) {
+            // Gate gradient.  o_t is linear in q_t and in the state, so the sensitivity to a rescaling of the state at token j
+            // can be read off the other gradients: with c_i = q_i . dq_i - v_i . dv_i,
+            //     dg_j = <dS_C, S_C> + sum_{i >= j} c_i = <dS_0, S_0> - sum_{i < j} c_i    (S_0, S_C: state before and after the chunk).
+            // In bf16 the c_i are small differences of rounded terms and their noise adds up along the sum, so the two sums are
+            // weighted by how short they are: half the error at the middle of the chunk, less towards both ends.
+            float c = -sCv[tq];
+#pragma unroll
+            for (int b = 0; b < DK / 32; ++b) c += sCq[b * C + tq];
+            float pre = c; // inclusive prefix sum
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const float up = __shfl_up(pre, d);
+                if (tq >= d) pre += up;
+            }
+            const float all = __shfl(pre, C - 1);
+            auto zsum = [&](const float *z) __attribute__((always_inline)) { return ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7])); };
+            const float w = (float)tq / (float)nvalid;
+            const float from_start = zsum(sZ + NWC) - (pre - c), from_end = zsum(sZ) + (all - (pre - c));
+            if (tq < nvalid) p.dg[(row0 + tq) * H + h] = from_start + w * (from_end - from_start);
+        }
+        if (GATED) { lds_barrier(); fresh(); }
+        it = nx;
+        cur = np;
+    }
+    // (after the walk, so that none of it costs the loop above registers)
+    if (__builtin_amdgcn_readfirstlane((int)(any_tiny != 0))) rare_dbeta<T, DK, DV, VAR>(sm, H, p, chunks_total, smem);
+}
+
+} // namespace dn

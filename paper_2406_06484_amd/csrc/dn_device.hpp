@@ -341,31 +341,29 @@ template <typename T, int ROWS, int COLS, int NT = NTHR> struct TileRegs {
 #pragma unroll
         for (int it = 0; it < NIT; ++it) *reinterpret_cast<uint4 *>(dst + (it * RPI + tr) * ld + tc) = v[it];
     }
-    // sum over the elements this lane holds of (this tile) * (a tile of the same shape parked in LDS by store())
-    __device__ inline float dot_lds(const T *src, int ld, int t = threadIdx.x) const {
+    // ... with the sign of every element flipped (exact)
+    __device__ inline void store_neg(T *dst, int ld, int t = threadIdx.x) const {
+        constexpr unsigned S = sizeof(T) == 2 ? 0x80008000u : 0x80000000u;
         const int tr = t / TPR, tc = (t % TPR) * VEC;
+#pragma unroll
+        for (int it = 0; it < NIT; ++it)
+            *reinterpret_cast<uint4 *>(dst + (it * RPI + tr) * ld + tc) = make_uint4(v[it].x ^ S, v[it].y ^ S, v[it].z ^ S, v[it].w ^ S);
+    }
+    // sum over the elements this lane holds in step `it` of (this tile) * (another held tile of the same shape)
+    __device__ inline float dot_row(const TileRegs &o, int it) const {
+        alignas(16) T a[VEC], b[VEC];
+        *reinterpret_cast<uint4 *>(a) = v[it];
+        *reinterpret_cast<uint4 *>(b) = o.v[it];
         float s = 0.f;
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            alignas(16) T a[VEC], b[VEC];
-            *reinterpret_cast<uint4 *>(a) = v[it];
-            *reinterpret_cast<uint4 *>(b) = *reinterpret_cast<const uint4 *>(src + (it * RPI + tr) * ld + tc);
-#pragma unroll
-            for (int u = 0; u < VEC; ++u) s += to_f32(a[u]) * to_f32(b[u]);
-        }
+        for (int u = 0; u < VEC; ++u) s += to_f32(a[u]) * to_f32(b[u]);
         return s;
     }
     // sum over the elements this lane holds of (this tile) * (another held tile of the same shape)
     __device__ inline float dot(const TileRegs &o) const {
         float s = 0.f;
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            alignas(16) T a[VEC], b[VEC];
-            *reinterpret_cast<uint4 *>(a) = v[it];
-            *reinterpret_cast<uint4 *>(b) = o.v[it];
-#pragma unroll
-            for (int u = 0; u < VEC; ++u) s += to_f32(a[u]) * to_f32(b[u]);
-        }
+        for (int it = 0; it < NIT; ++it) s += dot_row(o, it);
         return s;
     }
     // The query/key feature map of section 3.3 on the held tile, in place: every row x becomes

@@ -15,7 +15,7 @@ struct Problem {
     hipStream_t stream;
     int device;             // the current device
     int num_cus;            // its compute units
-    int save;               // forward: also leave X, Ut and the chunk-initial states in the workspace;
+    int save;               // forward: also leave Ut and the chunk-initial states in the workspace;
                             // backward: find them there instead of recomputing them
 };
 
@@ -26,14 +26,12 @@ struct Ptrs {
     void *o, *dq, *dk, *dv;
     float *ST, *dbeta, *dS0;
     // workspace tiles, indexed by (global chunk * H + head)
-    void *Tm, *Xm, *Ut, *dUt, *Sc, *dSc;
-    int want_x; // backward: k_wy_prep also stores the inverse X for the chunk kernel
+    void *Tm, *Ut, *Sc, *dSc;
     // gated variant (all null for the plain delta rule): g = log decay per token and head (fp32, user
     // tensor), dg its gradient; workspace: gam = per chunk the running decay gamma_i and 1/gamma_i
     // ([tile][2][C] fp32)
     const float *g;
     float *dg, *gam;
-    float *zg; // gated, head sizes that take the streaming chunk kernel: <dS_C, S_C> per (chunk, head), for the gate gradient
     // prologue variant: q and k hold the pre-activations of the feature map, beta the logits; dq, dk and
     // dbeta receive the gradients with respect to those; workspace: Qm, Km = q, k after the map (layout of q, k)
     int pro;
@@ -44,8 +42,6 @@ struct Ptrs {
     // ... and of the backward pass: per segment the gradient the reverse scan produces from zero, and the gradient
     // with respect to the segment's end state
     float *Rseg, *dSout;
-    int streamed;   // option: the backward pass takes the chunk kernel that streams S and dS' and rebuilds Ut, dUt (k_bwd_stream)
-    int skip_ut;    // that kernel will run: the scans do not write Ut and dUt
     int unit_state; // set inside k_scan_state for its transition-matrix pass
 };
 
@@ -86,7 +82,6 @@ template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs 
 template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs &p);
 // largest dynamic LDS any kernel of this instantiation needs
 template <typename T, int DK, int DV> size_t max_lds_bytes();
-template <typename T, int DK, int DV> size_t max_lds_fwd_bytes(); // prep and forward scan only
 
 // The compiled (element type, d_k, d_v) instantiations: X(enum value of the C header, element type, d_k, d_v).
 // (bf16_t names __bf16 where the list is expanded; d = 256: the chunk tiles of its backward pass are streamed, they do

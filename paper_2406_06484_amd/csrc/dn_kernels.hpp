@@ -4,10 +4,10 @@
 //   k_wy_prep    per chunk            A = tril(diag(beta) K K^T,-1); X = (I+A)^-1; T = X diag(beta); P = tril(Q K^T)   (Eq. 10)
 //   k_scan_fwd   per chain x v-block  serial over chunks: W = T K, U = T V (Eq. 11); Ut = U - W S; O = Q S + P Ut; S += K^T Ut  (Eq. 8-9)
 //   k_scan_pair  per chain x v-block  backward: the state-recompute scan (stores chunk-initial S and Ut) and the reverse
-//                                     scan (dUt = P^T dO + K dS'; dS = dS' + Q^T dO - W^T dUt) as one grid
+//                                     scan (dUt = P^T dO + K dS'; dV = T^T dUt; dS = dS' + Q^T dO - W^T dUt) as one grid
 //   k_scan_fwd_save / k_scan_bwd      the forward scan that also stores what the recompute scan would, and the reverse
 //                                     scan alone, for a backward pass that keeps the forward pass's tiles
-//   k_bwd_chunk  per chunk            adjoint of Eq. 8-9 given S, dS', Ut, dUt, then adjoint of Eq. 10-11: dQ, dK, dV, dbeta
+//   k_bwd_local  per chunk            given S, dS', Ut, dV: the chunk-local rest of the adjoint, dQ, dK, dbeta (dn_chunk_local.hpp)
 //
 // State S is [d_k][d_v] (orientation of the paper's pseudocode listing), fp32 in registers.
 #pragma once
@@ -21,7 +21,7 @@ constexpr int cmax(int a, int b) { return a > b ? a : b; }
 // the plain delta rule; the gated rule; the plain rule with the layer's prologue (q, k = SiLU(x) /
 // ||SiLU(x)||_2 of section 3.3, beta = sigmoid(b) of section 2.2).  For the prologue k_wy_prep maps q
 // and k once and leaves them in the workspace for the scans, which run the plain variant on them;
-// k_bwd_chunk maps its tiles itself on the way to LDS and sends the gradients back through the map on
+// k_bwd_local reads the mapped tiles too and sends the gradients back through the map on
 // the way out, so dq, dk never reach HBM in the mapped coordinates.
 enum { VAR_PLAIN = 0, VAR_GATED = 1, VAR_PROLOGUE = 2 };
 constexpr size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
@@ -92,8 +92,7 @@ static __global__ void k_state_copy(float *dst, const float *src, long count) {
 // =============================================================================================
 // k_wy_prep: per chunk, T = (I + tril(diag(beta) K K^T, -1))^-1 diag(beta) (Eq. 10).
 // W = T K and U = T V (Eq. 11) are rebuilt from T inside the scan kernels: T is 8 KB per chunk
-// where W and U are 32 KB.  In the backward pass the inverse X itself is stored as well, so that the
-// chunk kernel does not have to invert again.
+// where W and U are 32 KB.
 template <typename T, int DK, int DV> struct PrepSmem {
     static constexpr int LD = ldc<T>(DK), LF = C + 4, LO = 40;
     // region 1: K while the two Gram products run, then the fp32 matrix that is inverted in place
@@ -178,19 +177,14 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
     });
     lds_barrier();
     tri_inverse_64_inplace<T>(sX, SM::LF, sM, sOp, SM::LO);
-    // T = X diag(beta), and X itself for the backward pass, converted and written 16 bytes at a time
+    // T = X diag(beta), converted and written 16 bytes at a time
     constexpr int VEC = El<T>::VEC, SEGS = C / VEC;
     for (int e = tid; e < C * SEGS; e += NTHR) {
         const int i = e / SEGS, j0 = (e % SEGS) * VEC;
-        alignas(16) T tv[VEC], xv[VEC];
+        alignas(16) T tv[VEC];
 #pragma unroll
-        for (int u = 0; u < VEC; ++u) {
-            const float x = sX[i * SM::LF + j0 + u];
-            tv[u] = from_f32<T>(x * sBeta[j0 + u]);
-            xv[u] = from_f32<T>(x);
-        }
+        for (int u = 0; u < VEC; ++u) tv[u] = from_f32<T>(sX[i * SM::LF + j0 + u] * sBeta[j0 + u]);
         __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(tv), reinterpret_cast<u32x4 *>((T *)p.Tm + tile * C * C + i * C + j0));
-        if (p.want_x) __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(xv), reinterpret_cast<u32x4 *>((T *)p.Xm + tile * C * C + i * C + j0));
     }
 }
 
@@ -448,7 +442,7 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
         }
         lds_barrier();
         // the previous chunk's Ut^T leaves here, sent by the chain waves, which have no output tile to form in this interval
-        if (SAVE && !loader && ic > 0 && !p.skip_ut) flush_ut(ic - 1, (int)threadIdx.x);
+        if (SAVE && !loader && ic > 0) flush_ut(ic - 1, (int)threadIdx.x);
         if (does_o) { // O = Q S + P Ut (Eq. 9); the tile waits in this wave's staging area until the next step
             if (m.ua == 0) mma<32, false, false, T, true, MB>(acc, sP, SM::LT, sUT + 32 * m.ub * SM::LT, SM::LT);
             else mma<C, false, false, T, true, MB>(acc, sP + 32 * SM::LT, SM::LT, sUT + 32 * m.ub * SM::LT, SM::LT);
@@ -472,7 +466,7 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
         if (loader && ic + 1 < nchunks) stash((ic + 1) & 1);
     }
     if (loader && nchunks > 0) {
-        if (SAVE && !p.skip_ut) flush_ut(nchunks - 1, lt);
+        if (SAVE) flush_ut(nchunks - 1, lt);
         if (OUT) flush_out(nchunks - 1);
     }
     if ((OUT || MODE == SCAN_STATE) && p.ST && m.has_s) {
@@ -592,8 +586,8 @@ __global__ __launch_bounds__(NTHR) void k_seg_combine(CombineArgs a) {
 }
 
 // scan_bwd_body: reverse over chunks, carrying dS (gradient w.r.t. the chunk-initial state):
-//   dUt = P^T dO + K dS';  dS = dS' + Q^T dO - W^T dUt
-// Per chunk it leaves dS'^T and dUt^T in the workspace (the transposed LDS copies, written out by the loader waves).
+//   dUt = P^T dO + K dS';  dV = T^T dUt;  dS = dS' + Q^T dO - W^T dUt
+// Per chunk it leaves dS'^T in the workspace (the transposed LDS copy, written out by the loader waves) and stores dV.
 template <typename T, int DK, int DV> struct ScanBwdSmem {
     static constexpr int BV = VBlock<T, DV, DK>::BV;
     static constexpr int LQ = ldn<T>(DK), LK = ldn<T>(DK), LD = ldn<T>(BV), LS = ldc<T>(DK), LT = ldc<T>(C);
@@ -603,10 +597,13 @@ template <typename T, int DK, int DV> struct ScanBwdSmem {
     static constexpr size_t oDO = oW + align16(sizeof(T) * C * LQ);
     static constexpr size_t oDST = oDO + align16(sizeof(T) * C * LD);
     static constexpr size_t oDUT = oDST + align16(sizeof(T) * BV * LS);
-    static constexpr size_t szDUT = align16(sizeof(T) * BV * LT);    // two dUt^T buffers, alternating by chunk parity
-    static constexpr size_t oT = oDUT + 2 * szDUT;
-    static constexpr size_t oPT = oT + align16(sizeof(T) * C * LT);
-    static constexpr size_t bytes = oPT + align16(sizeof(T) * C * LT);
+    static constexpr size_t oT = oDUT + align16(sizeof(T) * BV * LT);
+    static constexpr size_t szT = align16(sizeof(T) * C * LT);       // two T buffers, alternating by chunk parity
+    // P^T; in the interval after its use, the staging tiles of the chain waves for dV
+    static constexpr size_t oPT = oT + 2 * szT, oStage = oPT;
+    static constexpr size_t szPT = cmax(szT, ScanMap<DK, BV>::U_TILES * sizeof(T) * Stage<T>::ELEMS);
+    static constexpr size_t oGi = oPT + szPT;                        // gated: 1 / gamma_i, two tables, alternating as T
+    static constexpr size_t bytes = oGi + 2 * sizeof(float) * C;
 };
 
 // STATE = true: only the gradient with respect to the initial state leaves the kernel (the first pass of a backward
@@ -625,9 +622,12 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
     T *sW = reinterpret_cast<T *>(smem + SM::oW);
     T *sDO = reinterpret_cast<T *>(smem + SM::oDO);
     T *sDST = reinterpret_cast<T *>(smem + SM::oDST);
-    T *sDUT0 = reinterpret_cast<T *>(smem + SM::oDUT), *sDUT1 = reinterpret_cast<T *>(smem + SM::oDUT + SM::szDUT);
-    T *sT = reinterpret_cast<T *>(smem + SM::oT);
+    T *sDUT = reinterpret_cast<T *>(smem + SM::oDUT);
+    T *sT0 = reinterpret_cast<T *>(smem + SM::oT), *sT1 = reinterpret_cast<T *>(smem + SM::oT + SM::szT);
     T *sPT = reinterpret_cast<T *>(smem + SM::oPT);
+    T *stg = reinterpret_cast<T *>(smem + SM::oStage) + ((threadIdx.x >> 6) % ScanMap<DK, VBlock<T, DV, DK>::BV>::U_TILES) * Stage<T>::ELEMS;
+    float *sGi = reinterpret_cast<float *>(smem + SM::oGi);
+    constexpr bool kWholeLines = SM::BV * sizeof(T) >= 128; // see scan_fwd_body
     constexpr bool gated = GATED; // compile-time, so the plain kernels carry none of the gate's registers
     // the gated kernels, and those with d_k = 256, request operand fragments in smaller batches: they have no registers to spare
     constexpr int MB = GATED ? 2 : (sizeof(T) == 4 ? 2 : (DK > 128 ? 4 : 0));
@@ -658,7 +658,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         TileRegs<T, C, DK, NTL> q, k;
         TileRegs<T, C, BV, NTL> d_o;
         TileRegs<T, C, C, NTL> t;
-        float dos[TileRegs<T, C, BV, NTL>::NIT]; // gated: gamma of this lane's dO rows
+        float dos[TileRegs<T, C, BV, NTL>::NIT], gi; // gated: gamma of this lane's dO rows; one entry of the 1 / gamma table
     } r;
     auto fetch_a = [&](int ic) __attribute__((always_inline)) {
         const int nvalid = min(C, len - ic * C);
@@ -672,20 +672,21 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         const long tile = ((long)(cb + ic) * H + h);
         r.d_o.template load_aux<kAuxKeep>((const T *)p.d_o + (row0 * H + h) * DV + vb, (long)H * DV, nvalid, lt);
         r.t.template load_aux<kAuxKeep>((const T *)p.Tm + tile * C * C, C, C, lt);
-        if (gated) r.d_o.load_row_factors(r.dos, p.gam + tile * 2 * C, lt);
+        if (gated) {
+            r.d_o.load_row_factors(r.dos, p.gam + tile * 2 * C, lt);
+            if (lt < C) r.gi = p.gam[tile * 2 * C + C + lt];
+        }
     };
-    auto flush_dut = [&](int icp, int t) __attribute__((always_inline)) { // dUt^T of chunk icp, still in LDS; t = 0 .. NTL - 1
-        copy_out<T, BV, C, NTL, true>((T *)p.dUt + (((long)(cb + icp) * H + h) * DV + vb) * C, (icp & 1) ? sDUT1 : sDUT0, SM::LT, t);
-    };
-    // As in the forward scan, the loader waves issue all global traffic of a step in one burst after
-    // its first barrier: next chunk's loads, this chunk's dS'^T, the previous step's dUt^T.
-    auto stash = [&]() __attribute__((always_inline)) { // fetched tiles: registers -> LDS
+    // As in the forward scan, the loader waves issue the global traffic of a step in one burst after
+    // its first barrier: next chunk's loads, this chunk's dS'^T.
+    auto stash = [&](int par) __attribute__((always_inline)) { // fetched tiles of a chunk of parity `par`: registers -> LDS
         r.q.store(sQ, SM::LQ, lt); r.k.store(sK, SM::LK, lt);
         if (gated) r.d_o.scale_rows(r.dos); // o_i = gamma_i o~_i, so the plain rule's output gradient is gamma_i dO_i
         r.d_o.store(sDO, SM::LD, lt);
-        r.t.store(sT, SM::LT, lt);
+        r.t.store(par ? sT1 : sT0, SM::LT, lt);
+        if (gated && lt < C) sGi[par * C + lt] = r.gi;
     };
-    if (loader && nchunks > 0) { fetch_a(nchunks - 1); fetch_b(nchunks - 1); stash(); }
+    if (loader && nchunks > 0) { fetch_a(nchunks - 1); fetch_b(nchunks - 1); stash((nchunks - 1) & 1); }
     // gated: the state after the chunk is gamma_C times the plain rule's, so its gradient is scaled by
     // gamma_C on entry; every wave requests the value for the next step one step ahead
     float gCn = 1.f, gHere = 1.f; // gHere: gamma_C of the chunk of the current step
@@ -697,7 +698,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
     if (m.has_s && nchunks > 0) acc_to_lds_t<T>(sDST, SM::LS, 32 * m.sa, 32 * m.sb, dS);
     for (int ic = nchunks - 1; ic >= 0; --ic) {
         const long tile = ((long)(cb + ic) * H + h);
-        T *sDUT = (ic & 1) ? sDUT1 : sDUT0;
+        const T *sT = (ic & 1) ? sT1 : sT0;
         if (gated && ic > 0) gCn = p.gam[(tile - H) * 2 * C + C - 1]; // for the end of this step
         lds_barrier();
         if (loader && ic > 0) fetch_a(ic - 1);
@@ -742,8 +743,6 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         }
         if (m.has_s) mma<C, true, true, T, true, MB>(dS, sQ + 32 * m.sa, SM::LQ, sDO + 32 * m.sb, SM::LD); // + Q^T dO
         lds_barrier();
-        // (sent by the chain waves, as in the forward scan: the loader waves have the next chunk's tiles to move in this interval)
-        if (!STATE && !loader && ic + 1 < nchunks && !p.skip_ut) flush_dut(ic + 1, (int)threadIdx.x);
         if (m.has_s) { // - W^T dUt
             f32x16 wd = zero16();
             mma<C, true, false, T, true, MB>(wd, sW + 32 * m.sa, SM::LQ, sDUT + 32 * m.sb * SM::LT, SM::LT);
@@ -756,10 +755,18 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
                 gHere = gCn;
             }
             if (m.has_s) acc_to_lds_t<T>(sDST, SM::LS, 32 * m.sa, 32 * m.sb, dS); // dS' of the next step
-            if (loader) stash(); // see k_scan_fwd
+            if (loader) stash((ic - 1) & 1); // see k_scan_fwd
+        }
+        // dV = T^T dUt (T^T is upper triangular), formed and sent by the chain waves: the loader waves have the next chunk's
+        // tiles to move in this interval
+        if (!STATE && m.does_u) {
+            f32x16 dv = zero16();
+            if (m.ua == 0) mma<C, true, false, T, true, MB>(dv, sT, SM::LT, sDUT + 32 * m.ub * SM::LT, SM::LT);
+            else mma<32, true, false, T, true, MB>(dv, sT + 32 * SM::LT + 32, SM::LT, sDUT + 32 * m.ub * SM::LT + 32, SM::LT);
+            if (gated) acc_each(dv, [&](int rr, int, float &val) { val *= sGi[(ic & 1) * C + 32 * m.ua + rr]; }); // v_i = gamma_i v~_i
+            acc_store<T, kWholeLines>(stg, (T *)p.dv + (((long)t0 + (long)ic * C) * H + h) * DV + vb, (long)H * DV, 32 * m.ua, 32 * m.ub, min(C, len - ic * C), dv);
         }
     }
-    if (!STATE && loader && nchunks > 0 && !p.skip_ut) flush_dut(0, lt);
     if (p.dS0 && m.has_s) {
         float *dst = p.dS0 + (long)chain * DK * DV + vb;
         if (gated) dS *= gHere; // out of the first chunk's coordinates
@@ -783,9 +790,8 @@ __global__ __launch_bounds__(NTS) void k_scan_bwd(SeqMap sm, int H, Ptrs p) {
 }
 
 // =============================================================================================
-// The chunk-parallel backward kernel.  Workgroups are persistent: each walks over (chunk, head)
-// tiles with a grid stride; a tile's operands (168 KB in bf16 at d = 128) fill the whole LDS, so
-// overlap of loads and MFMA work comes from the CUs running out of step with each other.
+// The chunk-parallel backward kernel (dn_chunk_local.hpp).  Workgroups are persistent: each walks over
+// (chunk, head) tiles with a grid stride.
 constexpr int NTC = 512, NWC = 8;
 
 struct TileIter { // grid-stride walk over (global chunk id, head) tiles
@@ -809,356 +815,6 @@ __device__ inline TilePos tile_pos(const SeqMap &sm, int H, int gid, int h) {
         tp.tile = (long)(cb + ic) * H + h;
     }
     return tp;
-}
-
-// k_bwd_chunk: everything of the backward pass that is local to one chunk, given the chunk-initial
-// state S, the gradient dS' w.r.t. the state after the chunk, Ut and dUt from the two scans (all four
-// arrive transposed, [d_v][d_k] and [d_v][C], as the scans hold them in LDS):
-//   adjoint of Eq. 8-9:  dP = tril(dO Ut^T); dQ = dO S^T + dP K; dK1 = dP^T Q + Ut dS'^T; dW = -dUt S^T
-//   adjoint of Eq. 10-11, with X = (I+A)^-1 (read back from k_wy_prep), A = tril(diag(beta) G,-1), G = K K^T, dU = dUt:
-//     dX' = dW K^T + dU V^T;  dX = dX' diag(beta);  dKb = X^T dW;  dV = diag(beta) X^T dU;
-//     dA = -tril(X^T dX X^T, -1);  Ah = diag(beta) dA;
-//     dK = dK1 + diag(beta) dKb + Ah K + Ah^T K;
-//     dbeta_i = sum_m X[m][i] dX'[m][i] + sum_j dA[i][j] G[i][j].
-// dW and dK1 never leave the chip.  LDS buffers are reused as operands die; V and dS' wait in
-// registers until their buffer is free.
-template <typename T, int DK, int DV> struct ChunkSmem {
-    static constexpr int LK = ldn<T>(DK), LV = ldn<T>(DV), LT = ldn<T>(C), LF = C + 4;
-    static constexpr int LQO = ldc<T>(DK); // rows of the dq / dk matrix of the prologue variant
-    static constexpr int LU = ldc<T>(C), LSK = ldn<T>(DK); // rows of Ut^T / dUt^T ([d_v][C]) and of S^T / dS'^T ([d_v][d_k])
-    static constexpr size_t szX = sizeof(float) * C * LF, szCC = sizeof(T) * C * LT;
-    static constexpr size_t oB1 = 0;                                   // dO; V; dA o G (fp32)
-    static constexpr size_t oB2 = oB1 + align16(cmax(sizeof(T) * C * LV, szX));     // Ut^T; dW
-    static constexpr size_t oB3 = oB2 + align16(cmax(sizeof(T) * DV * LU, sizeof(T) * C * LK)); // dUt^T
-    static constexpr size_t oB4 = oB3 + align16(sizeof(T) * DV * LU);  // K
-    static constexpr size_t oB5 = oB4 + align16(sizeof(T) * C * LK);   // Q; M1^T
-    static constexpr size_t oB6 = oB5 + align16(cmax(sizeof(T) * C * LK, szCC)); // dP; dX; Ah
-    static constexpr size_t oB7 = oB6 + align16(szCC);                 // S^T; dS'^T; X
-    static constexpr size_t szB7 = cmax(sizeof(T) * DV * LSK, szCC);
-    static constexpr size_t oBeta = oB7 + align16(szB7);
-    static constexpr size_t oGam = oBeta + sizeof(float) * C;          // gated: gamma_i, then 1 / gamma_i
-    static constexpr size_t oDb = oGam + sizeof(float) * 2 * C;
-    static constexpr size_t oZ = oDb + sizeof(float) * 4 * C;          // gated: per-wave shares of <dS_C, S_C>
-    static constexpr size_t oCq = oZ + sizeof(float) * NWC;            // gated: q_i . dq_i per column block of d_k
-    static constexpr size_t oCv = oCq + sizeof(float) * (DK / 32) * C; // gated: v_i . dv_i per column block of d_v
-    static constexpr size_t oStage = align16(oCv + sizeof(float) * (DV / 32) * C);
-    static constexpr size_t bytes = oStage + NWC * sizeof(T) * Stage<T>::ELEMS;
-};
-
-template <typename T, int DK, int DV, int VAR>
-__global__ __launch_bounds__(NTC) void k_bwd_chunk(SeqMap sm, int H, Ptrs p, int chunks_total) {
-    using SM = ChunkSmem<T, DK, DV>;
-    constexpr bool GATED = VAR == VAR_GATED, PRO = VAR == VAR_PROLOGUE;
-    constexpr int KT = 2 * (DK / 32), VT = 2 * (DV / 32);        // 32 x 32 tiles of a C x DK / C x DV matrix
-    constexpr int KW = (KT + NWC - 1) / NWC, VW = (VT + NWC - 1) / NWC; // ... per wave
-    extern __shared__ __align__(16) unsigned char smem[];
-    T *sDO = reinterpret_cast<T *>(smem + SM::oB1), *sV = sDO;
-    float *sProd = reinterpret_cast<float *>(smem + SM::oB1);
-    T *sUt = reinterpret_cast<T *>(smem + SM::oB2), *sDW = sUt;
-    T *sDU = reinterpret_cast<T *>(smem + SM::oB3);
-    T *sK = reinterpret_cast<T *>(smem + SM::oB4);
-    T *sQ = reinterpret_cast<T *>(smem + SM::oB5), *sM1T = sQ;
-    T *sDP = reinterpret_cast<T *>(smem + SM::oB6), *sDX = sDP;
-    T *sS = reinterpret_cast<T *>(smem + SM::oB7);
-    T *sXn = reinterpret_cast<T *>(smem + SM::oB7); // X = (I + A)^-1 as computed by k_wy_prep
-    float *sBeta = reinterpret_cast<float *>(smem + SM::oBeta);
-    float *sGam = reinterpret_cast<float *>(smem + SM::oGam), *sGi = sGam + C;
-    float *sDb = reinterpret_cast<float *>(smem + SM::oDb);
-    float *sZ = reinterpret_cast<float *>(smem + SM::oZ);
-    float *sCq = reinterpret_cast<float *>(smem + SM::oCq), *sCv = reinterpret_cast<float *>(smem + SM::oCv);
-    // prologue variant: dq (dk) as a C x d_k matrix, in bytes that are free when it is complete, for the way back through the map
-    T *sDQ = reinterpret_cast<T *>(smem + SM::oB1), *sDK = reinterpret_cast<T *>(smem + SM::oB2);
-    static_assert(!PRO || (sizeof(T) * C * SM::LQO <= SM::oB2 - SM::oB1 && sizeof(T) * C * SM::LQO <= SM::oB3 - SM::oB2), "dq / dk staging");
-    constexpr bool gated = GATED; // compile-time, so the plain kernels carry none of the gate's registers
-    // operand fragments are requested two contraction steps at a time (measured best among 2, 4 and 8 in every variant: the
-    // LDS is the busy unit here, and long batches only hold registers)
-    constexpr int MB = 2;
-    // The thread index as the helpers see it: re-read through an empty asm at the top of every barrier interval, so that the
-    // per-lane offsets and masks derived from it are formed where they are used.  Left to itself the compiler forms all of
-    // them ahead of the tile loop and carries them through it, which costs more registers than the kernel has to spare.
-    int tq = threadIdx.x;
-    auto fresh = [&]() __attribute__((always_inline)) { tq = threadIdx.x; asm volatile("" : "+v"(tq)); };
-    const int tid = threadIdx.x;
-    // The wave number, and with it every tile offset derived from it, is recomputed per tile in the variants
-    // that are short of registers: hoisted out of the tile loop, those offsets alone would take some 90 VGPRs.
-    int wave = tid >> 6;
-    // tile number sI of this wave in a C x DK (C x DV) matrix: row block ka, column block kb
-    // (head sizes with at most four such tiles give them to waves 4..7: the first four waves own the C x C tiles, and the
-    // two kinds of products then run side by side instead of one after the other on the same waves)
-    constexpr int TSHIFT = KT <= 4 ? 4 : 0;
-    auto kt = [&](int sI) __attribute__((always_inline)) { return TSHIFT ? ((wave + TSHIFT) & (NWC - 1)) + sI * NWC : wave + sI * NWC; };
-    auto ka = [&](int sI) __attribute__((always_inline)) { return kt(sI) / (DK / 32); };
-    auto kb = [&](int sI) __attribute__((always_inline)) { return kt(sI) % (DK / 32); };
-    auto va = [&](int sI) __attribute__((always_inline)) { return kt(sI) / (DV / 32); };
-    auto vbk = [&](int sI) __attribute__((always_inline)) { return kt(sI) % (DV / 32); };
-
-    struct Regs {
-        TileRegs<T, C, DV, NTC> d_o, v;
-        TileRegs<T, DV, C, NTC> ut, dut;
-        TileRegs<T, DV, DK, NTC> s, ds;
-        TileRegs<T, C, DK, NTC> k, q;
-        TileRegs<T, C, DK, NTC> raw; // prologue variant: the pre-activations of q, then of k, for the way back through the map
-        TileRegs<T, C, C, NTC> x;
-        T beta; // kept in storage format: converting here would wait for the whole prefetch
-        // gated: gamma of this lane's dO rows, 1 / gamma of its V rows; entry tid of the chunk's table of gamma_i, 1 / gamma_i
-        float dos[TileRegs<T, C, DV, NTC>::NIT], vsc[TileRegs<T, C, DV, NTC>::NIT], gm;
-    } r;
-    // Every tile of a chunk waits in registers from the moment it is requested.  As soon as one has moved to LDS, the same
-    // registers request that tile of the workgroup's next chunk (where there is none the request is issued with every
-    // row masked: no branch around a request, so the compiler knows how many are in flight and waits for exactly the
-    // one it needs), so about one chunk's worth of loads is in flight at any time.
-    // (`live` = 0 masks every row of a request: the instruction is issued, no memory is touched)
-    auto fetch_early = [&](const TilePos &tp, int live = 1) __attribute__((always_inline)) {
-        r.d_o.load_once((const T *)p.d_o + (tp.row0 * H + tp.h) * DV, (long)H * DV, tp.nvalid * live, tq);
-        r.ut.load_once((const T *)p.Ut + tp.tile * DV * C, C, DV * live, tq);
-        r.s.load_once((const T *)p.Sc + tp.tile * DV * DK, DK, DV * live, tq);
-        r.dut.load_once((const T *)p.dUt + tp.tile * DV * C, C, DV * live, tq);
-        if (gated) r.d_o.load_row_factors(r.dos, p.gam + tp.tile * 2 * C);
-    };
-    auto fetch_kq = [&](const TilePos &tp, int live = 1) __attribute__((always_inline)) {
-        // (prologue variant: the q and k that k_wy_prep mapped and left in the workspace, in the layout of q and k)
-        r.k.load_once((const T *)(PRO ? p.Km : p.k) + (tp.row0 * H + tp.h) * DK, (long)H * DK, tp.nvalid * live, tq);
-        r.q.load_once((const T *)(PRO ? p.Qm : p.q) + (tp.row0 * H + tp.h) * DK, (long)H * DK, tp.nvalid * live, tq);
-        if (tq < C) r.beta = ((const T *)p.beta)[(tp.row0 + min(tq, tp.nvalid - 1)) * H + tp.h];
-        if (gated && tid < 2 * C) r.gm = p.gam[tp.tile * 2 * C + tid];
-    };
-    auto fetch_ds = [&](const TilePos &tp, int live = 1) __attribute__((always_inline)) { r.ds.load_once((const T *)p.dSc + tp.tile * DV * DK, DK, DV * live, tq); };
-    auto fetch_v = [&](const TilePos &tp, int live = 1) __attribute__((always_inline)) {
-        r.v.load_once((const T *)p.v + (tp.row0 * H + tp.h) * DV, (long)H * DV, tp.nvalid * live, tq);
-        if (gated) r.v.load_row_factors(r.vsc, p.gam + tp.tile * 2 * C + C);
-    };
-    auto fetch_x = [&](const TilePos &tp, int live = 1) __attribute__((always_inline)) { r.x.load_once((const T *)p.Xm + tp.tile * C * C, C, C * live, tq); };
-    auto fetch_all = [&](const TilePos &tp) __attribute__((always_inline)) { fetch_early(tp); fetch_kq(tp); fetch_ds(tp); fetch_v(tp); fetch_x(tp); };
-    auto pos_of = [&](const TileIter &it) __attribute__((always_inline)) { return it.valid() ? tile_pos(sm, H, it.gid(), it.head()) : TilePos{0, 0, 0, 0, false}; };
-
-    // Workgroups that start together stay in lockstep: every CU issues its tile's load burst at the same
-    // moment and then all of them compute while HBM idles.  When each workgroup has several tiles to
-    // walk, delay it by (blockIdx mod 4) steps of s_sleep(32), about 2K cycles each (measured best among
-    // none, 2K, 4K and 8K, and against eight steps), so the bursts of neighbouring CUs interleave with each
-    // other's MFMA phases.
-    if ((long)chunks_total * H >= 4l * gridDim.x)
-        for (int i = 0; i < (int)(blockIdx.x & 3); ++i) __builtin_amdgcn_s_sleep(32);
-    TileIter it(chunks_total, H);
-    TilePos cur = pos_of(it);
-    if (cur.ok) fetch_all(cur);
-    while (cur.ok) { // packed layout: the first chunk past the last real one ends the walk (so would every later one)
-        TileIter nx = it;
-        nx.next();
-        const TilePos np = pos_of(nx);
-        const TilePos nf = np.ok ? np : cur; // what the freed registers request (masked where there is no next chunk)
-        const int nl = np.ok ? 1 : 0;
-        asm volatile("" : "+v"(wave)); // opaque: see above
-        const int mi = (wave >> 1) & 1, ni = wave & 1; // tile of every C x C matrix, for the first four waves
-        const bool cc = wave < 4, upper = (mi == 0 && ni == 1);
-        T *stg = reinterpret_cast<T *>(smem + SM::oStage) + wave * Stage<T>::ELEMS;
-        const int nvalid = cur.nvalid, h = cur.h;
-        const long row0 = cur.row0;
-        // ---- adjoint of Eq. 8-9
-        // gated: the chunk is the plain rule on v_i / gamma_i with outputs gamma_i o~_i, so dO rows come in
-        // scaled by gamma_i, V rows by 1 / gamma_i, and dV goes out scaled by 1 / gamma_i.
-        // zp: this thread's share of <dS_C, S_C> = <dS~', S_0> + <K, Ut dS~'^T>, for the gate gradient
-        float zp = 0.f;
-        if (gated) r.d_o.scale_rows(r.dos);
-        r.d_o.store(sDO, SM::LV, tq); r.ut.store(sUt, SM::LU, tq); r.s.store(sS, SM::LSK, tq);
-        r.dut.store(sDU, SM::LU, tq);
-        fetch_early(nf, nl);
-        // prologue variant: q and k come mapped (section 3.3) from the workspace, as k_wy_prep left them; the pre-activations
-        // are fetched on the side, q's now and k's once q's gradient has left, for the way back through the map
-        r.k.store(sK, SM::LK, tq); r.q.store(sQ, SM::LK, tq);
-        if (PRO) r.raw.load_once((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid, tq); // the pre-activations of q
-        if (tq < C) {
-            float b = tq < nvalid ? to_f32(r.beta) : 0.f;
-            if (PRO) b = tq < nvalid ? sigmoid_f32(b) : 0.f; // beta = sigmoid(logit), section 2.2
-            sBeta[tq] = b;
-        }
-        if (gated && tid < 2 * C) sGam[tid] = r.gm;
-        fetch_kq(nf, nl);
-        lds_barrier(); fresh();
-        if (cc) { // dP = tril(dO Ut^T)
-            f32x16 acc = zero16();
-            if (!upper) mma<DV, false, true, T, true, MB>(acc, sDO + 32 * mi * SM::LV, SM::LV, sUt + 32 * ni, SM::LU, tq);
-            acc_each(acc, [&](int rr, int c, float &val) { if (32 * ni + c > 32 * mi + rr) val = 0.f; }, tq);
-            acc_to_lds<T>(sDP, SM::LT, 32 * mi, 32 * ni, acc, tq);
-        }
-        f32x16 dq[KW], dw[KW], dk1[KW];
-#pragma unroll
-        for (int sI = 0; sI < KW; ++sI) {
-            dq[sI] = zero16(); dw[sI] = zero16(); dk1[sI] = zero16();
-            if (kt(sI) < KT) {
-                // dO S^T and dUt S^T: the fragments of S are read once for both
-                mma_shared_b<DV, false, true, true, T, 2>(dq[sI], dw[sI], sDO + 32 * ka(sI) * SM::LV, SM::LV, sDU + 32 * ka(sI), SM::LU,
-                                                          sS + 32 * kb(sI), SM::LSK, tq);
-            }
-        }
-        lds_barrier(); fresh(); // dP visible; S is dead
-        if (gated) zp = r.ds.dot_lds(sS, SM::LSK); // <dS~', S_0>: each thread meets the S values it parked there itself
-        r.ds.store(sS, SM::LSK, tq);
-        fetch_ds(nf, nl);
-#pragma unroll
-        for (int sI = 0; sI < KW; ++sI) if (kt(sI) < KT) { // dQ += dP K
-            if (ka(sI) == 0) mma<32, false, true, T, true, MB>(dq[sI], sDP, SM::LT, sK + 32 * kb(sI), SM::LK, tq);
-            else mma<C, false, true, T, true, MB>(dq[sI], sDP + 32 * SM::LT, SM::LT, sK + 32 * kb(sI), SM::LK, tq);
-            if (gated) { // also q_i . dq_i over this tile's columns, for the gate gradient
-                acc_to_lds<T>(stg, Stage<T>::LD, 0, 0, dq[sI], tq);
-                stage_flush_dot<T>(stg, (T *)p.dq + (row0 * H + h) * DK, (long)H * DK, 32 * ka(sI), 32 * kb(sI), nvalid, sQ, SM::LK,
-                                   sCq + kb(sI) * C);
-            } else if (PRO) { // dO's bytes are free: dq is assembled there for the way back through the map
-                acc_to_lds<T>(sDQ, SM::LQO, 32 * ka(sI), 32 * kb(sI), dq[sI], tq);
-            } else {
-                acc_store<T, true>(stg, (T *)p.dq + (row0 * H + h) * DK, (long)H * DK, 32 * ka(sI), 32 * kb(sI), nvalid, dq[sI], tq);
-            }
-        }
-        lds_barrier(); fresh();
-        if (PRO) { // gradient through the feature map: dq~ = SiLU'(q~) (dq - q (q . dq)) / ||SiLU(q~)||
-            r.raw.feature_map_bwd_store(sDQ, SM::LQO, (T *)p.dq + (row0 * H + h) * DK, (long)H * DK, nvalid, tq);
-            r.raw.load_once((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, tq); // ... and those of k, for the end of the chunk
-        }
-#pragma unroll
-        for (int sI = 0; sI < KW; ++sI) if (kt(sI) < KT) { // dK1 = dP^T Q + Ut dS'^T
-            if (gated) { // <K, Ut dS~'^T>, the second half of <dS_C, S_C>, taken while dK1 holds just that product
-                mma<DV, true, true, T, true, MB>(dk1[sI], sUt + 32 * ka(sI), SM::LU, sS + 32 * kb(sI), SM::LSK, tq);
-                acc_each(dk1[sI], [&](int rr, int c, float &val) { zp += val * to_f32(sK[(32 * ka(sI) + rr) * SM::LK + 32 * kb(sI) + c]); }, tq);
-            }
-            if (ka(sI) == 1) mma<32, true, true, T, true, MB>(dk1[sI], sDP + 32 * SM::LT + 32, SM::LT, sQ + 32 * SM::LK + 32 * kb(sI), SM::LK, tq);
-            else mma<C, true, true, T, true, MB>(dk1[sI], sDP, SM::LT, sQ + 32 * kb(sI), SM::LK, tq);
-            if (!gated) mma<DV, true, true, T, true, MB>(dk1[sI], sUt + 32 * ka(sI), SM::LU, sS + 32 * kb(sI), SM::LSK, tq);
-        }
-        lds_barrier(); fresh(); // dO, Ut, Q, dP, dS' are dead
-        // ---- adjoint of Eq. 10-11
-#pragma unroll
-        for (int sI = 0; sI < KW; ++sI) if (kt(sI) < KT) { // dW = -dUt S^T, as an operand
-            acc_each(dw[sI], [&](int, int, float &val) { val = -val; }, tq);
-            acc_to_lds<T>(sDW, SM::LK, 32 * ka(sI), 32 * kb(sI), dw[sI], tq);
-        }
-        if (gated) r.v.scale_rows(r.vsc);
-        r.v.store(sV, SM::LV, tq);
-        fetch_v(nf, nl);
-        r.x.store(sXn, SM::LT, tq); // over dS', which dK1 was the last to read
-        fetch_x(nf, nl);
-        lds_barrier(); fresh();
-        f32x16 g = zero16(), dxp = zero16();
-        if (cc && !upper) {
-            mma<DK, false, false, T, true, MB>(g, sK + 32 * mi * SM::LK, SM::LK, sK + 32 * ni * SM::LK, SM::LK, tq);
-            mma<DK, false, false, T, true, MB>(dxp, sDW + 32 * mi * SM::LK, SM::LK, sK + 32 * ni * SM::LK, SM::LK, tq);
-            mma<DV, true, false, T, true, MB>(dxp, sDU + 32 * mi, SM::LU, sV + 32 * ni * SM::LV, SM::LV, tq);
-        }
-        acc_each(g, [&](int rr, int c, float &val) { if (32 * ni + c >= 32 * mi + rr) val = 0.f; }, tq); // strictly lower G
-        // (dX goes to dP's bytes, dead since dK1: no barrier between the product and its scaled copy)
-        if (cc) { // dbeta part 1 (column sums of X o dX'), dX = dX' diag(beta)
-            float part = 0.f;
-            acc_each(dxp, [&](int rr, int c, float &val) {
-                const int i = 32 * mi + rr, j = 32 * ni + c;
-                part += to_f32(sXn[i * SM::LT + j]) * val;
-                val *= sBeta[j];
-            }, tq);
-            sDb[(2 * mi + ((tq & 63) >> 5)) * C + 32 * ni + (tq & 31)] = part; // summed in a fixed order at the end
-            acc_to_lds<T>(sDX, SM::LT, 32 * mi, 32 * ni, dxp, tq);
-        }
-        lds_barrier(); fresh();
-        f32x16 m1 = zero16(); // M1 = dX X^T
-        if (cc) mma<C, false, false, T, true, MB>(m1, sDX + 32 * mi * SM::LT, SM::LT, sXn + 32 * ni * SM::LT, SM::LT, tq);
-#pragma unroll
-        for (int sI = 0; sI < KW; ++sI) if (kt(sI) < KT) { // dKb = X^T dW (X^T is upper triangular)
-            f32x16 dKb = zero16();
-            if (ka(sI) == 1) mma<32, true, true, T, true, MB>(dKb, sXn + 32 * SM::LT + 32, SM::LT, sDW + 32 * SM::LK + 32 * kb(sI), SM::LK, tq);
-            else mma<C, true, true, T, true, MB>(dKb, sXn, SM::LT, sDW + 32 * kb(sI), SM::LK, tq);
-            acc_each(dKb, [&](int rr, int, float &val) { val *= sBeta[32 * ka(sI) + rr]; }, tq);
-            dk1[sI] += dKb; // dK1 + diag(beta) dKb
-        }
-#pragma unroll
-        for (int sI = 0; sI < VW; ++sI) if (kt(sI) < VT) { // dV = diag(beta) X^T dU
-            f32x16 acc = zero16();
-            if (va(sI) == 1) mma<32, true, false, T, true, MB>(acc, sXn + 32 * SM::LT + 32, SM::LT, sDU + 32 * vbk(sI) * SM::LU + 32, SM::LU, tq);
-            else mma<C, true, false, T, true, MB>(acc, sXn, SM::LT, sDU + 32 * vbk(sI) * SM::LU, SM::LU, tq);
-            acc_each(acc, [&](int rr, int, float &val) {
-                val *= gated ? sBeta[32 * va(sI) + rr] * sGi[32 * va(sI) + rr] : sBeta[32 * va(sI) + rr];
-            }, tq);
-            if (gated) { // also (v_i / gamma_i) . dv_i over this tile's columns
-                acc_to_lds<T>(stg, Stage<T>::LD, 0, 0, acc, tq);
-                stage_flush_dot<T>(stg, (T *)p.dv + (row0 * H + h) * DV, (long)H * DV, 32 * va(sI), 32 * vbk(sI), nvalid, sV, SM::LV,
-                                   sCv + vbk(sI) * C);
-            } else {
-                acc_store<T, true>(stg, (T *)p.dv + (row0 * H + h) * DV, (long)H * DV, 32 * va(sI), 32 * vbk(sI), nvalid, acc, tq);
-            }
-        }
-        if (cc) acc_to_lds_t<T>(sM1T, SM::LT, 32 * mi, 32 * ni, m1, tq); // Q's bytes: dead since dK1 (the inverse scratch, too)
-        lds_barrier(); fresh(); // dX is dead
-        if (cc) { // dA = -tril(X^T M1, -1); dA o G to sProd; Ah = diag(beta) dA into sDX
-            f32x16 acc = zero16();
-            if (!upper) {
-                if (mi == 1) mma<32, true, false, T, true, MB>(acc, sXn + 32 * SM::LT + 32, SM::LT, sM1T + 32 * ni * SM::LT + 32, SM::LT, tq);
-                else mma<C, true, false, T, true, MB>(acc, sXn, SM::LT, sM1T + 32 * ni * SM::LT, SM::LT, tq);
-            }
-            const int l31 = tq & 31, hh = (tq & 63) >> 5;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int i = 32 * mi + 8 * (e >> 2) + 4 * hh + (e & 3), j = 32 * ni + l31;
-                const float da = j < i ? -acc[e] : 0.f;
-                sProd[i * SM::LF + j] = da * g[e];
-                sDX[i * SM::LT + j] = from_f32<T>(sBeta[i] * da);
-            }
-        }
-        if (gated) { // this wave's share of <dS_C, S_C>, summed in a fixed order after the barrier
-            float zw = zp;
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) zw += __shfl_xor(zw, d);
-            if ((tq & 63) == 0) sZ[wave] = zw;
-        }
-        lds_barrier(); fresh();
-#pragma unroll
-        for (int sI = 0; sI < KW; ++sI) if (kt(sI) < KT) { // dK = dK1 + diag(beta) dKb + Ah K + Ah^T K; Ah is strictly lower triangular
-            if (ka(sI) == 0) mma<32, false, true, T, true, MB>(dk1[sI], sDX, SM::LT, sK + 32 * kb(sI), SM::LK, tq);
-            else mma<C, false, true, T, true, MB>(dk1[sI], sDX + 32 * SM::LT, SM::LT, sK + 32 * kb(sI), SM::LK, tq);
-            if (ka(sI) == 1) mma<32, true, true, T, true, MB>(dk1[sI], sDX + 32 * SM::LT + 32, SM::LT, sK + 32 * SM::LK + 32 * kb(sI), SM::LK, tq);
-            else mma<C, true, true, T, true, MB>(dk1[sI], sDX, SM::LT, sK + 32 * kb(sI), SM::LK, tq);
-            if (PRO) { // dW's bytes are free
-                acc_to_lds<T>(sDK, SM::LQO, 32 * ka(sI), 32 * kb(sI), dk1[sI], tq);
-            } else {
-                acc_store<T, true>(stg, (T *)p.dk + (row0 * H + h) * DK, (long)H * DK, 32 * ka(sI), 32 * kb(sI), nvalid, dk1[sI], tq);
-            }
-        }
-        if (gated && tid < C) {
-            // Gate gradient.  o_t is linear in q_t and in the state, so the sensitivity to a rescaling of the
-            // state at token j can be read off the other gradients:
-            //     dg_j = <dS_C, S_C> + sum_{i = j .. end of the chunk} (q_i . dq_i - v_i . dv_i).
-            // Thread t takes token C - 1 - t; an inclusive scan over t is the suffix sum over tokens.
-            const int tok = C - 1 - tid;
-            float c = 0.f;
-#pragma unroll
-            for (int b = 0; b < DK / 32; ++b) c += sCq[b * C + tok];
-            float cv = 0.f;
-#pragma unroll
-            for (int b = 0; b < DV / 32; ++b) cv += sCv[b * C + tok];
-            c -= cv * sGam[tok]; // v_i . dv_i = gamma_i (v_i / gamma_i) . dv_i
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const float up = __shfl_up(c, d);
-                if (tid >= d) c += up;
-            }
-            const float z = ((sZ[0] + sZ[1]) + (sZ[2] + sZ[3])) + ((sZ[4] + sZ[5]) + (sZ[6] + sZ[7]));
-            if (tok < nvalid) p.dg[(row0 + tok) * H + h] = c + z;
-        }
-        if (tq < 256) { // dbeta = column sums from part 1 + row sums of dA o G
-            const int i = tq >> 2, seg = tq & 3;
-            float sum = 0.f;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) sum += sProd[i * SM::LF + seg * 16 + j];
-            sum += __shfl_xor(sum, 1);
-            sum += __shfl_xor(sum, 2);
-            if (seg == 0 && i < nvalid) {
-                float db = sum + ((sDb[i] + sDb[C + i]) + (sDb[2 * C + i] + sDb[3 * C + i]));
-                if (PRO) db *= sBeta[i] * (1.f - sBeta[i]); // through the sigmoid
-                p.dbeta[(row0 + i) * H + h] = db;
-            }
-        }
-        if (PRO) { // dk is assembled: back through the feature map, as for dq
-            lds_barrier(); fresh();
-            r.raw.feature_map_bwd_store(sDK, SM::LQO, (T *)p.dk + (row0 * H + h) * DK, (long)H * DK, nvalid, tq);
-        }
-        lds_barrier(); fresh(); // every buffer is free for the next tile
-        it = nx;
-        cur = np;
-    }
 }
 
 } // namespace dn

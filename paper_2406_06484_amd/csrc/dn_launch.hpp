@@ -6,8 +6,7 @@
 
 #include "dn_host.hpp"
 #include "dn_kernels.hpp"
-#include "dn_chunk_wide.hpp"
-#include "dn_chunk_stream.hpp"
+#include "dn_chunk_local.hpp"
 
 namespace dn {
 
@@ -56,20 +55,6 @@ static inline int launch_offsets(const Problem &pb) {
     return 0;
 }
 
-// Head sizes whose chunk operands do not fit the LDS at once take the streaming chunk kernel.
-template <typename T, int DK, int DV> constexpr bool kChunkFits = ChunkSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup;
-template <typename T, int DK, int DV> constexpr bool kWideBwd = !kChunkFits<T, DK, DV> && sizeof(T) == 2 && DK % 128 == 0 && DV % 64 == 0;
-// The plain delta rule in bf16 at head sizes whose resident tiles fit can take the chunk kernel that rebuilds Ut and dUt
-// from the streamed blocks of S and dS' (k_bwd_stream; option DN_OPT_STREAMED_CHUNK_KERNEL); the scans then skip those two stores.
-template <typename T, int DK, int DV> constexpr bool stream_fits() {
-    if constexpr (sizeof(T) == 2 && DK % 64 == 0 && DV % 64 == 0 && DK <= 128 && DV <= 128) return StreamSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup;
-    else return false;
-}
-template <typename T, int DK, int DV> constexpr bool kStreamBwd = stream_fits<T, DK, DV>();
-static inline bool use_stream_kernel(bool compiled, const Ptrs &p) { return compiled && p.streamed && !p.g && !p.pro; }
-// whether the backward pass is compiled for this head size
-template <typename T, int DK, int DV> constexpr bool kHasBwd = kChunkFits<T, DK, DV> || kWideBwd<T, DK, DV>;
-
 template <typename T, int DK, int DV> size_t max_lds_bytes() {
     static_assert(PrepSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_wy_prep LDS");
     static_assert(ScanFwdSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_scan_fwd LDS");
@@ -77,22 +62,10 @@ template <typename T, int DK, int DV> size_t max_lds_bytes() {
     size_t m = PrepSmem<T, DK, DV>::bytes;
     if (ScanFwdSmem<T, DK, DV>::bytes > m) m = ScanFwdSmem<T, DK, DV>::bytes;
     if (ScanBwdSmem<T, DK, DV>::bytes > m) m = ScanBwdSmem<T, DK, DV>::bytes;
-    if constexpr (kStreamBwd<T, DK, DV>)
-        if (StreamSmem<T, DK, DV>::bytes > m) m = StreamSmem<T, DK, DV>::bytes;
-    if constexpr (kChunkFits<T, DK, DV>) {
-        if (ChunkSmem<T, DK, DV>::bytes > m) m = ChunkSmem<T, DK, DV>::bytes;
-    } else {
-        static_assert(WideSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_bwd_chunk_wide LDS");
-        if (WideSmem<T, DK, DV>::bytes > m) m = WideSmem<T, DK, DV>::bytes;
-    }
+    static_assert(LocalSmem<T, DK, DV>::bytes_pro <= kLdsPerWorkgroup && LocalSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_bwd_local LDS");
+    if (LocalSmem<T, DK, DV>::bytes > m) m = LocalSmem<T, DK, DV>::bytes;
+    if (LocalSmem<T, DK, DV>::bytes_pro > m) m = LocalSmem<T, DK, DV>::bytes_pro;
     return m;
-}
-
-// forward-only instantiations (head sizes whose backward tiles do not fit)
-template <typename T, int DK, int DV> size_t max_lds_fwd_bytes() {
-    static_assert(PrepSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_wy_prep LDS");
-    static_assert(ScanFwdSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_scan_fwd LDS");
-    return PrepSmem<T, DK, DV>::bytes > ScanFwdSmem<T, DK, DV>::bytes ? PrepSmem<T, DK, DV>::bytes : ScanFwdSmem<T, DK, DV>::bytes;
 }
 
 // launches kernel<T, DK, DV, variant> for the variant the pointers ask for.  The scans know two variants
@@ -102,17 +75,9 @@ template <typename T, int DK, int DV> size_t max_lds_fwd_bytes() {
         if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED>), grid, nthreads, lds, __VA_ARGS__);            \
         else DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PLAIN>), grid, nthreads, lds, __VA_ARGS__);                \
     } while (0)
-#define DN_LAUNCH_VAR(kernel, grid, nthreads, lds, ...)                                                     \
-    do {                                                                                                    \
-        if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED>), grid, nthreads, lds, __VA_ARGS__);            \
-        else if (p.pro) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PROLOGUE>), grid, nthreads, lds, __VA_ARGS__);  \
-        else DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PLAIN>), grid, nthreads, lds, __VA_ARGS__);                \
-    } while (0)
-
 // what the scans see: with the prologue, the mapped q and k in the workspace
-static inline Ptrs scan_ptrs(const Ptrs &p, bool stream_compiled) {
+static inline Ptrs scan_ptrs(const Ptrs &p) {
     Ptrs ps = p;
-    ps.skip_ut = use_stream_kernel(stream_compiled, p);
     if (p.pro) { ps.q = p.Qm; ps.k = p.Km; ps.pro = 0; }
     return ps;
 }
@@ -131,7 +96,7 @@ template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs 
     const dim3 gchunk(pb.chunks_ub, pb.H);
     dim3 gchain(chain_grid(pb.N * pb.H, VBlock<T, DV, DK>::NV));
     DN_LAUNCH((k_wy_prep<T, DK, DV>), gchunk, (PrepSmem<T, DK, DV>::bytes), sm, pb.H, p);
-    Ptrs ps = scan_ptrs(p, kStreamBwd<T, DK, DV>);
+    Ptrs ps = scan_ptrs(p);
     if constexpr (DK == DV && DK <= 128) {
         // few long chains: cut the sequences into G segments, get every segment's start state from a first pass
         // (k_scan_state, k_seg_combine), then run the scan below over the segments side by side
@@ -147,13 +112,8 @@ template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs 
             gchain = gseg;
         }
     }
-    if constexpr (kHasBwd<T, DK, DV>) {
-        if (pb.save) {
-            DN_LAUNCH_SCAN(k_scan_fwd_save, gchain, NTS, (ScanFwdSmem<T, DK, DV>::bytes), sm, pb.H, ps);
-            return 0;
-        }
-    }
-    DN_LAUNCH_SCAN(k_scan_fwd, gchain, NTS, (ScanFwdSmem<T, DK, DV>::bytes), sm, pb.H, ps);
+    if (pb.save) DN_LAUNCH_SCAN(k_scan_fwd_save, gchain, NTS, (ScanFwdSmem<T, DK, DV>::bytes), sm, pb.H, ps);
+    else DN_LAUNCH_SCAN(k_scan_fwd, gchain, NTS, (ScanFwdSmem<T, DK, DV>::bytes), sm, pb.H, ps);
     return 0;
 }
 
@@ -162,7 +122,7 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
     const SeqMap sm = make_map(pb);
     if (int e = launch_offsets(pb)) return e;
     const dim3 gchunk(pb.chunks_ub, pb.H), gchain(chain_grid(pb.N * pb.H, VBlock<T, DV, DK>::NV));
-    Ptrs ps = scan_ptrs(p, kStreamBwd<T, DK, DV>);
+    Ptrs ps = scan_ptrs(p);
     constexpr size_t lds_pair = cmax(ScanFwdSmem<T, DK, DV>::bytes, ScanBwdSmem<T, DK, DV>::bytes);
     // few long chains: the scans run over G segments of the sequences side by side (see k_scan_state)
     int G = 1;
@@ -196,38 +156,16 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
         DN_LAUNCH_SCAN(k_scan_pair, gpair, NTS, lds_pair, sm, pb.H, ps, (int)gchain.x);
     }
     if (pb.chunks_ub) {
-        const long tiles = (long)pb.chunks_ub * pb.H;
-        const dim3 gpers((unsigned)(tiles < pb.num_cus ? tiles : pb.num_cus)); // one persistent workgroup per CU
-        if constexpr (kWideBwd<T, DK, DV>) {
-            if (p.pro) { // on the mapped q, k; then dq and dk go back through the feature map, in place
-                DN_LAUNCH_NT((k_bwd_chunk_wide<T, DK, DV, VAR_PROLOGUE>), gpers, NTC, (WideSmem<T, DK, DV>::bytes), sm, pb.H, ps, pb.chunks_ub);
-                const long rows = (long)(pb.cu ? pb.L : (long)pb.N * pb.L) * pb.H;
-                const dim3 grows((unsigned)((rows + C - 1) / C));
-                constexpr size_t lds_map = sizeof(T) * C * ldn<T>(DK);
-                DN_LAUNCH((k_feature_map_bwd<T, DK>), grows, lds_map, (const T *)p.q, (T *)p.dq, rows);
-                DN_LAUNCH((k_feature_map_bwd<T, DK>), grows, lds_map, (const T *)p.k, (T *)p.dk, rows);
-            } else if (p.g) { // the kernel leaves <dS_C, S_C> per chunk; the per-token terms of the gate gradient follow
-                DN_LAUNCH_NT((k_bwd_chunk_wide<T, DK, DV, VAR_GATED>), gpers, NTC, (WideSmem<T, DK, DV>::bytes), sm, pb.H, p, pb.chunks_ub);
-                DN_LAUNCH((k_gate_grad<T, DK, DV>), gchunk, 0, sm, pb.H, p);
-            } else {
-                DN_LAUNCH_NT((k_bwd_chunk_wide<T, DK, DV, VAR_PLAIN>), gpers, NTC, (WideSmem<T, DK, DV>::bytes), sm, pb.H, p, pb.chunks_ub);
-            }
-        } else {
-            if constexpr (kStreamBwd<T, DK, DV>) {
-                if (use_stream_kernel(true, p)) {
-                    DN_LAUNCH_NT((k_bwd_stream<T, DK, DV>), gpers, NTC, (StreamSmem<T, DK, DV>::bytes), sm, pb.H, p, pb.chunks_ub);
-                    return 0;
-                }
-            }
-            DN_LAUNCH_VAR(k_bwd_chunk, gpers, NTC, (ChunkSmem<T, DK, DV>::bytes), sm, pb.H, p, pb.chunks_ub);
-        }
+        using SM = LocalSmem<T, DK, DV>;
+        const long tiles = (long)pb.chunks_ub * pb.H, slots = (long)pb.num_cus * SM::WPC;
+        const dim3 gpers((unsigned)(tiles < slots ? tiles : slots)); // persistent: as many workgroups as the chip holds
+        if (p.g) DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_GATED>), gpers, NTC, SM::bytes, sm, pb.H, p, pb.chunks_ub);
+        else if (p.pro) DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_PROLOGUE>), gpers, NTC, SM::bytes_pro, sm, pb.H, p, pb.chunks_ub);
+        else DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_PLAIN>), gpers, NTC, SM::bytes, sm, pb.H, p, pb.chunks_ub);
     }
     return 0;
 }
 
-#define DN_INSTANTIATE_FWD(T, DK, DV)                                    \
-    template int run_fwd<T, DK, DV>(const Problem &, const Ptrs &);      \
-    template size_t max_lds_fwd_bytes<T, DK, DV>();
 #define DN_INSTANTIATE(T, DK, DV)                                        \
     template int run_fwd<T, DK, DV>(const Problem &, const Ptrs &);      \
     template int run_bwd<T, DK, DV>(const Problem &, const Ptrs &);      \
