@@ -496,95 +496,83 @@ __device__ inline void copy_out(T *dst, const T *src, int ld, int t) {
 }
 // ---------------------------------------------------------------------------------------------
 // X = (I + A)^{-1} for a 64x64 strictly-lower-triangular A (section 3.2: the inverse of the unit
-// lower-triangular matrix of Eq. 10 by forward substitution), done blockwise and in place.
-// On entry sX (fp32, leading dimension ld) holds the
-// strictly lower triangular A with zeros elsewhere; on exit it holds X = (I + A)^{-1}.
-// Blocked forward substitution: the eight 8x8 diagonal blocks are solved column by column (16
-// lanes of every wavefront), then 2x2 block merges X21 = -X22 (A21 X11) double the block size
-// 8 -> 16 -> 32 on the vector ALU in fp32 and 32 -> 64 on the matrix cores with operands of type T.
-// sM: 512 floats of scratch (may share its bytes with sOp: it is dead before sOp is written).  sOp: 3 x 32 x LO elements of
-// type T, LO >= 32 + 8.  Ends with a barrier.
-template <typename T, int NT = NTHR>
-__device__ inline void tri_inverse_64_inplace(float *sX, int ld, float *sM, T *sOp, int LO) {
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const bool act = tid < 256; // the fp32 stages are laid out for 256 threads; extra waves only join the barriers
-    if (act && lane < 16) {
-        const int b = (2 * wave + (lane >> 3)) * 8, j = lane & 7;
-        float x[8];
+// lower-triangular matrix of Eq. 10 by forward substitution), blockwise, fp32 throughout.
+// On entry sX (fp32, leading dimension ld, a multiple of 4) holds A in its three lower 32 x 32 blocks, the strictly lower
+// part of the diagonal ones with zeros above; the upper right block need not hold anything.  On exit the diagonal blocks hold
+// those of X, and the UPPER RIGHT block holds X21, the lower left block of X (whose own place is still being read as A21 by
+// the other wave when a wave writes its columns; X itself is zero up there).
+// The four 16x16 diagonal blocks are solved column by column by one wavefront (a lane per column), then 2x2 block merges
+// X21 = -X22 (A21 X11) double the block size 16 -> 32 -> 64 on the fp32 matrix cores (16x16x4).  The contraction index of a
+// merge is walked so that lane group g = lane >> 4 feeds k = 4 g + i in step i: an A operand is then 16 bytes of one row, and
+// the accumulator of the inner product is, register by register, the B operand of the outer one, so it never leaves the
+// registers.  That keeps the inverse at about 150 LDS instructions and one barrier (before its last stage, which
+// two wavefronts share); merging on the vector ALU from LDS took about 800 and seven, and bound the whole prep kernel.
+// Ends with a barrier.
+__device__ inline f32x4 mfma16(f32x4 acc, float a, float b) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0); }
+// acc += A B for 16x16 blocks in LDS
+__device__ inline void mma16_lds(f32x4 &acc, const float *A, const float *B, int ld) {
+    const int lane = threadIdx.x & 63, j = lane & 15, g4 = 4 * (lane >> 4);
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(A + j * ld + g4);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 4; ++i) acc = mfma16(acc, a[i], B[(g4 + i) * ld + j]);
+}
+// acc += A M for a 16x16 block in LDS and one in accumulator layout
+__device__ inline void mma16_acc(f32x4 &acc, const float *A, const f32x4 &M, int ld) {
+    const int lane = threadIdx.x & 63, j = lane & 15, g4 = 4 * (lane >> 4);
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(A + j * ld + g4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = mfma16(acc, a[i], M[i]);
+}
+__device__ inline void acc16_store_neg(float *dst, const f32x4 &acc, int ld) {
+    const int lane = threadIdx.x & 63, j = lane & 15, g4 = 4 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dst[(g4 + i) * ld + j] = -acc[i];
+}
+__device__ inline void tri_inverse_64(float *sX, int ld) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (wave == 0) {
+        float *blk = sX + (lane >> 4) * 16 * (ld + 1);
+        const int j = lane & 15;
+        float x[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
             float s = (i == j) ? 1.f : 0.f;
 #pragma unroll
-            for (int m = 0; m < i; ++m) s -= sX[(b + i) * ld + b + m] * x[m];
-            x[i] = (i < j) ? 0.f : s;
-        }
+            for (int m0 = 0; m0 < i; m0 += 4) {
+                const f32x4 a = *reinterpret_cast<const f32x4 *>(blk + i * ld + m0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) sX[(b + i) * ld + b + j] = x[i];
-    }
-    lds_barrier();
-    { // 8 -> 16: four merges, one output element per thread
-        const int m = (tid >> 6) & 3, i = (tid >> 3) & 7, j = tid & 7, r0 = 16 * m + 8, c0 = 16 * m;
-        float s = 0.f;
-        if (act) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) s += sX[(r0 + i) * ld + c0 + k] * sX[(c0 + k) * ld + c0 + j];
-            sM[tid] = s;
-        }
-        lds_barrier();
-        if (act) {
-            s = 0.f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) s += sX[(r0 + i) * ld + r0 + k] * sM[(m << 6) + k * 8 + j];
-            sX[(r0 + i) * ld + c0 + j] = -s;
-        }
-        lds_barrier();
-    }
-    { // 16 -> 32: two merges, two output elements per thread
-        const int m = (tid >> 7) & 1, i = (tid >> 3) & 15, j = 2 * (tid & 7), r0 = 32 * m + 16, c0 = 32 * m;
-        float s0 = 0.f, s1 = 0.f;
-        if (act) {
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const float a = sX[(r0 + i) * ld + c0 + k];
-                s0 += a * sX[(c0 + k) * ld + c0 + j];
-                s1 += a * sX[(c0 + k) * ld + c0 + j + 1];
+                for (int m = m0; m < m0 + 4 && m < i; ++m) s -= a[m - m0] * x[m];
             }
-            sM[(m << 8) + i * 16 + j] = s0;
-            sM[(m << 8) + i * 16 + j + 1] = s1;
+            x[i] = s;
         }
-        lds_barrier();
-        if (act) {
-            s0 = s1 = 0.f;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const float a = sX[(r0 + i) * ld + r0 + k];
-                s0 += a * sM[(m << 8) + k * 16 + j];
-                s1 += a * sM[(m << 8) + k * 16 + j + 1];
-            }
-            sX[(r0 + i) * ld + c0 + j] = -s0;
-            sX[(r0 + i) * ld + c0 + j + 1] = -s1;
+        for (int i = 0; i < 16; ++i) blk[i * ld + j] = x[i];
+        // 16 -> 32 (LDS accesses of one wavefront stay in order: no barrier)
+        f32x4 m0 = {0.f, 0.f, 0.f, 0.f}, m1 = m0, y0 = m0, y1 = m0;
+        float *d0 = sX, *d1 = sX + 32 * (ld + 1);
+        mma16_lds(m0, d0 + 16 * ld, d0, ld);
+        mma16_lds(m1, d1 + 16 * ld, d1, ld);
+        mma16_acc(y0, d0 + 16 * (ld + 1), m0, ld);
+        mma16_acc(y1, d1 + 16 * (ld + 1), m1, ld);
+        acc16_store_neg(d0 + 16 * ld, y0, ld);
+        acc16_store_neg(d1 + 16 * ld, y1, ld);
+    }
+    lds_barrier();
+    if (wave < 2) { // 32 -> 64: wave n forms columns 16 n .. 16 n + 15
+        const int n = wave;
+        const float *A21 = sX + 32 * ld, *X22 = sX + 32 * (ld + 1);
+        f32x4 m0 = {0.f, 0.f, 0.f, 0.f}, m1 = m0, y0 = m0, y1 = m0;
+        if (n == 0) { // X11 is lower triangular
+            mma16_lds(m0, A21, sX, ld);
+            mma16_lds(m1, A21 + 16 * ld, sX, ld);
         }
-        lds_barrier();
-    }
-    // 32 -> 64 on the matrix cores: operands A21, X11^T, X22 and (later) M^T, each 32 x LO
-    T *oA = sOp, *oX11T = sOp + 32 * LO, *oX22 = sOp + 64 * LO, *oMT = oA; // M^T takes A21's place: one wave reads the one, then writes the other
-    for (int e = tid; e < 32 * 32; e += NT) {
-        const int i = e >> 5, k = e & 31;
-        oA[i * LO + k] = from_f32<T>(sX[(32 + i) * ld + k]);
-        oX11T[k * LO + i] = from_f32<T>(sX[i * ld + k]);
-        oX22[i * LO + k] = from_f32<T>(sX[(32 + i) * ld + 32 + k]);
-    }
-    lds_barrier();
-    f32x16 acc = zero16();
-    if (wave == 0) {
-        mma<32, false, false, T>(acc, oA, LO, oX11T, LO); // M = A21 X11
-        acc_to_lds_t<T>(oMT, LO, 0, 0, acc);
-    }
-    lds_barrier();
-    if (wave == 0) {
-        acc = zero16();
-        mma<32, false, false, T>(acc, oX22, LO, oMT, LO); // X22 M
-        acc_each(acc, [&](int r, int c, float &v) { sX[(32 + r) * ld + c] = -v; });
+        mma16_lds(m0, A21 + 16, sX + 16 * ld + 16 * n, ld);
+        mma16_lds(m1, A21 + 16 * ld + 16, sX + 16 * ld + 16 * n, ld);
+        mma16_acc(y0, X22, m0, ld); // so is X22
+        mma16_acc(y1, X22 + 16 * ld, m0, ld);
+        mma16_acc(y1, X22 + 16 * (ld + 1), m1, ld);
+        acc16_store_neg(sX + 32 + 16 * n, y0, ld);
+        acc16_store_neg(sX + 16 * ld + 32 + 16 * n, y1, ld);
     }
     lds_barrier();
 }

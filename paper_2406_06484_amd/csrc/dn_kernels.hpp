@@ -93,37 +93,37 @@ static __global__ void k_state_copy(float *dst, const float *src, long count) {
 // k_wy_prep: per chunk, T = (I + tril(diag(beta) K K^T, -1))^-1 diag(beta) (Eq. 10).
 // W = T K and U = T V (Eq. 11) are rebuilt from T inside the scan kernels: T is 8 KB per chunk
 // where W and U are 32 KB.
+// A chain of short serial stages per workgroup: what counts is how many are resident (eight per CU; K unpadded beyond 16 bytes a
+// row, the inverse in K's bytes and without scratch) and the LDS instructions of the inverse.  Against the form with the merges
+// on the vector ALU (six per CU, chunks fastest): 16 384 tokens of width 2048, d = 128 34 -> 25 us (100 MB, 4 TB/s), d = 64
+// 59 -> 43 us, d = 256 30 -> 24 us.  The prologue variant (two tiles mapped on the way, five per CU) takes 67 us for 300 MB as before.
 template <typename T, int DK, int DV> struct PrepSmem {
-    static constexpr int LD = ldc<T>(DK), LF = C + 4, LO = 40;
-    // region 1: K while the two Gram products run, then the fp32 matrix that is inverted in place
+    static constexpr int LD = ldc<T>(DK), LF = C + 4;
+    // K while the Gram product runs, then the fp32 matrix that is inverted in place
     static constexpr size_t oK = 0, oX = 0;
-    static constexpr size_t sz1 = cmax(sizeof(T) * C * LD, sizeof(float) * C * LF);
-    // region 2: the operands of the inverse's MFMA stage
-    static constexpr size_t oOp = oX + align16(sz1);
-    static constexpr size_t sz2 = cmax(sizeof(T) * 3 * 32 * LO, sizeof(float) * 512); // ... and, before that, the merges' scratch
-    static constexpr size_t oM = oOp;
-    static constexpr size_t oBeta = oOp + align16(sz2);
+    static constexpr size_t oBeta = align16(cmax(sizeof(T) * C * LD, sizeof(float) * C * LF));
     static constexpr size_t bytes = oBeta + sizeof(float) * C;
 };
 
-// (bf16 up to d_k = 128: held to the registers of six workgroups per CU, which is what its LDS allows; the other
-// instantiations would spill under that cap)
-template <typename T, int DK> struct PrepWaves { static constexpr int lo = (sizeof(T) == 2 && DK <= 128) ? 6 : 1, hi = (sizeof(T) == 2 && DK <= 128) ? 6 : 8; };
-template <typename T, int DK, int DV>
-__global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<T, DK>::lo, PrepWaves<T, DK>::hi))) void k_wy_prep(SeqMap sm, int H, Ptrs p) {
+// (bf16 up to d_k = 128: held to the registers of eight workgroups per CU, which is what its LDS allows, five with the
+// prologue's registers; the other instantiations would spill under such a cap)
+template <typename T, int DK, bool PRO> struct PrepWaves { static constexpr int lo = (sizeof(T) == 2 && DK <= 128) ? (PRO ? 5 : 8) : 1, hi = lo > 1 ? lo : 8; };
+template <typename T, int DK, int DV, bool PRO>
+__global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<T, DK, PRO>::lo, PrepWaves<T, DK, PRO>::hi))) void k_wy_prep(SeqMap sm, int H, Ptrs p) {
     using SM = PrepSmem<T, DK, DV>;
     extern __shared__ __align__(16) unsigned char smem[];
     T *sK = reinterpret_cast<T *>(smem + SM::oK);
     float *sX = reinterpret_cast<float *>(smem + SM::oX);
-    T *sOp = reinterpret_cast<T *>(smem + SM::oOp);
-    float *sM = reinterpret_cast<float *>(smem + SM::oM);
     float *sBeta = reinterpret_cast<float *>(smem + SM::oBeta);
 
+    // heads run fastest: the workgroups in flight then read whole rows of k between them (a head's part of a row is 128 to 512
+    // bytes; many of those at a stride of a row is a pattern that HBM serves at about half its rate)
     int n, ic;
-    if (!sm.chunk(blockIdx.x, n, ic)) return;
+    const int h = (int)(blockIdx.x % (unsigned)H);
+    if (!sm.chunk((int)(blockIdx.x / (unsigned)H), n, ic)) return;
     int t0, len, cb;
     sm.seq(n, t0, len, cb);
-    const int h = blockIdx.y, tid = threadIdx.x, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = tid >> 6;
     const int nvalid = min(C, len - ic * C);
     const long row0 = (long)t0 + (long)ic * C;
     const long tile = ((long)(cb + ic) * H + h);
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
     {
         TileRegs<T, C, DK> kr;
         kr.template load_aux<kAuxKeep>((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, threadIdx.x);
-        if (p.pro) { // prologue variant: q and k arrive before the feature map of section 3.3
+        if constexpr (PRO) { // prologue variant: q and k arrive before the feature map of section 3.3
             TileRegs<T, C, DK> qr;
             qr.load((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid);
             float inv[TileRegs<T, C, DK>::NIT];
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
     }
     if (tid < C) {
         float b = tid < nvalid ? to_f32(((const T *)p.beta)[(row0 + tid) * H + h]) : 0.f;
-        if (p.pro) b = tid < nvalid ? sigmoid_f32(b) : 0.f; // ... and beta before the sigmoid
+        if (PRO) b = tid < nvalid ? sigmoid_f32(b) : 0.f; // ... and beta before the sigmoid
         sBeta[tid] = b;
     }
     if (p.g && tid < C) {
@@ -169,21 +169,24 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
     }
     lds_barrier();
     f32x16 g = zero16();
-    if (!upper) mma<DK, false, false, T>(g, sK + 32 * mi * SM::LD, SM::LD, sK + 32 * ni * SM::LD, SM::LD); // K K^T
+    if (!upper) mma<DK, false, false, T, true, sizeof(T) == 2 ? 2 : 0>(g, sK + 32 * mi * SM::LD, SM::LD, sK + 32 * ni * SM::LD, SM::LD); // K K^T
     lds_barrier(); // K is dead from here on; its bytes take the fp32 matrix
-    acc_each(g, [&](int r, int c, float &val) { // A = tril(diag(beta) K K^T, -1)
-        const int i = 32 * mi + r, j = 32 * ni + c;
-        sX[i * SM::LF + j] = j < i ? sBeta[i] * val : 0.f;
-    });
+    if (!upper)
+        acc_each(g, [&](int r, int c, float &val) { // A = tril(diag(beta) K K^T, -1)
+            const int i = 32 * mi + r, j = 32 * ni + c;
+            sX[i * SM::LF + j] = j < i ? sBeta[i] * val : 0.f;
+        });
     lds_barrier();
-    tri_inverse_64_inplace<T>(sX, SM::LF, sM, sOp, SM::LO);
-    // T = X diag(beta), converted and written 16 bytes at a time
+    tri_inverse_64(sX, SM::LF);
+    // T = X diag(beta), converted and written 16 bytes at a time (X21 stands in the upper right block)
     constexpr int VEC = El<T>::VEC, SEGS = C / VEC;
     for (int e = tid; e < C * SEGS; e += NTHR) {
         const int i = e / SEGS, j0 = (e % SEGS) * VEC;
+        const float *x = sX + (i >= 32 && j0 < 32 ? (i - 32) * SM::LF + 32 + j0 : i * SM::LF + j0);
+        const bool zero = i < 32 && j0 >= 32;
         alignas(16) T tv[VEC];
 #pragma unroll
-        for (int u = 0; u < VEC; ++u) tv[u] = from_f32<T>(sX[i * SM::LF + j0 + u] * sBeta[j0 + u]);
+        for (int u = 0; u < VEC; ++u) tv[u] = from_f32<T>(zero ? 0.f : x[u] * sBeta[j0 + u]);
         __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(tv), reinterpret_cast<u32x4 *>((T *)p.Tm + tile * C * C + i * C + j0));
     }
 }

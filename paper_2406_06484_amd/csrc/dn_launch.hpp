@@ -82,6 +82,13 @@ static inline Ptrs scan_ptrs(const Ptrs &p) {
     return ps;
 }
 
+template <typename T, int DK, int DV> int launch_prep(const Problem &pb, const SeqMap &sm, const Ptrs &p) {
+    const dim3 grid((unsigned)pb.chunks_ub * (unsigned)pb.H); // (rows * H < 2^31)
+    if (p.pro) DN_LAUNCH((k_wy_prep<T, DK, DV, true>), grid, (PrepSmem<T, DK, DV>::bytes), sm, pb.H, p);
+    else DN_LAUNCH((k_wy_prep<T, DK, DV, false>), grid, (PrepSmem<T, DK, DV>::bytes), sm, pb.H, p);
+    return 0;
+}
+
 template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs &p) {
     if (pb.N == 0) return 0;
     if (pb.chunks_ub == 0) { // no tokens at all: the state passes through (section 2.2: nothing is written)
@@ -93,9 +100,8 @@ template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs 
     }
     SeqMap sm = make_map(pb);
     if (int e = launch_offsets(pb)) return e;
-    const dim3 gchunk(pb.chunks_ub, pb.H);
     dim3 gchain(chain_grid(pb.N * pb.H, VBlock<T, DV, DK>::NV));
-    DN_LAUNCH((k_wy_prep<T, DK, DV>), gchunk, (PrepSmem<T, DK, DV>::bytes), sm, pb.H, p);
+    if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;
     Ptrs ps = scan_ptrs(p);
     if constexpr (DK == DV && DK <= 128) {
         // few long chains: cut the sequences into G segments, get every segment's start state from a first pass
@@ -121,7 +127,7 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
     if (pb.N == 0) return 0;
     const SeqMap sm = make_map(pb);
     if (int e = launch_offsets(pb)) return e;
-    const dim3 gchunk(pb.chunks_ub, pb.H), gchain(chain_grid(pb.N * pb.H, VBlock<T, DV, DK>::NV));
+    const dim3 gchain(chain_grid(pb.N * pb.H, VBlock<T, DV, DK>::NV));
     Ptrs ps = scan_ptrs(p);
     constexpr size_t lds_pair = cmax(ScanFwdSmem<T, DK, DV>::bytes, ScanBwdSmem<T, DK, DV>::bytes);
     // few long chains: the scans run over G segments of the sequences side by side (see k_scan_state)
@@ -139,7 +145,7 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
                 ps.dST = p.dSout; ps.dS0 = nullptr;
                 DN_LAUNCH_SCAN(k_scan_bwd, gseg, NTS, (ScanBwdSmem<T, DK, DV>::bytes), sg, pb.H, ps);
             } else {
-                DN_LAUNCH((k_wy_prep<T, DK, DV>), gchunk, (PrepSmem<T, DK, DV>::bytes), sm, pb.H, p);
+                if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;
                 DN_LAUNCH_SCAN(k_scan_state, dim3(3 * gseg.x), NTS, lds_pair, sg, pb.H, ps, (int)gseg.x);
                 const CombineArgs ca{p.Mseg, p.Nseg, p.S0, p.Sin, nullptr, p.Rseg, p.dST, p.dSout, p.dS0, G, pb.H, 0};
                 DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 2), NTHR, (CombineSmem<DK, DV>::bytes), ca);
@@ -150,7 +156,7 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
     } else if (pb.save) { // T, X, Ut and the chunk-initial states are the forward pass's: only the reverse scan is left
         DN_LAUNCH_SCAN(k_scan_bwd, gchain, NTS, (ScanBwdSmem<T, DK, DV>::bytes), sm, pb.H, ps);
     } else {
-        if (pb.chunks_ub) DN_LAUNCH((k_wy_prep<T, DK, DV>), gchunk, (PrepSmem<T, DK, DV>::bytes), sm, pb.H, p);
+        if (pb.chunks_ub) if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;
         // both scans of the backward pass as one grid: reverse scan first, recompute scan behind it
         const dim3 gpair(2 * gchain.x);
         DN_LAUNCH_SCAN(k_scan_pair, gpair, NTS, lds_pair, sm, pb.H, ps, (int)gchain.x);
