@@ -215,7 +215,149 @@ __global__ __launch_bounds__(256) void k_recurrent_fwd(RecArgs a) {
     }
 }
 
+// A few tokens on a kept state (generation): the state is read and written once and that is the time, so the lanes are laid
+// out for the state's rows instead of for the token loop.  Lane l = 16 * rb + 8 * cp + e holds columns 4e .. 4e + 3 of the
+// wave's 32 and, of the quarter rb of the rows, those with r % 4 in {2 cp, 2 cp + 1}: every access is 16 bytes per lane and
+// whole 128-byte lines, four loads for every sixteen of k_recurrent_fwd, and no work is done for tokens that are not there (its
+// block of eight is unrolled).  Each of the four partial sums over a quarter of the rows, and the order in which they are
+// added, is that of k_recurrent_fwd, so a call per token and one call for all of them return the same bits.
+// Waves are independent (no barrier): with few chains a workgroup is one wave, so that they spread over the chip.
+// Bound by HBM: 512 states of 128 x 128 (67 MB) for one token 12.3 us, 5.4 TB/s, what a copy reaches; in k_recurrent_fwd 17.6 us.
+constexpr int kDecCols = 32;
+// The most tokens a call may have to come here.  A token costs this kernel about 0.7 us (its sums are spread over twice as many
+// lanes) and k_recurrent_fwd next to nothing up to its block of eight, so few chains decide: 16 chains of d = 128 in bf16 take
+// 3.3, 4.0, 4.7, 5.4, 6.2 us for 1 to 5 tokens against 5.4, 5.5, 5.6, 5.8, 5.9; 128 chains in fp32 5.7, 6.3, 7.3 us against 6.4,
+// 6.5, 6.8.  At d_k = 256 the lanes hold 128 values of the state: 2304 chains in bf16 245, 249, 254 us against 253, 253, 252, and
+// in fp32 the two are level (33.0 and 32.5 us for 256 chains), so the loop keeps it.
+template <typename T, int DK> constexpr int kDecTokens = sizeof(T) == 2 ? (DK > 128 ? 2 : 4) : (DK > 128 ? 0 : 2);
+
+template <typename T> struct DecQuad; // four neighbouring elements of v or o
+template <> struct DecQuad<float> { typedef float4 raw; };
+template <> struct DecQuad<rbf16> { typedef uint2 raw; };
+__device__ inline void dec_unpack(const float4 &w, float (&f)[4]) { f[0] = w.x; f[1] = w.y; f[2] = w.z; f[3] = w.w; }
+__device__ inline void dec_unpack(const uint2 &w, float (&f)[4]) {
+    f[0] = __uint_as_float(w.x << 16); f[1] = __uint_as_float(w.x & 0xffff0000u);
+    f[2] = __uint_as_float(w.y << 16); f[3] = __uint_as_float(w.y & 0xffff0000u);
+}
+// sum over the lanes l and l ^ 8 (a rotation by 8 inside each row of 16 lanes), then over the quarters of the rows
+__device__ inline float dec_sum(float x) {
+    const int o = __builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x128, 0xf, 0xf, false); // row_ror:8
+    return rec_sum4(x + __uint_as_float((unsigned)o));
+}
+
+template <typename T, int DK, bool GATED>
+__global__ __launch_bounds__(256) void k_decode_fwd(RecArgs a) {
+    constexpr int R = DK / 4, NI = R / 4;                    // rows per quarter; row pairs per lane
+    constexpr int ROWW = DK * (int)sizeof(T) / 16, WT = 2 * ROWW; // 16-byte words of one k (or q) row; of a token's k and q
+    constexpr int EPW = 16 / (int)sizeof(T);
+    constexpr int NW = (kDecTokens<T, DK> * WT + 63) / 64;           // words per lane for all tokens
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int e = lane & 7, cp = (lane >> 3) & 1, rb = lane >> 4;
+    const int chain = blockIdx.x, n = chain / a.H, h = chain - n * a.H;
+    const int col0 = (blockIdx.y * (blockDim.x >> 6) + wave) * kDecCols, col = col0 + 4 * e;
+    const int H = a.H, DV = a.DV, len = a.L;
+    if (col0 >= DV) return;
+    const long t0 = (long)n * len;
+    float *kq = reinterpret_cast<float *>(smem) + wave * (len * 2 * DK); // this wave's: per token k and q as fp32
+
+    uint4 w[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const int x = i * 64 + lane, tok = x / WT, y = x % WT;
+        if (tok < len) w[i] = reinterpret_cast<const uint4 *>((const T *)(y < ROWW ? a.k : a.q) + ((t0 + tok) * H + h) * DK)[y % ROWW];
+    }
+    typename DecQuad<T>::raw vr[kDecTokens<T, DK>];
+    T br[kDecTokens<T, DK>];
+    float gr[kDecTokens<T, DK>];
+#pragma unroll
+    for (int t = 0; t < kDecTokens<T, DK>; ++t)
+        if (t < len) {
+            vr[t] = *reinterpret_cast<const typename DecQuad<T>::raw *>((const T *)a.v + ((t0 + t) * H + h) * DV + col);
+            br[t] = ((const T *)a.beta)[(t0 + t) * H + h];
+            gr[t] = GATED ? a.g[(t0 + t) * H + h] : 0.f;
+        }
+    float S[2 * NI][4]; // rows rb R + 4 i + 2 cp + {0, 1}
+    const long base = ((long)chain * DK + rb * R + 2 * cp) * DV + col;
+#pragma unroll
+    for (int i = 0; i < 2 * NI; ++i) {
+        const float4 x = a.S0 ? *reinterpret_cast<const float4 *>(a.S0 + base + (long)(4 * (i >> 1) + (i & 1)) * DV) : make_float4(0.f, 0.f, 0.f, 0.f);
+        S[i][0] = x.x; S[i][1] = x.y; S[i][2] = x.z; S[i][3] = x.w;
+    }
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const int x = i * 64 + lane;
+        if (x / WT < len) {
+            float f[EPW];
+            RowRegs<T, EPW> r;
+            r.w[0] = w[i];
+            r.unpack(f);
+#pragma unroll
+            for (int u = 0; u < EPW; u += 4) *reinterpret_cast<float4 *>(kq + x * EPW + u) = make_float4(f[u], f[u + 1], f[u + 2], f[u + 3]);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); // (parked by all lanes, read by all lanes, of the same wave)
+#pragma unroll
+    for (int t = 0; t < kDecTokens<T, DK>; ++t) {
+        if (t >= len) break;
+        const float *kt = kq + t * 2 * DK + rb * R + 2 * cp, *qt = kt + DK;
+        float v[4], u[4], out[4];
+        dec_unpack(vr[t], v);
+        const float bt = rec_to_f32(br[t]), at = GATED ? __expf(gr[t]) : 1.f;
+        float d[2][4] = {};
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const float2 kk = *reinterpret_cast<const float2 *>(kt + 4 * i);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { d[0][c] = fmaf(S[2 * i][c], kk.x, d[0][c]); d[1][c] = fmaf(S[2 * i + 1][c], kk.y, d[1][c]); }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) u[c] = bt * (v[c] - at * dec_sum(d[0][c] + d[1][c]));
+        float o[2][4] = {};
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const float2 kk = *reinterpret_cast<const float2 *>(kt + 4 * i), qq = *reinterpret_cast<const float2 *>(qt + 4 * i);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (GATED) { S[2 * i][c] *= at; S[2 * i + 1][c] *= at; }
+                S[2 * i][c] = fmaf(kk.x, u[c], S[2 * i][c]);
+                o[0][c] = fmaf(S[2 * i][c], qq.x, o[0][c]);
+                S[2 * i + 1][c] = fmaf(kk.y, u[c], S[2 * i + 1][c]);
+                o[1][c] = fmaf(S[2 * i + 1][c], qq.y, o[1][c]);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) out[c] = dec_sum(o[0][c] + o[1][c]);
+        if (lane < 8) {
+            alignas(16) T ov[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) rec_store(ov + c, out[c]);
+            *reinterpret_cast<typename DecQuad<T>::raw *>((T *)a.o + ((t0 + t) * H + h) * DV + col) = *reinterpret_cast<const typename DecQuad<T>::raw *>(ov);
+        }
+    }
+    if (a.ST) {
+#pragma unroll
+        for (int i = 0; i < 2 * NI; ++i)
+            *reinterpret_cast<float4 *>(a.ST + base + (long)(4 * (i >> 1) + (i & 1)) * DV) = make_float4(S[i][0], S[i][1], S[i][2], S[i][3]);
+    }
+}
+
+template <typename T, int DK> static int launch_decode(const RecArgs &a, hipStream_t stream) {
+    const int slices = a.DV / kDecCols;
+    const int waves = slices * (long)a.N * a.H <= 2048 ? 1 : (slices < 4 ? slices : 4);
+    const dim3 grid(a.N * a.H, (slices + waves - 1) / waves);
+    const int lds = waves * a.L * 2 * DK * (int)sizeof(float); // at most 32 KB
+    void *args[] = {const_cast<RecArgs *>(&a)};
+    const void *fn = a.g ? reinterpret_cast<const void *>(k_decode_fwd<T, DK, true>) : reinterpret_cast<const void *>(k_decode_fwd<T, DK, false>);
+    prof_begin("k_decode_fwd", stream);
+    const hipError_t e = hipLaunchKernel(fn, grid, dim3(64 * waves), args, lds, stream);
+    prof_end(stream);
+    return (int)e;
+}
+
 template <typename T, int DK> static int launch_rec(const RecArgs &a, hipStream_t stream) {
+    if constexpr (kDecTokens<T, DK> > 0)
+        if (!a.cu && a.L >= 1 && a.L <= kDecTokens<T, DK> && a.DV % kDecCols == 0) return launch_decode<T, DK>(a, stream);
     const dim3 grid(a.N * a.H, (a.DV + 4 * kRecCols - 1) / (4 * kRecCols));
     constexpr int lds = 4 * 2 * RecStage<T, DK>::bytes; // four waves, two buffers each
     static_assert(lds <= 160 * 1024, "staging fits the LDS");

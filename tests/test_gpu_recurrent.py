@@ -91,3 +91,28 @@ def test_recurrent_full_size_configs():
     # the benchmark shape and the packed variable-length batch, every element against the oracle
     check(make_config(1), "recurrent cfg1")
     check(make_config(4), "recurrent cfg4")
+
+
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("dtype,dk,dv,B,H", [("f32", 32, 32, 1, 1), ("f32", 64, 160, 3, 5), ("f32", 256, 64, 2, 3), ("bf16", 32, 96, 2, 3),
+                                             ("bf16", 64, 64, 70, 16), ("bf16", 128, 128, 33, 16), ("bf16", 128, 288, 1, 3), ("bf16", 256, 256, 9, 8)])
+def test_decode_kernel_equals_token_loop(dtype, dk, dv, B, H, gated):
+    # a few dense tokens take the kernel laid out for the state; the same tokens with cu_seqlens take the token loop, and both
+    # form the same sums in the same order
+    for L in (1, 2, 3, 4, 5):
+        inp = make_inputs(600 + L, B=B, L=L, H=H, dk=dk, dv=dv, dtype=dtype, with_initial_state=True)
+        d = dev_inputs(inp)
+        g = torch.log(0.5 + 0.5 * torch.rand(B, L, H, generator=torch.Generator().manual_seed(L))).cuda()
+        call = lambda args, S, **kw: (dn.deltanet_gated_recurrent_fwd(*args, kw.pop("g"), S, **kw) if gated
+                                      else dn.deltanet_recurrent_fwd(*args, S, **{k: x for k, x in kw.items() if k != "g"}))
+        dense = [d[n] for n in ("q", "k", "v", "beta")]
+        flat = [x.reshape(B * L, *x.shape[2:]) for x in dense]
+        cu = torch.arange(B + 1, dtype=torch.int32, device="cuda") * L
+        for S0 in (d["S0"], None):
+            o_p, S_p = call(flat, S0, cu_seqlens=cu, g=g.reshape(B * L, H))
+            o_d, S_d = call(dense, S0, g=g)
+            assert torch.equal(o_d.reshape(o_p.shape), o_p) and torch.equal(S_d, S_p), (L, S0 is None)
+        S = d["S0"].clone()
+        o_i, _ = call(dense, S, g=g, final_state=S) # the state updated where it stands
+        o_p, S_p = call(flat, d["S0"], cu_seqlens=cu, g=g.reshape(B * L, H))
+        assert torch.equal(o_i.reshape(o_p.shape), o_p) and torch.equal(S, S_p), L
