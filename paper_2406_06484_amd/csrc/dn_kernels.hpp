@@ -192,7 +192,7 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
 }
 
 // =============================================================================================
-// The two chain-serial kernels.  One workgroup of 8 wavefronts owns one chain and BV = 64 columns
+// The two chain-serial kernels.  One workgroup of 8 wavefronts owns one chain and BV = 64 columns (32: see VBlock)
 // of the state; the state lives in accumulator registers, one 32 x 32 tile per wave.
 // Waves 0..3 own the Ut / dUt tiles of the dependent chain; waves 4..7 have the lighter work between
 // barriers and double as loaders: they request the next chunk's tiles and send most of the results
@@ -209,6 +209,8 @@ template <typename T, int DV, int DK> struct VBlock {
     static constexpr int WANT = (sizeof(T) == 2 && DK <= 128) ? DN_VBLOCK_COLS : 32;
     static constexpr int BV = DV < WANT ? DV : WANT;
     static constexpr int NV = DV / BV;
+    // what the scans of few chains take instead (see narrow_blocks in dn_launch.hpp)
+    static constexpr int NARROW = BV == 64 ? 32 : BV;
 };
 
 __device__ inline bool chain_of_block(int bid, int nchains, int nv, int &chain, int &vbi) {
@@ -240,8 +242,7 @@ template <int DK, int BV> struct ScanMap {
 // backward pass will not recompute) does both; SCAN_STATE writes only the final state (the first pass of a
 // forward pass that is split over segments of the sequence, see k_scan_state).
 enum { SCAN_OUT = 0, SCAN_STORE = 1, SCAN_BOTH = 2, SCAN_STATE = 3 };
-template <typename T, int DK, int DV> struct ScanFwdSmem {
-    static constexpr int BV = VBlock<T, DV, DK>::BV;
+template <typename T, int DK, int DV, int BV> struct ScanFwdSmem {
     static constexpr int LQ = ldc<T>(DK), LK = ldn<T>(DK), LV = ldn<T>(BV), LS = ldc<T>(DK), LT = ldc<T>(C);
     static constexpr size_t oQ = 0;
     static constexpr size_t oK = oQ + align16(sizeof(T) * C * LQ);
@@ -264,13 +265,13 @@ template <typename T, int DK, int DV> struct ScanFwdSmem {
     static constexpr size_t bytes = kMerge ? oGam2 + sizeof(float) * 2 * C : bytes1;
 };
 
-template <typename T, int DK, int DV, int MODE, int VAR>
+template <typename T, int DK, int DV, int MODE, int VAR, int BV>
 __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptrs &p, int bid) {
-    using SM = ScanFwdSmem<T, DK, DV>;
+    using SM = ScanFwdSmem<T, DK, DV, BV>;
     static_assert(VAR != VAR_PROLOGUE, "the scans read q and k already mapped");
     constexpr bool GATED = VAR == VAR_GATED;
     constexpr bool OUT = MODE == SCAN_OUT || MODE == SCAN_BOTH, SAVE = MODE == SCAN_STORE || MODE == SCAN_BOTH;
-    constexpr int BV = SM::BV, NV = VBlock<T, DV, DK>::NV;
+    constexpr int NV = DV / BV;
     using Map = ScanMap<DK, BV>;
     constexpr int NWT = (Map::W_TILES + 3) / 4; // W tiles per chain wave
     extern __shared__ __align__(16) unsigned char smem[];
@@ -477,16 +478,16 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
         acc_each(S, [&](int r, int c, float &val) { dst[(long)(32 * m.sa + r) * DV + 32 * m.sb + c] = val; });
     }
 }
-template <typename T, int DK, int DV, int VAR>
+template <typename T, int DK, int DV, int VAR, int BV>
 __global__ __launch_bounds__(NTS) void k_scan_fwd(SeqMap sm, int H, Ptrs p) {
-    scan_fwd_body<T, DK, DV, SCAN_OUT, VAR>(sm, H, p, blockIdx.x);
+    scan_fwd_body<T, DK, DV, SCAN_OUT, VAR, BV>(sm, H, p, blockIdx.x);
 }
-template <typename T, int DK, int DV, int VAR>
+template <typename T, int DK, int DV, int VAR, int BV>
 __global__ __launch_bounds__(NTS) void k_scan_fwd_save(SeqMap sm, int H, Ptrs p) {
-    scan_fwd_body<T, DK, DV, SCAN_BOTH, VAR>(sm, H, p, blockIdx.x);
+    scan_fwd_body<T, DK, DV, SCAN_BOTH, VAR, BV>(sm, H, p, blockIdx.x);
 }
 
-template <typename T, int DK, int DV, int VAR, bool STATE>
+template <typename T, int DK, int DV, int VAR, bool STATE, int BV>
 __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptrs &p, int bid);
 
 // A forward pass over few, long chains leaves most CUs idle.  Every stretch of a chain acts on the state as an
@@ -507,18 +508,18 @@ __global__ __launch_bounds__(NTS) void k_scan_state(SeqMap sm, int H, Ptrs p, in
     const int part = (int)blockIdx.x / half, bid = (int)blockIdx.x - part * half;
     if (part == 2) {
         ps.dST = nullptr; ps.dS0 = p.Rseg;
-        scan_bwd_body<T, DK, DV, VAR, true>(sm, H, ps, bid);
+        scan_bwd_body<T, DK, DV, VAR, true, VBlock<T, DV, DK>::BV>(sm, H, ps, bid);
         return;
     }
     if (part == 0) { ps.unit_state = 0; ps.ST = p.Nseg; }
     else { ps.unit_state = 1; ps.ST = p.Mseg; }
-    scan_fwd_body<T, DK, DV, SCAN_STATE, VAR>(sm, H, ps, bid);
+    scan_fwd_body<T, DK, DV, SCAN_STATE, VAR, VBlock<T, DV, DK>::BV>(sm, H, ps, bid);
 }
 template <typename T, int DK, int DV, int VAR>
 __global__ __launch_bounds__(NTS) void k_scan_bwd_state(SeqMap sm, int H, Ptrs p) {
     Ptrs ps = p;
     ps.dST = nullptr; ps.dS0 = p.Rseg;
-    scan_bwd_body<T, DK, DV, VAR, true>(sm, H, ps, blockIdx.x);
+    scan_bwd_body<T, DK, DV, VAR, true, VBlock<T, DV, DK>::BV>(sm, H, ps, blockIdx.x);
 }
 
 // S_in(0) = the caller's initial state (or zero); S_in(g + 1) = M_g S_in(g) + N_g; the state after the last segment is
@@ -591,8 +592,7 @@ __global__ __launch_bounds__(NTHR) void k_seg_combine(CombineArgs a) {
 // scan_bwd_body: reverse over chunks, carrying dS (gradient w.r.t. the chunk-initial state):
 //   dUt = P^T dO + K dS';  dV = T^T dUt;  dS = dS' + Q^T dO - W^T dUt
 // Per chunk it leaves dS'^T in the workspace (the transposed LDS copy, written out by the loader waves) and stores dV.
-template <typename T, int DK, int DV> struct ScanBwdSmem {
-    static constexpr int BV = VBlock<T, DV, DK>::BV;
+template <typename T, int DK, int DV, int BV> struct ScanBwdSmem {
     static constexpr int LQ = ldn<T>(DK), LK = ldn<T>(DK), LD = ldn<T>(BV), LS = ldc<T>(DK), LT = ldc<T>(C);
     static constexpr size_t oQ = 0;
     static constexpr size_t oK = oQ + align16(sizeof(T) * C * LQ);
@@ -611,12 +611,12 @@ template <typename T, int DK, int DV> struct ScanBwdSmem {
 
 // STATE = true: only the gradient with respect to the initial state leaves the kernel (the first pass of a backward
 // pass that is split over segments of the sequence).
-template <typename T, int DK, int DV, int VAR, bool STATE>
+template <typename T, int DK, int DV, int VAR, bool STATE, int BV>
 __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptrs &p, int bid) {
-    using SM = ScanBwdSmem<T, DK, DV>;
+    using SM = ScanBwdSmem<T, DK, DV, BV>;
     static_assert(VAR != VAR_PROLOGUE, "the scans read q and k already mapped");
     constexpr bool GATED = VAR == VAR_GATED;
-    constexpr int BV = SM::BV, NV = VBlock<T, DV, DK>::NV;
+    constexpr int NV = DV / BV;
     using Map = ScanMap<DK, BV>;
     constexpr int NWT = (Map::W_TILES + 3) / 4; // W tiles per chain wave
     extern __shared__ __align__(16) unsigned char smem[];
@@ -628,9 +628,9 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
     T *sDUT = reinterpret_cast<T *>(smem + SM::oDUT);
     T *sT0 = reinterpret_cast<T *>(smem + SM::oT), *sT1 = reinterpret_cast<T *>(smem + SM::oT + SM::szT);
     T *sPT = reinterpret_cast<T *>(smem + SM::oPT);
-    T *stg = reinterpret_cast<T *>(smem + SM::oStage) + ((threadIdx.x >> 6) % ScanMap<DK, VBlock<T, DV, DK>::BV>::U_TILES) * Stage<T>::ELEMS;
+    T *stg = reinterpret_cast<T *>(smem + SM::oStage) + ((threadIdx.x >> 6) % ScanMap<DK, BV>::U_TILES) * Stage<T>::ELEMS;
     float *sGi = reinterpret_cast<float *>(smem + SM::oGi);
-    constexpr bool kWholeLines = SM::BV * sizeof(T) >= 128; // see scan_fwd_body
+    constexpr bool kWholeLines = BV * sizeof(T) >= 128; // see scan_fwd_body
     constexpr bool gated = GATED; // compile-time, so the plain kernels carry none of the gate's registers
     // the gated kernels, and those with d_k = 256, request operand fragments in smaller batches: they have no registers to spare
     constexpr int MB = GATED ? 2 : (sizeof(T) == 4 ? 2 : (DK > 128 ? 4 : 0));
@@ -781,15 +781,15 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
 // scan needs T; the reverse scan needs T and P^T), so the first half of the grid runs the reverse
 // scan and the second half the recompute scan: a CU picks up one of each with no kernel boundary
 // in between.  `half` = workgroups per scan.
-template <typename T, int DK, int DV, int VAR>
+template <typename T, int DK, int DV, int VAR, int BV>
 __global__ __launch_bounds__(NTS) void k_scan_pair(SeqMap sm, int H, Ptrs p, int half) {
-    if ((int)blockIdx.x < half) scan_bwd_body<T, DK, DV, VAR, false>(sm, H, p, blockIdx.x);
-    else scan_fwd_body<T, DK, DV, SCAN_STORE, VAR>(sm, H, p, blockIdx.x - half);
+    if ((int)blockIdx.x < half) scan_bwd_body<T, DK, DV, VAR, false, BV>(sm, H, p, blockIdx.x);
+    else scan_fwd_body<T, DK, DV, SCAN_STORE, VAR, BV>(sm, H, p, blockIdx.x - half);
 }
 // the reverse scan alone, for a backward pass that finds the forward scan's tiles already in the workspace
-template <typename T, int DK, int DV, int VAR>
+template <typename T, int DK, int DV, int VAR, int BV>
 __global__ __launch_bounds__(NTS) void k_scan_bwd(SeqMap sm, int H, Ptrs p) {
-    scan_bwd_body<T, DK, DV, VAR, false>(sm, H, p, blockIdx.x);
+    scan_bwd_body<T, DK, DV, VAR, false, BV>(sm, H, p, blockIdx.x);
 }
 
 // =============================================================================================

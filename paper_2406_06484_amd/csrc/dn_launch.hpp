@@ -57,11 +57,13 @@ static inline int launch_offsets(const Problem &pb) {
 
 template <typename T, int DK, int DV> size_t max_lds_bytes() {
     static_assert(PrepSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_wy_prep LDS");
-    static_assert(ScanFwdSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_scan_fwd LDS");
-    static_assert(ScanBwdSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_scan_bwd LDS");
+    static_assert(ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes <= kLdsPerWorkgroup, "k_scan_fwd LDS");
+    static_assert(ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes <= kLdsPerWorkgroup, "k_scan_bwd LDS");
+    static_assert(ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::NARROW>::bytes <= ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes &&
+                  ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::NARROW>::bytes <= ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes, "narrow blocks");
     size_t m = PrepSmem<T, DK, DV>::bytes;
-    if (ScanFwdSmem<T, DK, DV>::bytes > m) m = ScanFwdSmem<T, DK, DV>::bytes;
-    if (ScanBwdSmem<T, DK, DV>::bytes > m) m = ScanBwdSmem<T, DK, DV>::bytes;
+    if (ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes > m) m = ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes;
+    if (ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes > m) m = ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes;
     static_assert(LocalSmem<T, DK, DV>::bytes_pro <= kLdsPerWorkgroup && LocalSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_bwd_local LDS");
     if (LocalSmem<T, DK, DV>::bytes > m) m = LocalSmem<T, DK, DV>::bytes;
     if (LocalSmem<T, DK, DV>::bytes_pro > m) m = LocalSmem<T, DK, DV>::bytes_pro;
@@ -75,6 +77,24 @@ template <typename T, int DK, int DV> size_t max_lds_bytes() {
         if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED>), grid, nthreads, lds, __VA_ARGS__);            \
         else DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PLAIN>), grid, nthreads, lds, __VA_ARGS__);                \
     } while (0)
+// ... with BV state columns per workgroup
+#define DN_LAUNCH_SCAN_BV(kernel, grid, BV, lds, ...)                                                       \
+    do {                                                                                                    \
+        if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED, BV>), grid, NTS, lds, __VA_ARGS__);             \
+        else DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PLAIN, BV>), grid, NTS, lds, __VA_ARGS__);                 \
+    } while (0)
+// Scans of few chains (`wide` = workgroups of the grid with the ordinary column blocks) run with blocks half as wide: the
+// workgroups still fit the chip at once, and the step of each, whose length is the longest of a chain of products, is shorter.
+// The tiles are formed by the same products in the same order, so the results are the same bits.
+// Measured, d = 128, 16 heads, wide and narrow: forward pass of 1 x 1000 tokens 43.6 and 38.8 us, 4 x 2000 (the line, half the
+// chip) 84.7 and 75.8, training step 97.8 and 86.7, 250.8 and 232.8; beyond the line two rounds (8 x 2048: 104 and 155 us).
+// With d_k = 64 a forward pass that keeps no tiles has its line at a quarter of the chip: between the two it gains 3 us, but a
+// backward pass behind it loses more (its output, in half lines, is written back then): 4 x 2000 of 32 heads, gated, forward and
+// backward pass with recomputation 271 and 277 us.  Segmented scans (sm.N > pb.N) keep the ordinary blocks: little to
+// gain in their short steps (1 x 1024: forward pass 52.8 and 51.1 us, training step 112.2 and 113.0).
+static inline bool narrow_blocks(const Problem &pb, const SeqMap &sm, unsigned wide, int share) {
+    return sm.N == pb.N && (long)wide * share <= pb.num_cus;
+}
 // what the scans see: with the prologue, the mapped q and k in the workspace
 static inline Ptrs scan_ptrs(const Ptrs &p) {
     Ptrs ps = p;
@@ -111,15 +131,43 @@ template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs 
             sm.N = pb.N * G; sm.L = pb.L / G; sm.ncd = sm.L / C;
             const dim3 gseg(chain_grid(sm.N * pb.H, VBlock<T, DV, DK>::NV));
             const dim3 gstate(2 * gseg.x);
-            DN_LAUNCH_SCAN(k_scan_state, gstate, NTS, (ScanFwdSmem<T, DK, DV>::bytes), sm, pb.H, ps, (int)gseg.x);
+            DN_LAUNCH_SCAN(k_scan_state, gstate, NTS, (ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes), sm, pb.H, ps, (int)gseg.x);
             const CombineArgs ca{p.Mseg, p.Nseg, p.S0, p.Sin, p.ST, nullptr, nullptr, nullptr, nullptr, G, pb.H, 0};
             DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 1), NTHR, (CombineSmem<DK, DV>::bytes), ca);
             ps.S0 = p.Sin; ps.ST = nullptr;
             gchain = gseg;
         }
     }
-    if (pb.save) DN_LAUNCH_SCAN(k_scan_fwd_save, gchain, NTS, (ScanFwdSmem<T, DK, DV>::bytes), sm, pb.H, ps);
-    else DN_LAUNCH_SCAN(k_scan_fwd, gchain, NTS, (ScanFwdSmem<T, DK, DV>::bytes), sm, pb.H, ps);
+    constexpr int WB = VBlock<T, DV, DK>::BV, NB = VBlock<T, DV, DK>::NARROW;
+    if constexpr (NB < WB) {
+        if (narrow_blocks(pb, sm, gchain.x, DK <= 64 && !pb.save ? 4 : 2)) {
+            gchain.x *= WB / NB;
+            if (pb.save) DN_LAUNCH_SCAN_BV(k_scan_fwd_save, gchain, NB, (ScanFwdSmem<T, DK, DV, NB>::bytes), sm, pb.H, ps);
+            else DN_LAUNCH_SCAN_BV(k_scan_fwd, gchain, NB, (ScanFwdSmem<T, DK, DV, NB>::bytes), sm, pb.H, ps);
+            return 0;
+        }
+    }
+    if (pb.save) DN_LAUNCH_SCAN_BV(k_scan_fwd_save, gchain, WB, (ScanFwdSmem<T, DK, DV, WB>::bytes), sm, pb.H, ps);
+    else DN_LAUNCH_SCAN_BV(k_scan_fwd, gchain, WB, (ScanFwdSmem<T, DK, DV, WB>::bytes), sm, pb.H, ps);
+    return 0;
+}
+
+// the reverse scan of a backward pass, with the recompute scan in the same grid unless the forward pass left its tiles
+// (gscan: the ordinary grid of one scan)
+template <typename T, int DK, int DV> int launch_bwd_scans(const Problem &pb, const SeqMap &sm, const Ptrs &p, const Ptrs &ps, unsigned gscan) {
+    constexpr int WB = VBlock<T, DV, DK>::BV, NB = VBlock<T, DV, DK>::NARROW;
+    constexpr size_t lds_w = cmax(ScanFwdSmem<T, DK, DV, WB>::bytes, ScanBwdSmem<T, DK, DV, WB>::bytes);
+    if constexpr (NB < WB) {
+        if (narrow_blocks(pb, sm, pb.save ? gscan : 2 * gscan, 2)) {
+            constexpr size_t lds_n = cmax(ScanFwdSmem<T, DK, DV, NB>::bytes, ScanBwdSmem<T, DK, DV, NB>::bytes);
+            const unsigned half = gscan * (WB / NB);
+            if (pb.save) DN_LAUNCH_SCAN_BV(k_scan_bwd, dim3(half), NB, (ScanBwdSmem<T, DK, DV, NB>::bytes), sm, pb.H, ps);
+            else DN_LAUNCH_SCAN_BV(k_scan_pair, dim3(2 * half), NB, lds_n, sm, pb.H, ps, (int)half);
+            return 0;
+        }
+    }
+    if (pb.save) DN_LAUNCH_SCAN_BV(k_scan_bwd, dim3(gscan), WB, (ScanBwdSmem<T, DK, DV, WB>::bytes), sm, pb.H, ps);
+    else DN_LAUNCH_SCAN_BV(k_scan_pair, dim3(2 * gscan), WB, lds_w, sm, pb.H, ps, (int)gscan);
     return 0;
 }
 
@@ -129,7 +177,7 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
     if (int e = launch_offsets(pb)) return e;
     const dim3 gchain(chain_grid(pb.N * pb.H, VBlock<T, DV, DK>::NV));
     Ptrs ps = scan_ptrs(p);
-    constexpr size_t lds_pair = cmax(ScanFwdSmem<T, DK, DV>::bytes, ScanBwdSmem<T, DK, DV>::bytes);
+    constexpr size_t lds_pair = cmax(ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes, ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes);
     // few long chains: the scans run over G segments of the sequences side by side (see k_scan_state)
     int G = 1;
     if constexpr (DK == DV && DK <= 128) G = segment_count_bwd(pb.N, pb.L, pb.H, DK, DV, VBlock<T, DV, DK>::NV, pb.cu != nullptr);
@@ -139,27 +187,26 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
             sg.N = pb.N * G; sg.L = pb.L / G; sg.ncd = sg.L / C;
             const dim3 gseg(chain_grid(sg.N * pb.H, VBlock<T, DV, DK>::NV));
             if (pb.save) { // the forward pass left its tiles and the segments' transition matrices
-                DN_LAUNCH_SCAN(k_scan_bwd_state, gseg, NTS, (ScanBwdSmem<T, DK, DV>::bytes), sg, pb.H, ps);
+                DN_LAUNCH_SCAN(k_scan_bwd_state, gseg, NTS, (ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes), sg, pb.H, ps);
                 const CombineArgs ca{p.Mseg, nullptr, nullptr, nullptr, nullptr, p.Rseg, p.dST, p.dSout, p.dS0, G, pb.H, 1};
                 DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 1), NTHR, (CombineSmem<DK, DV>::bytes), ca);
                 ps.dST = p.dSout; ps.dS0 = nullptr;
-                DN_LAUNCH_SCAN(k_scan_bwd, gseg, NTS, (ScanBwdSmem<T, DK, DV>::bytes), sg, pb.H, ps);
+                if (int e = launch_bwd_scans<T, DK, DV>(pb, sg, p, ps, gseg.x)) return e;
             } else {
                 if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;
                 DN_LAUNCH_SCAN(k_scan_state, dim3(3 * gseg.x), NTS, lds_pair, sg, pb.H, ps, (int)gseg.x);
                 const CombineArgs ca{p.Mseg, p.Nseg, p.S0, p.Sin, nullptr, p.Rseg, p.dST, p.dSout, p.dS0, G, pb.H, 0};
                 DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 2), NTHR, (CombineSmem<DK, DV>::bytes), ca);
                 ps.S0 = p.Sin; ps.dST = p.dSout; ps.dS0 = nullptr;
-                DN_LAUNCH_SCAN(k_scan_pair, dim3(2 * gseg.x), NTS, lds_pair, sg, pb.H, ps, (int)gseg.x);
+                if (int e = launch_bwd_scans<T, DK, DV>(pb, sg, p, ps, gseg.x)) return e;
             }
         }
     } else if (pb.save) { // T, X, Ut and the chunk-initial states are the forward pass's: only the reverse scan is left
-        DN_LAUNCH_SCAN(k_scan_bwd, gchain, NTS, (ScanBwdSmem<T, DK, DV>::bytes), sm, pb.H, ps);
+        if (int e = launch_bwd_scans<T, DK, DV>(pb, sm, p, ps, gchain.x)) return e;
     } else {
         if (pb.chunks_ub) if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;
         // both scans of the backward pass as one grid: reverse scan first, recompute scan behind it
-        const dim3 gpair(2 * gchain.x);
-        DN_LAUNCH_SCAN(k_scan_pair, gpair, NTS, lds_pair, sm, pb.H, ps, (int)gchain.x);
+        if (int e = launch_bwd_scans<T, DK, DV>(pb, sm, p, ps, gchain.x)) return e;
     }
     if (pb.chunks_ub) {
         using SM = LocalSmem<T, DK, DV>;
