@@ -84,8 +84,7 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
 template <typename T, int DK, int DV> size_t max_lds_bytes();
 
 // The compiled (element type, d_k, d_v) instantiations: X(enum value of the C header, element type, d_k, d_v).
-// (bf16_t names __bf16 where the list is expanded; d = 256: the chunk tiles of its backward pass are streamed, they do
-// not fit the LDS)
+// (bf16_t names __bf16 where the list is expanded)
 #define DN_FOR_EACH_IMPL(X)                                                                        \
     X(DN_F32, float, 64, 64) X(DN_F32, float, 32, 64) X(DN_F32, float, 64, 32)                     \
     X(DN_BF16, bf16_t, 128, 128) X(DN_BF16, bf16_t, 64, 64) X(DN_BF16, bf16_t, 64, 128)            \
