@@ -71,7 +71,7 @@ template <typename T, int DK, int DV> size_t max_lds_bytes() {
 }
 
 // launches kernel<T, DK, DV, variant> for the variant the pointers ask for.  The scans know two variants
-// (for the prologue they run the plain one on the q, k that k_wy_prep mapped), the chunk kernel three.
+// (for the prologue they run the plain one on the q, k that k_wy_prep mapped), the chunk kernel and the reverse scan three.
 #define DN_LAUNCH_SCAN(kernel, grid, nthreads, lds, ...)                                                    \
     do {                                                                                                    \
         if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED>), grid, nthreads, lds, __VA_ARGS__);            \
@@ -82,6 +82,16 @@ template <typename T, int DK, int DV> size_t max_lds_bytes() {
     do {                                                                                                    \
         if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED, BV>), grid, NTS, lds, __VA_ARGS__);             \
         else DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PLAIN, BV>), grid, NTS, lds, __VA_ARGS__);                 \
+    } while (0)
+// ... of the reverse scan, whose dV depends on how beta was rounded: in bf16 the prologue has its own variant
+#define DN_LAUNCH_SCAN_DV(kernel, grid, BV, lds, ...)                                                       \
+    do {                                                                                                    \
+        if constexpr (sizeof(T) == 2)                                                                       \
+            if (p.pro) {                                                                                    \
+                DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PROLOGUE, BV>), grid, NTS, lds, __VA_ARGS__);           \
+                break;                                                                                      \
+            }                                                                                               \
+        DN_LAUNCH_SCAN_BV(kernel, grid, BV, lds, __VA_ARGS__);                                              \
     } while (0)
 // Scans of few chains (`wide` = workgroups of the grid with the ordinary column blocks) run with blocks half as wide: the
 // workgroups still fit the chip at once, and the step of each, whose length is the longest of a chain of products, is shorter.
@@ -161,13 +171,13 @@ template <typename T, int DK, int DV> int launch_bwd_scans(const Problem &pb, co
         if (narrow_blocks(pb, sm, pb.save ? gscan : 2 * gscan, 2)) {
             constexpr size_t lds_n = cmax(ScanFwdSmem<T, DK, DV, NB>::bytes, ScanBwdSmem<T, DK, DV, NB>::bytes);
             const unsigned half = gscan * (WB / NB);
-            if (pb.save) DN_LAUNCH_SCAN_BV(k_scan_bwd, dim3(half), NB, (ScanBwdSmem<T, DK, DV, NB>::bytes), sm, pb.H, ps);
-            else DN_LAUNCH_SCAN_BV(k_scan_pair, dim3(2 * half), NB, lds_n, sm, pb.H, ps, (int)half);
+            if (pb.save) DN_LAUNCH_SCAN_DV(k_scan_bwd, dim3(half), NB, (ScanBwdSmem<T, DK, DV, NB>::bytes), sm, pb.H, ps);
+            else DN_LAUNCH_SCAN_DV(k_scan_pair, dim3(2 * half), NB, lds_n, sm, pb.H, ps, (int)half);
             return 0;
         }
     }
-    if (pb.save) DN_LAUNCH_SCAN_BV(k_scan_bwd, dim3(gscan), WB, (ScanBwdSmem<T, DK, DV, WB>::bytes), sm, pb.H, ps);
-    else DN_LAUNCH_SCAN_BV(k_scan_pair, dim3(2 * gscan), WB, lds_w, sm, pb.H, ps, (int)gscan);
+    if (pb.save) DN_LAUNCH_SCAN_DV(k_scan_bwd, dim3(gscan), WB, (ScanBwdSmem<T, DK, DV, WB>::bytes), sm, pb.H, ps);
+    else DN_LAUNCH_SCAN_DV(k_scan_pair, dim3(2 * gscan), WB, lds_w, sm, pb.H, ps, (int)gscan);
     return 0;
 }
 
