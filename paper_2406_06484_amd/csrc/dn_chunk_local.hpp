@@ -7,7 +7,10 @@
 // The inverse of Eq. 10 and the gradients with respect to W and T never have to exist here.  Per chunk:
 //     dP = tril(dO Ut^T)                  Ah = diag(beta) dA = -tril(dV Ut^T, -1)
 //     dQ = dO S^T + dP K                  dK = Ut dS'^T - dV S^T + dP^T Q + (Ah + Ah^T) K
-//     dbeta_i = G_i . (v_i - S_{i-1}^T k_i) = dV_i . Ut_i / beta_i^2,   the diagonal of dV Ut^T
+//     dbeta_i = G_i . (v_i - S_{i-1}^T k_i) = dV_i . (v_i - S^T k_i - sum_{j<i} (k_i . k_j) Ut_j) / beta_i
+// In dbeta only dV carries a rounding of the row itself (v is exact, K S stays in the fp32 accumulators, Ut enters off the
+// diagonal).  The shorter form dV_i . Ut_i / beta_i^2, the diagonal of dV Ut^T, has Ut_i's as well: 12 to 22 % further from the
+// exact dbeta (rms, against 64 bits), 30 % in the gated variant, whose rows of dV are rounded again when they are scaled.
 // (rows whose beta is zero, or so small that the quotient could leave the range of fp32, take dbeta from G and the
 // prediction error themselves: rare_dbeta below).
 //
@@ -15,10 +18,10 @@
 // once; K and Q stay in LDS for the chunk.  Every block waits in registers from the moment it is requested; as soon as it has
 // moved to LDS the same registers request the block NS blocks on (of the workgroup's next chunk, at the end), so about one
 // chunk's worth of loads (d = 128; NS blocks at d = 256) is in flight at any time.
-// Bound by HBM: per chunk and head 176 KB at d = 128 in bf16 (read q, k, dO, dV, Ut, S, dS'; write dq, dk), with a third of the
-// matrix and LDS work of the form that goes through the inverse (which read X, V and dUt and wrote dV as well, 216 KB, in
-// eleven barrier intervals; here six).  Measured, 16 384 tokens of width 2048, kernel time before and now: d = 128 185 -> 138 us
-// (5.2 TB/s, what a copy reaches), d = 64 223 -> 115 us, d = 256 247 -> 195 us, gated 223 -> 191 us, prologue 229 -> 190 us.
+// Per chunk and head 192 KB through HBM at d = 128 in bf16 (read q, k, v, dO, dV, Ut, S, dS'; write dq, dk).  Kernel time at
+// 16 384 tokens of width 2048, with the shorter form of dbeta (no V, no products K S and K K^T) and now: d = 128 147 -> 170 us
+// (4.6 TB/s), d = 64 116 -> 130, d = 256 200 -> 224, gated 196 -> 207, prologue 187 -> 213.  Of the 23 us at d = 128 the product
+// K S takes 12 (10 since it is formed transposed), K K^T 7, V 3.
 #pragma once
 #include <type_traits>
 
@@ -37,11 +40,12 @@ template <typename T, int DK, int DV> struct LocalSmem {
     static constexpr size_t oK = 0;
     static constexpr size_t oQ = oK + align16(sizeof(T) * C * LK);
     static constexpr size_t oBeta = oQ + align16(sizeof(T) * C * LK);
-    static constexpr size_t oDg = oBeta + sizeof(float) * C;           // diagonal of dV Ut^T
-    static constexpr size_t oGam = oDg + sizeof(float) * C;            // gated: gamma_i
+    static constexpr size_t oPr = oBeta + sizeof(float) * C;           // -dV_i . (K S)_i per 32 columns of a block
+    static constexpr size_t oPl = oPr + sizeof(float) * (BVB / 32) * C; // -dV_i . sum_{j<i} (k_i . k_j) Ut_j per 32 tokens j
+    static constexpr size_t oGam = oPl + sizeof(float) * 2 * C;        // gated: gamma_i
     static constexpr size_t oZ = oGam + sizeof(float) * C;             // gated: per-wave shares of <dS_C, S_C> and <dS_0, S_0>
     static constexpr size_t oCq = oZ + sizeof(float) * 2 * NWC;          // gated: q_i . dq_i per column block of d_k
-    static constexpr size_t oCv = oCq + sizeof(float) * (DK / 32) * C; // gated: v_i . dv_i
+    static constexpr size_t oCv = oCq + sizeof(float) * (DK / 32) * C; // v_i . dv_i
     static constexpr size_t oMask = align16(oCv + sizeof(float) * C);
     // the current block ...
     static constexpr size_t oS = oMask + 16;
@@ -173,7 +177,7 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
     using SM = LocalSmem<T, DK, DV>;
     constexpr bool GATED = VAR == VAR_GATED, PRO = VAR == VAR_PROLOGUE;
     constexpr int BVB = SM::BVB, NB = SM::NB;
-    constexpr int NS = GATED ? 1 : SM::NS; // (the gated kernels have no registers for a second set)
+    constexpr int NS = GATED || (PRO && DK > 128) ? 1 : SM::NS; // (the gated kernels, and the prologue's at d_k = 256, have no registers for a second set)
     constexpr int KT = SM::TILES, KW = (KT + NWC - 1) / NWC; // 32 x 32 tiles of a C x d_k matrix, and per wave
     // operand fragments per request batch (one where registers are short: two workgroups per CU, the gated kernels)
     constexpr int MB = (SM::WPC == 2 || (GATED && sizeof(T) == 2)) ? 1 : 2;
@@ -186,7 +190,8 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
     T *sUt = reinterpret_cast<T *>(smem + SM::oUt);
     T *sDP = reinterpret_cast<T *>(smem + SM::oDP), *sBm = reinterpret_cast<T *>(smem + SM::oBm);
     T *sDQm = reinterpret_cast<T *>(smem + SM::oDQm), *sDKm = reinterpret_cast<T *>(smem + SM::oDKm);
-    float *sBeta = reinterpret_cast<float *>(smem + SM::oBeta), *sDg = reinterpret_cast<float *>(smem + SM::oDg);
+    float *sBeta = reinterpret_cast<float *>(smem + SM::oBeta), *sPr = reinterpret_cast<float *>(smem + SM::oPr);
+    float *sPl = reinterpret_cast<float *>(smem + SM::oPl);
     float *sGam = reinterpret_cast<float *>(smem + SM::oGam);
     float *sZ = reinterpret_cast<float *>(smem + SM::oZ), *sCq = reinterpret_cast<float *>(smem + SM::oCq), *sCv = reinterpret_cast<float *>(smem + SM::oCv);
     unsigned long long *sMask = reinterpret_cast<unsigned long long *>(smem + SM::oMask);
@@ -210,7 +215,7 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
         TokTile a;                                            // dO (HALF: first half dO, second half dV)
         std::conditional_t<HALF, NoTile, TokTile> b;          // dV
         TileRegs<T, BVB, C, HALF ? 256 : NTC> ut;             // (HALF: both halves hold a copy, the first one stores it)
-        std::conditional_t<GATED, TokTile, NoTile> v;         // gated: V, for v_i . dv_i (HALF: used by the second half)
+        TokTile v;                                            // V, for v_i . dv_i (HALF: in the second half, beside dV)
         float gr[TokTile::NIT];                               // gated: gamma of this thread's rows
     } r[NS];
     struct Head {
@@ -232,10 +237,8 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
             x.b.load_once((const T *)p.dv + row, (long)H * DV, tp.nvalid * live, tq);
         }
         x.ut.load_once((const T *)p.Ut + tv * C, C, BVB * live, tt);
-        if constexpr (GATED) {
-            x.v.load_once((const T *)p.v + row, (long)H * DV, tp.nvalid * live, tt);
-            x.a.load_row_factors(x.gr, p.gam + tp.tile * 2 * C, tt);
-        }
+        x.v.load_once((const T *)p.v + row, (long)H * DV, HALF && first_half ? 0 : tp.nvalid * live, tt);
+        if constexpr (GATED) x.a.load_row_factors(x.gr, p.gam + tp.tile * 2 * C, tt);
     };
     auto fetch_head = [&](const TilePos &tp, int live) __attribute__((always_inline)) {
         // (prologue variant: the q and k that k_wy_prep mapped and left in the workspace, in the layout of q and k)
@@ -285,33 +288,41 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
             }
         };
         if (DK <= 128) fetch_raw();
-        if (DK <= 128 || VAR == VAR_PLAIN) fetch_head(nf, nl);
+        if (DK <= 128) fetch_head(nf, nl);
         // gated: this thread's shares of <dS~', S_0> and <K, Ut dS~'^T>
         float zs = 0.f, zk = 0.f;
         f32x16 dpc = zero16(), ahc = zero16(), dq[KW], dk[KW];
         // (where the C x C tiles and the C x d_k tiles are on different waves, they share registers)
         f32x16 &dp = TSHIFT ? dq[0] : dpc, &ah = TSHIFT ? dk[0] : ahc;
+        // The tiles of (K S)^T (BVB x C) go to the waves with less to do in a block, tile kst to token block ua, column block ub:
+        // the first ones, if others own the C x d_k tiles, and otherwise those that own no C x C tile, in the registers of one.
+        // (Transposed: the lane's column is a token, so the sum over the state columns is over its own registers.)
+        const int kst = TSHIFT ? wave : wave - 4, ua = kst / (BVB / 32), ub = kst % (BVB / 32);
+        const bool does_ks = kst >= 0 && kst < 2 * (BVB / 32);
+        f32x16 ksx = zero16();
+        f32x16 &ks = TSHIFT ? ksx : dpc;
+        float pr = 0.f;
 #pragma unroll
         for (int sI = 0; sI < KW; ++sI) { dq[sI] = zero16(); dk[sI] = zero16(); }
 
         auto block = [&](Blk &x, int vb) __attribute__((always_inline)) {
-            // gated: the chunk is the plain rule on v_i / gamma_i with outputs gamma_i o~_i, so dO and dV rows come in scaled by gamma_i
-            if constexpr (GATED) {
-                zs += x.ds.dot(x.s);
-                // v_i . dv_i over this block's columns: the lanes that hold a row are adjacent
+            { // v_i . dv_i over this block's columns: the lanes that hold a row are adjacent
                 const int tt = HALF ? (tq & 255) : tq;
 #pragma unroll
                 for (int i = 0; i < TokTile::NIT; ++i) {
                     float s;
                     if constexpr (HALF) s = x.a.dot_row(x.v, i);
                     else s = x.b.dot_row(x.v, i);
-#pragma unroll
-                    for (int d = 1; d < TokTile::TPR; d <<= 1) s += __shfl_xor(s, d);
+                    s = lane_sum<TokTile::TPR>(s);
                     if (tt % TokTile::TPR == 0 && (!HALF || !first_half)) {
                         float *to = sCv + i * TokTile::RPI + tt / TokTile::TPR;
                         *to = vb == 0 ? s : *to + s;
                     }
                 }
+            }
+            // gated: the chunk is the plain rule on v_i / gamma_i with outputs gamma_i o~_i, so dO and dV rows come in scaled by gamma_i
+            if constexpr (GATED) {
+                zs += x.ds.dot(x.s);
                 x.a.scale_rows(x.gr);
                 if constexpr (!HALF) x.b.scale_rows(x.gr);
             }
@@ -327,6 +338,16 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
             const bool wrap = vb + NS >= NB;
             fetch_blk(x, wrap ? nf : cur, wrap ? vb + NS - NB : vb + NS, wrap ? nl : 1);
             lds_barrier(); fresh();
+            if (does_ks) { // (K S)^T, and its products with -dV
+                ks = zero16();
+                mma<DK, false, false, T, true, (DK > 128 ? 1 : MB)>(ks, sS + 32 * ub * SM::LK, SM::LK, sK + 32 * ua * SM::LK, SM::LK, tq);
+                acc_each4(ks, [&](int v, int i, float a, float b, float c, float d) {
+                    T x[4];
+                    ld4(x, sDV + (32 * ua + i) * SM::LB + 32 * ub + v);
+                    pr += (a * to_f32(x[0]) + b * to_f32(x[1])) + (c * to_f32(x[2]) + d * to_f32(x[3]));
+                }, tq);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if (cc && !upper) // dO Ut^T, -dV Ut^T: the fragments of Ut are read once for both
                 mma_shared_b<BVB, false, false, true, T, MB>(dp, ah, sDO + 32 * mi * SM::LB, SM::LB, sDV + 32 * mi * SM::LB, SM::LB, sUt + 32 * ni, SM::LU, tq);
 #pragma unroll
@@ -356,8 +377,20 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
                 if (NS == 2) block(r[NS - 1], vb + 1);
             }
         }
+        if (does_ks) {
+            pr += __shfl_xor(pr, 32);
+            if ((tq & 63) < 32) sPr[ub * C + 32 * ua + (tq & 31)] = pr;
+        }
+                    if (cc && !upper) { // -dV_i . sum_{j<i} (k_i . k_j) Ut_j
+                        f32x16 l = zero16();
+                        mma<DK, false, false, T, true, (DK > 128 ? 1 : MB)>(l, sK + 32 * mi * SM::LK, SM::LK, sK + 32 * ni * SM::LK, SM::LK, tq);
+                        const int lane = tq & 63, below = 32 * (mi - ni) + 4 * (lane >> 5) - (lane & 31); // row - column of element 0
+        #pragma unroll
+                        for (int e = 0; e < 16; ++e) l[e] = below + 8 * (e >> 2) + (e & 3) > 0 ? l[e] * ah[e] : 0.f;
+                        row_sums(sPl + ni * C + 32 * mi, l, tq);
+                    }
         if (DK > 128) fetch_raw();
-        if (DK > 128 && VAR != VAR_PLAIN) fetch_head(nf, nl); // (no registers to hold it longer)
+        if (DK > 128) fetch_head(nf, nl); // (no registers to hold it longer)
 
         float z0 = 0.f; // gated: this thread's share of <Q, dO S^T> + <K, Ut dS~'^T - dV S^T>
         if (GATED) {
@@ -370,13 +403,12 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
             }
         }
         if (cc) {
-            // dP = tril(dO Ut^T); Bm = Ah + Ah^T with Ah = -tril(dV Ut^T, -1); the diagonal of -dV Ut^T for dbeta
+            // dP = tril(dO Ut^T); Bm = Ah + Ah^T with Ah = -tril(dV Ut^T, -1)
             if (mi == ni) {
                 const int lane = tq & 63, c = lane & 31, hh = lane >> 5;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int rr = 8 * (e >> 2) + 4 * hh + (e & 3), i = 32 * mi + rr, j = 32 * mi + c;
-                    if (rr == c) sDg[i] = -ah[e];
                     if (rr >= c) {
                         const T x = from_f32<T>(rr == c ? 0.f : ah[e]);
                         sBm[i * SM::LT + j] = x;
@@ -413,10 +445,13 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
             }
         }
         any_tiny |= *sMask;
-        if (tq < nvalid) { // (nvalid <= C) dbeta, from the diagonal of dV Ut^T
-            const float b = sBeta[tq], ib = 1.f / b;
-            float db = sDg[tq] * ib * ib;
-            if (PRO) db *= b * (1.f - b); // through the sigmoid
+        if (tq < nvalid) { // (nvalid <= C) dbeta
+            float db = sCv[tq] + sPl[tq];
+            if (tq >= 32) db += sPl[C + tq];
+#pragma unroll
+            for (int c = 0; c < BVB / 32; ++c) db += sPr[c * C + tq];
+            const float b = sBeta[tq];
+            db = PRO ? db * (1.f - b) : db / b; // (fused: through the sigmoid)
             if (!((*sMask >> tq) & 1)) p.dbeta[(row0 + tq) * H + h] = db;
         }
         if (GATED) { // this wave's shares of <dS_C, S_C> and <dS_0, S_0>, summed in a fixed order after the barrier

@@ -238,6 +238,45 @@ template <typename F> __device__ inline void acc_each4(const f32x16 &acc, F f, i
     for (int g = 0; g < 4; ++g) f(8 * g + 4 * h, col, acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
 }
 
+// Lane exchanges inside a row of 16 lanes on the vector ALU (a __shfl_xor goes through the LDS).  The distances 8, 4, 2, 1 pair
+// lane l with l ^ 8, l ^ 7 (the mirror image within 8), l ^ 2 and l ^ 1: a chain of sums in that order, or in the reverse one
+// from any of them, covers the same lanes as the butterfly.
+template <int D> __device__ inline float lane_across(float x) {
+    constexpr int ctrl = D == 8 ? 0x128 /* row_ror:8 */ : D == 4 ? 0x141 /* row_half_mirror */ : D == 2 ? 0x4e /* quad_perm 2,3,0,1 */ : 0xb1 /* quad_perm 1,0,3,2 */;
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xf, 0xf, false));
+}
+// sum over N neighbouring lanes (N = 4, 8, 16), delivered to all of them
+template <int N> __device__ inline float lane_sum(float x) {
+    static_assert(N == 4 || N == 8 || N == 16, "inside a row of lanes");
+    x += lane_across<1>(x);
+    x += lane_across<2>(x);
+    if (N >= 8) x += lane_across<4>(x);
+    if (N >= 16) x += lane_across<8>(x);
+    return x;
+}
+// dst[r] = sum over the columns of row r of the 32 x 32 tile.  Each of the first four steps sends one half of the remaining rows
+// to the lane across and keeps the other, so a tile takes 16 exchanges instead of 80; the order of the additions is fixed.
+template <int D> __device__ inline void row_sums_step(float (&v)[16], int lane) {
+    const bool hi = (lane & D) != 0;
+#pragma unroll
+    for (int e = 0; e < D; ++e) {
+        const float send = hi ? v[e] : v[e + D], keep = hi ? v[e + D] : v[e];
+        v[e] = keep + lane_across<D>(send);
+    }
+}
+__device__ inline void row_sums(float *dst, const f32x16 &acc, int tx = threadIdx.x) {
+    const int lane = tx & 63;
+    float v[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = acc[e];
+    row_sums_step<8>(v, lane);
+    row_sums_step<4>(v, lane);
+    row_sums_step<2>(v, lane);
+    row_sums_step<1>(v, lane);
+    v[0] += __shfl_xor(v[0], 16); // lane & 15 is the element index now
+    if (!(lane & 16)) dst[8 * ((lane & 15) >> 2) + 4 * (lane >> 5) + (lane & 3)] = v[0];
+}
+
 __device__ inline void st4(float *p, float a, float b, float c, float d) {
     *reinterpret_cast<f32x4 *>(p) = f32x4{a, b, c, d};
 }
@@ -245,6 +284,13 @@ __device__ inline void st4(bf16 *p, float a, float b, float c, float d) {
     *reinterpret_cast<bf16x4 *>(p) = bf16x4{(bf16)a, (bf16)b, (bf16)c, (bf16)d};
 }
 
+// four neighbouring elements from LDS (16 bytes, 8 in bf16)
+template <typename T> __device__ inline void ld4(T (&x)[4], const T *p) {
+    struct alignas(4 * sizeof(T)) quad { T e[4]; };
+    const quad q = *reinterpret_cast<const quad *>(p);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = q.e[i];
+}
 // tile (32x32) of the accumulator -> LDS, row-major destination dst[row][col]
 template <typename T> __device__ inline void acc_to_lds(T *dst, int ld, int row0, int col0, f32x16 &acc, int tx = threadIdx.x) {
     acc_each(acc, [&](int r, int c, float &v) { dst[(row0 + r) * ld + col0 + c] = from_f32<T>(v); }, tx);

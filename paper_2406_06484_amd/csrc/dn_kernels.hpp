@@ -593,9 +593,11 @@ __global__ __launch_bounds__(NTHR) void k_seg_combine(CombineArgs a) {
 // scan_bwd_body: reverse over chunks, carrying dS (gradient w.r.t. the chunk-initial state):
 //   dUt = P^T dO + K dS';  dV = T^T dUt;  dS = dS' + Q^T dO - W^T dUt
 // Per chunk it leaves dS'^T in the workspace (the transposed LDS copy, written out by the loader waves) and stores dV.
-// Prologue variant in bf16: beta is the fp32 sigmoid of the logit, and the diagonal of T (the largest term of a row of dV) is
-// that value rounded to bf16, the same factor for a whole row.  What the rounding took is put back from the fp32 accumulators,
-// dV = T^T dUt + (beta - bf16(beta)) dUt; without it dV is 8 to 12 % further from the exact one (rms, against 64 bits).
+// In bf16 the product for dV reads dUt rounded, and the diagonal of T is beta (prologue variant: the fp32 sigmoid) rounded, one
+// factor for a whole row.  The diagonal is the largest term of a row, so it is put in from the fp32 accumulators instead:
+// dV = T^T bf16(dUt) + (beta dUt - bf16(beta) bf16(dUt)).  That brings dV 14 to 17 % closer to the exact one (rms, against 64
+// bits) and makes up for the rounding that storing dV adds to dbeta, which the chunk kernel forms from it; it costs 2 to 4 %
+// of the scan (16 384 tokens of width 2048: d = 64 118 -> 123 us, d = 256 229 -> 233).
 template <typename T, int DK, int DV, int BV> struct ScanBwdSmem {
     static constexpr int LQ = ldn<T>(DK), LK = ldn<T>(DK), LD = ldn<T>(BV), LS = ldc<T>(DK), LT = ldc<T>(C);
     static constexpr size_t oQ = 0;
@@ -609,8 +611,9 @@ template <typename T, int DK, int DV, int BV> struct ScanBwdSmem {
     // P^T; in the interval after its use, the staging tiles of the chain waves for dV
     static constexpr size_t oPT = oT + 2 * szT, oStage = oPT;
     static constexpr size_t szPT = cmax(szT, ScanMap<DK, BV>::U_TILES * sizeof(T) * Stage<T>::ELEMS);
-    static constexpr size_t oGi = oPT + szPT;                        // gated: 1 / gamma_i (prologue: beta_i - bf16(beta_i)), two tables, alternating as T
-    static constexpr size_t bytes = oGi + 2 * sizeof(float) * C;
+    static constexpr size_t oGi = oPT + szPT;                        // gated: 1 / gamma_i, two tables, alternating as T
+    static constexpr size_t oBeta = oGi + 2 * sizeof(float) * C;     // bf16: beta_i, two tables as well
+    static constexpr size_t bytes = oBeta + 2 * sizeof(float) * C;
 };
 
 // STATE = true: only the gradient with respect to the initial state leaves the kernel (the first pass of a backward
@@ -632,7 +635,8 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
     T *sT0 = reinterpret_cast<T *>(smem + SM::oT), *sT1 = reinterpret_cast<T *>(smem + SM::oT + SM::szT);
     T *sPT = reinterpret_cast<T *>(smem + SM::oPT);
     T *stg = reinterpret_cast<T *>(smem + SM::oStage) + ((threadIdx.x >> 6) % ScanMap<DK, BV>::U_TILES) * Stage<T>::ELEMS;
-    float *sGi = reinterpret_cast<float *>(smem + SM::oGi);
+    float *sGi = reinterpret_cast<float *>(smem + SM::oGi), *sBeta = reinterpret_cast<float *>(smem + SM::oBeta);
+    constexpr bool DIAG = sizeof(T) == 2 && !STATE; // the diagonal term of dV from the accumulators
     constexpr bool kWholeLines = BV * sizeof(T) >= 128; // see scan_fwd_body
     constexpr bool gated = GATED; // compile-time, so the plain kernels carry none of the gate's registers
     // the gated kernels, and those with d_k = 256, request operand fragments in smaller batches: they have no registers to spare
@@ -665,7 +669,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         TileRegs<T, C, BV, NTL> d_o;
         TileRegs<T, C, C, NTL> t;
         float dos[TileRegs<T, C, BV, NTL>::NIT], gi; // gated: gamma of this lane's dO rows; one entry of the 1 / gamma table
-        T beta;                                      // prologue: one row's logit, in storage format (converting here would wait for the load)
+        T beta;                                      // one row's beta (logit), in storage format (converting here would wait for the load)
     } r;
     auto fetch_a = [&](int ic) __attribute__((always_inline)) {
         const int nvalid = min(C, len - ic * C);
@@ -683,7 +687,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             r.d_o.load_row_factors(r.dos, p.gam + tile * 2 * C, lt);
             if (lt < C) r.gi = p.gam[tile * 2 * C + C + lt];
         }
-        if (PRO && lt < C) r.beta = ((const T *)p.beta)[(row0 + min(lt, nvalid - 1)) * H + h]; // (dUt of a row past the end meets rows of zeros)
+        if (DIAG && lt < C) r.beta = ((const T *)p.beta)[(row0 + min(lt, nvalid - 1)) * H + h]; // (dUt of a row past the end meets rows of zeros)
     };
     // As in the forward scan, the loader waves issue the global traffic of a step in one burst after
     // its first barrier: next chunk's loads, this chunk's dS'^T.
@@ -693,9 +697,9 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         r.d_o.store(sDO, SM::LD, lt);
         r.t.store(par ? sT1 : sT0, SM::LT, lt);
         if (gated && lt < C) sGi[par * C + lt] = r.gi;
-        if (PRO && lt < C) {
-            const float bt = sigmoid_f32(to_f32(r.beta));
-            sGi[par * C + lt] = bt - to_f32(from_f32<T>(bt));
+        if (DIAG && lt < C) {
+            const float bt = to_f32(r.beta);
+            sBeta[par * C + lt] = PRO ? sigmoid_f32(bt) : bt;
         }
     };
     if (loader && nchunks > 0) { fetch_a(nchunks - 1); fetch_b(nchunks - 1); stash((nchunks - 1) & 1); }
@@ -775,12 +779,15 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             f32x16 dv = zero16();
             if (m.ua == 0) mma<C, true, false, T, true, MB>(dv, sT, SM::LT, sDUT + 32 * m.ub * SM::LT, SM::LT);
             else mma<32, true, false, T, true, MB>(dv, sT + 32 * SM::LT + 32, SM::LT, sDUT + 32 * m.ub * SM::LT + 32, SM::LT);
-            if (gated) acc_each(dv, [&](int rr, int, float &val) { val *= sGi[(ic & 1) * C + 32 * m.ua + rr]; }); // v_i = gamma_i v~_i
-            if (PRO) {
-                const float *dl = sGi + (ic & 1) * C + 32 * m.ua + 4 * ((threadIdx.x & 63) >> 5);
+            if (DIAG) {
+                const float *bt = sBeta + (ic & 1) * C + 32 * m.ua + 4 * ((threadIdx.x & 63) >> 5);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) dv[e] += dl[8 * (e >> 2) + (e & 3)] * acc[e];
+                for (int e = 0; e < 16; ++e) {
+                    const float b = bt[8 * (e >> 2) + (e & 3)], rd = to_f32(from_f32<T>(acc[e]));
+                    dv[e] += PRO ? b * acc[e] - to_f32(from_f32<T>(b)) * rd : b * (acc[e] - rd);
+                }
             }
+            if (gated) acc_each(dv, [&](int rr, int, float &val) { val *= sGi[(ic & 1) * C + 32 * m.ua + rr]; }); // v_i = gamma_i v~_i
             acc_store<T, kWholeLines>(stg, (T *)p.dv + (((long)t0 + (long)ic * C) * H + h) * DV + vb, (long)H * DV, 32 * m.ua, 32 * m.ub, min(C, len - ic * C), dv);
         }
     }
