@@ -284,12 +284,16 @@ __device__ inline void st4(bf16 *p, float a, float b, float c, float d) {
     *reinterpret_cast<bf16x4 *>(p) = bf16x4{(bf16)a, (bf16)b, (bf16)c, (bf16)d};
 }
 
-// four neighbouring elements from LDS (16 bytes, 8 in bf16)
+// four neighbouring elements, from or to LDS or global memory (16 bytes, 8 in bf16)
 template <typename T> __device__ inline void ld4(T (&x)[4], const T *p) {
     struct alignas(4 * sizeof(T)) quad { T e[4]; };
     const quad q = *reinterpret_cast<const quad *>(p);
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[i] = q.e[i];
+}
+template <typename T> __device__ inline void st4v(T *p, const T (&x)[4]) {
+    struct alignas(4 * sizeof(T)) quad { T e[4]; };
+    *reinterpret_cast<quad *>(p) = quad{{x[0], x[1], x[2], x[3]}};
 }
 // tile (32x32) of the accumulator -> LDS, row-major destination dst[row][col]
 template <typename T> __device__ inline void acc_to_lds(T *dst, int ld, int row0, int col0, f32x16 &acc, int tx = threadIdx.x) {

@@ -21,10 +21,13 @@ constexpr int cmax(int a, int b) { return a > b ? a : b; }
 // the plain delta rule; the gated rule; the plain rule with the layer's prologue (q, k = SiLU(x) /
 // ||SiLU(x)||_2 of section 3.3, beta = sigmoid(b) of section 2.2).  For the prologue k_wy_prep maps q
 // and k once and leaves them in the workspace for the scans, which run the plain variant on them (the reverse scan
-// that stores dV in bf16 has one of its own, see scan_bwd_body);
+// that stores dV has one of its own, see scan_bwd_body);
 // k_bwd_local reads the mapped tiles too and sends the gradients back through the map on
 // the way out, so dq, dk never reach HBM in the mapped coordinates.
 enum { VAR_PLAIN = 0, VAR_GATED = 1, VAR_PROLOGUE = 2 };
+// |beta| below this counts as a masked token in the backward pass: dbeta is not taken from a quotient by it (its square, and
+// products of its size, stay far inside fp32 above it)
+constexpr float kTinyBeta = 0x1p-40f;
 constexpr size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
 // ---------------------------------------------------------------------------------------------
@@ -597,7 +600,9 @@ __global__ __launch_bounds__(NTHR) void k_seg_combine(CombineArgs a) {
 // factor for a whole row.  The diagonal is the largest term of a row, so it is put in from the fp32 accumulators instead:
 // dV = T^T bf16(dUt) + (beta dUt - bf16(beta) bf16(dUt)).  That brings dV 14 to 17 % closer to the exact one (rms, against 64
 // bits) and makes up for the rounding that storing dV adds to dbeta, which the chunk kernel forms from it; it costs 2 to 4 %
-// of the scan (16 384 tokens of width 2048: d = 64 118 -> 123 us, d = 256 229 -> 233).
+// of the scan (16 384 tokens of width 2048: d = 64 118 -> 123 us, d = 256 229 -> 233).  The factors of dUt and bf16(dUt) come
+// from two tables, and so a masked token (beta zero, or below kTinyBeta) costs nothing here: its row of T^T has nothing but the
+// diagonal, beta, and with factors 1 and 0 the row that is stored is dUt_i, which the chunk kernel makes G_i and beta_i G_i from.
 template <typename T, int DK, int DV, int BV> struct ScanBwdSmem {
     static constexpr int LQ = ldn<T>(DK), LK = ldn<T>(DK), LD = ldn<T>(BV), LS = ldc<T>(DK), LT = ldc<T>(C);
     static constexpr size_t oQ = 0;
@@ -612,8 +617,8 @@ template <typename T, int DK, int DV, int BV> struct ScanBwdSmem {
     static constexpr size_t oPT = oT + 2 * szT, oStage = oPT;
     static constexpr size_t szPT = cmax(szT, ScanMap<DK, BV>::U_TILES * sizeof(T) * Stage<T>::ELEMS);
     static constexpr size_t oGi = oPT + szPT;                        // gated: 1 / gamma_i, two tables, alternating as T
-    static constexpr size_t oBeta = oGi + 2 * sizeof(float) * C;     // bf16: beta_i, two tables as well
-    static constexpr size_t bytes = oBeta + 2 * sizeof(float) * C;
+    static constexpr size_t oDiag = oGi + 2 * sizeof(float) * C;     // factors of dUt_i and of its rounded value in dV_i, two tables each
+    static constexpr size_t bytes = oDiag + 4 * sizeof(float) * C;
 };
 
 // STATE = true: only the gradient with respect to the initial state leaves the kernel (the first pass of a backward
@@ -635,8 +640,8 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
     T *sT0 = reinterpret_cast<T *>(smem + SM::oT), *sT1 = reinterpret_cast<T *>(smem + SM::oT + SM::szT);
     T *sPT = reinterpret_cast<T *>(smem + SM::oPT);
     T *stg = reinterpret_cast<T *>(smem + SM::oStage) + ((threadIdx.x >> 6) % ScanMap<DK, BV>::U_TILES) * Stage<T>::ELEMS;
-    float *sGi = reinterpret_cast<float *>(smem + SM::oGi), *sBeta = reinterpret_cast<float *>(smem + SM::oBeta);
-    constexpr bool DIAG = sizeof(T) == 2 && !STATE; // the diagonal term of dV from the accumulators
+    float *sGi = reinterpret_cast<float *>(smem + SM::oGi), *sDiag = reinterpret_cast<float *>(smem + SM::oDiag);
+    constexpr bool DIAG = !STATE && (sizeof(T) == 2 || !PRO); // a diagonal term of dV from the accumulators (fp32: the masked rows' only)
     constexpr bool kWholeLines = BV * sizeof(T) >= 128; // see scan_fwd_body
     constexpr bool gated = GATED; // compile-time, so the plain kernels carry none of the gate's registers
     // the gated kernels, and those with d_k = 256, request operand fragments in smaller batches: they have no registers to spare
@@ -698,8 +703,10 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         r.t.store(par ? sT1 : sT0, SM::LT, lt);
         if (gated && lt < C) sGi[par * C + lt] = r.gi;
         if (DIAG && lt < C) {
-            const float bt = to_f32(r.beta);
-            sBeta[par * C + lt] = PRO ? sigmoid_f32(bt) : bt;
+            const float bt = PRO ? sigmoid_f32(to_f32(r.beta)) : to_f32(r.beta);
+            const bool tiny = !PRO && fabsf(bt) < kTinyBeta;
+            sDiag[2 * par * C + lt] = tiny ? 1.f : sizeof(T) == 2 ? bt : 0.f;
+            sDiag[(2 * par + 1) * C + lt] = tiny || sizeof(T) == 4 ? 0.f : -to_f32(from_f32<T>(bt));
         }
     };
     if (loader && nchunks > 0) { fetch_a(nchunks - 1); fetch_b(nchunks - 1); stash((nchunks - 1) & 1); }
@@ -780,11 +787,11 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             if (m.ua == 0) mma<C, true, false, T, true, MB>(dv, sT, SM::LT, sDUT + 32 * m.ub * SM::LT, SM::LT);
             else mma<32, true, false, T, true, MB>(dv, sT + 32 * SM::LT + 32, SM::LT, sDUT + 32 * m.ub * SM::LT + 32, SM::LT);
             if (DIAG) {
-                const float *bt = sBeta + (ic & 1) * C + 32 * m.ua + 4 * ((threadIdx.x & 63) >> 5);
+                const float *fa = sDiag + 2 * (ic & 1) * C + 32 * m.ua + 4 * ((threadIdx.x & 63) >> 5), *fr = fa + C;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const float b = bt[8 * (e >> 2) + (e & 3)], rd = to_f32(from_f32<T>(acc[e]));
-                    dv[e] += PRO ? b * acc[e] - to_f32(from_f32<T>(b)) * rd : b * (acc[e] - rd);
+                    dv[e] += fa[8 * (e >> 2) + (e & 3)] * acc[e];
+                    if (sizeof(T) == 2) dv[e] += fr[8 * (e >> 2) + (e & 3)] * to_f32(from_f32<T>(acc[e]));
                 }
             }
             if (gated) acc_each(dv, [&](int rr, int, float &val) { val *= sGi[(ic & 1) * C + 32 * m.ua + rr]; }); // v_i = gamma_i v~_i

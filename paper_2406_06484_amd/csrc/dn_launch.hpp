@@ -83,15 +83,11 @@ template <typename T, int DK, int DV> size_t max_lds_bytes() {
         if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED, BV>), grid, NTS, lds, __VA_ARGS__);             \
         else DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PLAIN, BV>), grid, NTS, lds, __VA_ARGS__);                 \
     } while (0)
-// ... of the reverse scan, whose dV depends on how beta was rounded: in bf16 the prologue has its own variant
+// ... of the reverse scan, whose dV depends on how beta was rounded and on which tokens are masked
 #define DN_LAUNCH_SCAN_DV(kernel, grid, BV, lds, ...)                                                       \
     do {                                                                                                    \
-        if constexpr (sizeof(T) == 2)                                                                       \
-            if (p.pro) {                                                                                    \
-                DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PROLOGUE, BV>), grid, NTS, lds, __VA_ARGS__);           \
-                break;                                                                                      \
-            }                                                                                               \
-        DN_LAUNCH_SCAN_BV(kernel, grid, BV, lds, __VA_ARGS__);                                              \
+        if (p.pro) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PROLOGUE, BV>), grid, NTS, lds, __VA_ARGS__);        \
+        else DN_LAUNCH_SCAN_BV(kernel, grid, BV, lds, __VA_ARGS__);                                         \
     } while (0)
 // Scans of few chains (`wide` = workgroups of the grid with the ordinary column blocks) run with blocks half as wide: the
 // workgroups still fit the chip at once, and the step of each, whose length is the longest of a chain of products, is shorter.
