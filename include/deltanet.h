@@ -105,6 +105,9 @@ int deltanet_fwd_static(const dn_shape *shape, const void *q, const void *k, con
  * (section 3.2, "hidden states recomputed during the backward pass"), so nothing from the forward
  * call has to be kept.  dfinal_state may be NULL (zeros); dinitial_state may be NULL (not written).
  * Outputs: dq, dk, dv (element type dtype), dbeta (fp32, shape of beta), dinitial_state (fp32).
+ * dq, dk and dv may each take the place of a whole input of the same shape (dq over q, dk over k, dv over v or d_o, ...);
+ * dv then costs one more copy.  No output may overlap another one, or an input in any other way.  This holds for every
+ * backward pass below.
  */
 int deltanet_bwd(const dn_shape *shape, const void *q, const void *k, const void *v, const void *beta,
                  const float *initial_state, const void *d_o, const float *dfinal_state, void *dq,

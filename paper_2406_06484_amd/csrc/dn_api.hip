@@ -44,7 +44,7 @@ constexpr int kChunk = 64;
 
 struct Plan {
     Problem pb;
-    size_t off_coff, off_T, off_Ut, off_Sc, off_dSc, off_gam, off_Qm, off_Km, off_seg, seg_bytes, total;
+    size_t off_coff, off_T, off_dV, off_Ut, off_Sc, off_dSc, off_gam, off_Qm, off_Km, off_seg, seg_bytes, total;
     size_t esz;
 };
 
@@ -109,11 +109,11 @@ void make_plan(const dn_shape *s, int want_bwd, Plan *pl, bool gated = false, bo
     const size_t tC = up256(tiles * kChunk * kChunk * pl->esz);
     pl->off_T = o; o += tC; // T of Eq. 10
     if (want_bwd) {
-        // (one C x C and one C x d_v tile per chunk and head are unused: the size that callers were told, and may have
-        // stored, for a shape stays what it was)
+        // (one C x C tile per chunk and head is unused: the size that callers were told, and may have stored, for a shape
+        // stays what it was)
         o += tC;
         pl->off_Ut = o; o += tV;
-        o += tV;
+        pl->off_dV = o; o += tV; // dv, layout of v, where the caller's buffer is also an input (64 rows per chunk: at least as many as v has)
         pl->off_Sc = o; o += tS;
         pl->off_dSc = o; o += tS;
     }
@@ -133,6 +133,12 @@ void make_plan(const dn_shape *s, int want_bwd, Plan *pl, bool gated = false, bo
         pl->off_Km = o; o += tQ;
     }
     pl->total = o;
+}
+
+// do [a, a + na) and [b, b + nb) have a byte in common?
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + nb && y < x + na;
 }
 
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
@@ -226,6 +232,17 @@ int bwd_impl(const dn_shape *shape, const void *q, const void *k, const void *v,
     pl.pb.save = saved;
     p.pro = prologue;
     bind_workspace(pl, workspace, &p, &pl.pb, true, gated, prologue);
+    // dv is written by the reverse scan, while other workgroups and the chunk kernel still read the inputs.  A caller that has
+    // dv replace one of them (v, d_o: the other gradients are stored tile by tile when the tile's inputs have been read) gets it
+    // through the workspace.
+    const size_t rows = (size_t)shape->B * shape->L * shape->H, states = sizeof(float) * (size_t)pl.pb.N * shape->H * shape->d_k * shape->d_v;
+    const size_t nk = rows * shape->d_k * pl.esz, nv = rows * shape->d_v * pl.esz;
+    if (overlap(dv, nv, q, nk) || overlap(dv, nv, k, nk) || overlap(dv, nv, v, nv) || overlap(dv, nv, d_o, nv) ||
+        overlap(dv, nv, beta, rows * pl.esz) || overlap(dv, nv, p.g, rows * sizeof(float)) ||
+        overlap(dv, nv, initial_state, states) || overlap(dv, nv, dfinal_state, states)) {
+        p.dv_out = dv;
+        p.dv = static_cast<unsigned char *>(workspace) + pl.off_dV;
+    }
     return impl->bwd(pl.pb, p) == 0 ? DN_OK : DN_ERR_LAUNCH;
 }
 

@@ -25,6 +25,7 @@ struct Ptrs {
     const float *S0, *dST;
     void *o, *dq, *dk, *dv;
     float *ST, *dbeta, *dS0;
+    void *dv_out; // backward, where the caller's dv is also an input: that buffer (dv then points into the workspace); else nullptr
     // workspace tiles, indexed by (global chunk * H + head)
     void *Tm, *Ut, *Sc, *dSc;
     // gated variant (all null for the plain delta rule): g = log decay per token and head (fp32, user

@@ -88,7 +88,8 @@ static __global__ void k_chunk_offsets(const int32_t *cu_in, int N, int L, int32
     for (int n = lo; n < hi; ++n) { coff[n] = run; run += (cu[n + 1] - cu[n] + C - 1) / C; }
 }
 
-// final_state of a pass over no tokens at all: the initial state, or zero
+// plain copy of 32-bit words (src null: zeros): final_state of a pass over no tokens at all, which is the initial state or zero;
+// dv from the workspace to a buffer that was also an input
 static __global__ void k_state_copy(float *dst, const float *src, long count) {
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (long)gridDim.x * blockDim.x) dst[i] = src ? src[i] : 0.f;
 }

@@ -221,6 +221,10 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
         if (p.g) DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_GATED>), gpers, NTC, SM::bytes, sm, pb.H, p, pb.chunks_ub);
         else if (p.pro) DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_PROLOGUE>), gpers, NTC, SM::bytes_pro, sm, pb.H, p, pb.chunks_ub);
         else DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_PLAIN>), gpers, NTC, SM::bytes, sm, pb.H, p, pb.chunks_ub);
+        if (p.dv_out) { // the inputs have been read
+            const long words = (long)(pb.cu ? 1 : pb.N) * pb.L * pb.H * DV * (long)sizeof(T) / 4; // (rows are at least 64 bytes)
+            DN_LAUNCH(k_state_copy, dim3((unsigned)((words + 4 * NTHR - 1) / (4 * NTHR))), 0, static_cast<float *>(p.dv_out), static_cast<const float *>(p.dv), words);
+        }
     }
     return 0;
 }
