@@ -597,7 +597,10 @@ __device__ inline void tri_inverse_64(float *sX, int ld) {
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) blk[i * ld + j] = x[i];
-        // 16 -> 32 (LDS accesses of one wavefront stay in order: no barrier)
+        // 16 -> 32, from what other lanes of this wavefront have just stored.  The hardware keeps a wavefront's LDS accesses in
+        // order, so no barrier is needed; the compiler has to be told (per lane the addresses look unrelated).
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         f32x4 m0 = {0.f, 0.f, 0.f, 0.f}, m1 = m0, y0 = m0, y1 = m0;
         float *d0 = sX, *d1 = sX + 32 * (ld + 1);
         mma16_lds(m0, d0 + 16 * ld, d0, ld);
