@@ -53,18 +53,9 @@ def kernel_flops_per_chunk_head(name: str, d: int, c: int = C) -> float:
         return (4 * c * d * d + 4 * c * c * d) + (6 * c * d * d + 8 * c * c * d)
     if "k_scan_fwd" in name:     # T K, T V, Q K^T, P Ut (4 x 2C^2 d); W S, Q S, K^T Ut (3 x 2Cd^2)
         return 6 * c * d * d + 8 * c * c * d
-    if "k_bwd_stream" in name:
-        # K S, K dS', dO S^T, Ut dS'^T, dV S^T (5 x 2Cd^2); T R, P^T dO, X^T dUt, dO Ut^T, dUt R^T, Q K^T, dP K, dP^T Q,
-        # K K^T, Ah K, Ah^T K (11 x 2C^2 d); dX X^T, X^T M1 (2 x 2C^3)
-        return 10 * c * d * d + 22 * c * c * d + 4 * c ** 3
     if "k_bwd_local" in name:
-        # dO S^T, dV S^T, Ut dS'^T (3 x 2Cd^2); dO Ut^T, dV Ut^T, dP K, dP^T Q, (Ah + Ah^T) K (5 x 2C^2 d)
-        return 6 * c * d * d + 10 * c * c * d
-    if "k_bwd_chunk" in name:    # the form through the inverse that k_bwd_local replaced
-        # adjoint of Eq. 8-9: dO S^T, dUt S^T, Ut dS^T (3 x 2Cd^2); dO Ut^T, dP K, dP^T Q (3 x 2C^2 d)
-        # adjoint of Eq. 10-11: K K^T, dW K^T, dU V^T, X^T dW, X^T dU, Ah K, Ah^T K (7 x 2C^2 d);
-        #                       dX X^T, X^T M1 (2 x 2C^3); forward substitution (2/3 C^3)
-        return 6 * c * d * d + 20 * c * c * d + 4 * c ** 3 + (2.0 / 3.0) * c ** 3
+        # K S, dO S^T, dV S^T, Ut dS'^T (4 x 2Cd^2); K K^T, dO Ut^T, dV Ut^T, dP K, dP^T Q, (Ah + Ah^T) K (6 x 2C^2 d)
+        return 8 * c * d * d + 12 * c * c * d
     return 0.0
 
 
@@ -78,18 +69,14 @@ def kernel_bytes_per_chunk_head(name: str, d: int, c: int = C, es: int = 2) -> f
         return tile + beta + cc
     if "k_scan_fwd_save" in name:  # Q, K, V, T -> O, Ut, S
         return 3 * tile + cc + 2 * tile + st
-    if "k_scan_bwd" in name:     # Q, K, dO, T -> dV, dS'
-        return 3 * tile + cc + tile + st
-    if "k_scan_pair" in name:    # K, V, T -> Ut, S   and   Q, K, dO, T -> dV, dS'
-        return (2 * tile + cc + tile + st) + (3 * tile + cc + tile + st)
+    if "k_scan_bwd" in name:     # Q, K, dO, T, beta -> dV, dS'
+        return 3 * tile + cc + beta + tile + st
+    if "k_scan_pair" in name:    # K, V, T -> Ut, S   and   Q, K, dO, T, beta -> dV, dS'
+        return (2 * tile + cc + tile + st) + (3 * tile + cc + beta + tile + st)
     if "k_scan_fwd" in name:     # Q, K, V, T -> O
         return 3 * tile + cc + tile
-    if "k_bwd_stream" in name:   # dO, K, Q, V, S, dS', X, beta -> dQ, dK, dV, dbeta
-        return 4 * tile + 2 * st + cc + beta + 3 * tile + c * 4
-    if "k_bwd_local" in name:    # dO, dV, Ut, K, Q, S, dS', beta -> dQ, dK, dbeta
-        return 5 * tile + 2 * st + beta + 2 * tile + c * 4
-    if "k_bwd_chunk" in name:    # dO, Ut, dUt, K, Q, V, S, dS', X, beta -> dQ, dK, dV, dbeta
-        return 6 * tile + 2 * st + cc + beta + 3 * tile + c * 4
+    if "k_bwd_local" in name:    # dO, dV, Ut, V, K, Q, S, dS', beta -> dQ, dK, dbeta
+        return 6 * tile + 2 * st + beta + 2 * tile + c * 4
     return 0.0
 
 
@@ -103,14 +90,12 @@ def kernel_algorithmic_bytes_per_token_head(name: str, d: int, es: int = 2) -> f
         return row + b_in
     if "k_scan_fwd" in name:                         # the forward pass: q, k, v, beta -> o
         return 3 * row + b_in + row
-    if "k_scan_bwd" in name:                         # q, k, do
-        return 3 * row
-    if "k_scan_pair" in name:                        # q, k, do and (recompute) k, v
-        return 5 * row
-    if "k_bwd_local" in name:                        # q, k, beta, do -> dq, dk, dbeta (dv leaves in the reverse scan)
-        return 3 * row + b_in + 2 * row + b_out
-    if "k_bwd_chunk" in name or "k_bwd_stream" in name:   # the backward pass: q, k, v, beta, do -> dq, dk, dv, dbeta
-        return 4 * row + b_in + 3 * row + b_out
+    if "k_scan_bwd" in name:                         # q, k, beta, do -> dv
+        return 3 * row + b_in + row
+    if "k_scan_pair" in name:                        # q, k, beta, do -> dv and (recompute) k, v
+        return 5 * row + b_in + row
+    if "k_bwd_local" in name:                        # q, k, v, beta, do -> dq, dk, dbeta
+        return 4 * row + b_in + 2 * row + b_out
     return 0.0
 
 

@@ -144,13 +144,10 @@ int deltanet_bwd_saved(const dn_shape *shape, const void *q, const void *k, cons
  *     q_t = SiLU(q_pre_t) / ||SiLU(q_pre_t)||_2 ,  k_t likewise,  beta_t = sigmoid(beta_logit_t)
  *
  * per token and head (fp32 arithmetic, result rounded to the element type).  The kernel that builds T
- * maps q and k once and leaves them in the workspace for the chain scans; the backward's chunk kernel
- * maps its tiles on their way to the LDS and sends dq, dk back through the map on their way out, so at head
- * sizes up to 128 the gradients never reach HBM in the mapped coordinates and no separate elementwise pass runs
- * in either direction.  At head size 256 the way back is not fused: the chunk kernel writes dq, dk in the mapped
- * coordinates (element type dtype) and one more kernel per tensor takes them through the map in place, so those
- * two gradients are rounded to the element type twice.  A row whose SiLU image is exactly zero maps to zero (the
- * paper gives no epsilon).
+ * maps q and k once and leaves them in the workspace for the chain scans and the backward's chunk kernel, which
+ * sends dq, dk back through the map on their way out, so the gradients never reach HBM in the mapped coordinates
+ * and no separate elementwise pass runs in either direction.  A row whose SiLU image is exactly zero maps to zero
+ * (the paper gives no epsilon).
  * deltanet_fused_bwd returns the gradients with respect to q_pre, k_pre and beta_logit (through the
  * normalisation, the SiLU and the sigmoid) in dq_pre, dk_pre (element type dtype) and dbeta_logit
  * (fp32); dv and dinitial_state are as for deltanet_bwd.  Workspace (and `saved`) sizes come from

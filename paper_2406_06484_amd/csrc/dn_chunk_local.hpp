@@ -21,9 +21,10 @@
 // moved to LDS the same registers request the block NS blocks on (of the workgroup's next chunk, at the end), so about one
 // chunk's worth of loads (d = 128; NS blocks at d = 256) is in flight at any time.
 // Per chunk and head 192 KB through HBM at d = 128 in bf16 (read q, k, v, dO, dV, Ut, S, dS'; write dq, dk).  Kernel time at
-// 16 384 tokens of width 2048, with the shorter form of dbeta (no V, no products K S and K K^T) and now: d = 128 147 -> 170 us
-// (4.6 TB/s), d = 64 116 -> 130, d = 256 200 -> 224, gated 196 -> 207, prologue 187 -> 213.  Of the 23 us at d = 128 the product
-// K S takes 12 (10 since it is formed transposed), K K^T 7, V 3.
+// 16 384 tokens of width 2048, with the shorter form of dbeta (no V, no products K S and K K^T) and now, between event records:
+// d = 128 147 -> 171 us, d = 64 116 -> 132, d = 256 200 -> 213, gated 196 -> 218, prologue 187 -> 212.  In a kernel trace d = 128
+// takes 161 us for 836 MB of counted traffic: 5.2 TB/s, the rate of a large copy, which is what bounds it.  (The kernel that went
+// through the inverse, with eleven barrier intervals a chunk where this one has six: 200, 224, 249, 229, 233 us between records.)
 #pragma once
 #include <type_traits>
 
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
         // dbeta and dV of the masked rows, over the columns of block vb, by the waves that have just formed (K S)^T: the
         // accumulators of a lane are 16 columns of its token i, so each of
         //     e_i = v_i - S^T k_i - sum_{j<i} (k_i . k_j) Ut_j,   G_i = dUt_i - sum_{j>i} (k_i . k_j) dV_j
-        // is one more product with tril(K K^T, -1) and four loads, and G_i . e_i a sum over registers.  In sDV the masked rows
+        // is one more product with tril(K K^T, -1) and four loads per lane, and G_i . e_i a sum over registers.  In sDV the masked rows
         // are zero so far (dV_i = beta_i G_i, and beta_i is zero but for the tiny ones, which are filled in at the end).
         // Ut_i = beta_i e_i holds for them as for any row, so nothing else of the chunk is touched.  A training step on 16 384
         // tokens of width 2048 without masked tokens, with a tenth of them masked, and padded to twice the shortest length:

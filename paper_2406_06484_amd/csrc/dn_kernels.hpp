@@ -1,8 +1,8 @@
 // The kernels of the chunkwise DeltaNet forward/backward (gfx950), templated on the element
 // type T (float: fp32 MFMA; bf16: bf16 MFMA with fp32 accumulation) and the head dims.
 //
-//   k_wy_prep    per chunk            A = tril(diag(beta) K K^T,-1); X = (I+A)^-1; T = X diag(beta); P = tril(Q K^T)   (Eq. 10)
-//   k_scan_fwd   per chain x v-block  serial over chunks: W = T K, U = T V (Eq. 11); Ut = U - W S; O = Q S + P Ut; S += K^T Ut  (Eq. 8-9)
+//   k_wy_prep    per chunk            A = tril(diag(beta) K K^T,-1); X = (I+A)^-1; T = X diag(beta)   (Eq. 10)
+//   k_scan_fwd   per chain x v-block  serial over chunks: W = T K, U = T V (Eq. 11); Ut = U - W S; P = tril(Q K^T); O = Q S + P Ut; S += K^T Ut  (Eq. 8-9)
 //   k_scan_pair  per chain x v-block  backward: the state-recompute scan (stores chunk-initial S and Ut) and the reverse
 //                                     scan (dUt = P^T dO + K dS'; dV = T^T dUt; dS = dS' + Q^T dO - W^T dUt) as one grid
 //   k_scan_fwd_save / k_scan_bwd      the forward scan that also stores what the recompute scan would, and the reverse
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
     if (p.g && tid < C) {
         // Gated variant: with the running decay exp(g_1 + ... + g_i) within the chunk (rows past the end keep the last
         // value), the state divided by it follows the plain delta rule on equally divided values, so the other kernels
-        // only rescale rows with gamma_i and 1 / gamma_i; T and X do not depend on the gate.  The table holds the decay
+        // only rescale rows with gamma_i and 1 / gamma_i; T does not depend on the gate.  The table holds the decay
         // relative to the chunk's geometric middle, gamma_i = exp(g_1 + ... + g_i - (g_1 + ... + g_C) / 2): both
         // gamma_i and 1 / gamma_i then stay within exp(+-sum|g| / 2), which doubles the decay per chunk that fp32 holds.
         // The chain scans move the state into these coordinates when a chunk begins (factor gamma_C, which in them is

@@ -92,12 +92,14 @@ template <typename T, int DK, int DV> size_t max_lds_bytes() {
 // Scans of few chains (`wide` = workgroups of the grid with the ordinary column blocks) run with blocks half as wide: the
 // workgroups still fit the chip at once, and the step of each, whose length is the longest of a chain of products, is shorter.
 // The tiles are formed by the same products in the same order, so the results are the same bits.
-// Measured, d = 128, 16 heads, wide and narrow: forward pass of 1 x 1000 tokens 43.6 and 38.8 us, 4 x 2000 (the line, half the
-// chip) 84.7 and 75.8, training step 97.8 and 86.7, 250.8 and 232.8; beyond the line two rounds (8 x 2048: 104 and 155 us).
-// With d_k = 64 a forward pass that keeps no tiles has its line at a quarter of the chip: between the two it gains 3 us, but a
-// backward pass behind it loses more (its output, in half lines, is written back then): 4 x 2000 of 32 heads, gated, forward and
-// backward pass with recomputation 271 and 277 us.  Segmented scans (sm.N > pb.N) keep the ordinary blocks: little to
-// gain in their short steps (1 x 1024: forward pass 52.8 and 51.1 us, training step 112.2 and 113.0).
+// Measured, d = 128, 16 heads, wide and narrow: forward pass of 1 x 1000 tokens 43.5 and 38.7 us, 4 x 2000 (the line, half the
+// chip) 84.0 and 81.4, training step 101 and 92, 266 and 247; beyond the line two rounds (8 x 2048: 104 and 155 us).
+// With d_k = 64 a forward pass that keeps no tiles has its line at a quarter of the chip.  Between the two, 4 x 2000 of 32 heads,
+// wide and narrow: alone it is 72.7 and 69.5 us (gated 84.1 and 86.1), but a backward pass behind it loses what it gains (its
+// output, in half lines, is written back then): gated, with recomputation, 275 and 276 us.  Segmented scans (sm.N > pb.N) keep
+// the ordinary blocks: little to gain in their short steps (1 x 1024: forward pass 52.8 and 51.1 us, training step 112.2 and
+// 113.0).  The line of the segments themselves (segment_count) is older than the narrow blocks and lies too low for short
+// sequences: 1 x 1024 takes 51.5, 113 and 130 us (forward, training step, with recomputation), the uncut 1 x 1000 38.7, 92 and 97.
 static inline bool narrow_blocks(const Problem &pb, const SeqMap &sm, unsigned wide, int share) {
     return sm.N == pb.N && (long)wide * share <= pb.num_cus;
 }
@@ -207,7 +209,7 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
                 if (int e = launch_bwd_scans<T, DK, DV>(pb, sg, p, ps, gseg.x)) return e;
             }
         }
-    } else if (pb.save) { // T, X, Ut and the chunk-initial states are the forward pass's: only the reverse scan is left
+    } else if (pb.save) { // T, Ut and the chunk-initial states are the forward pass's: only the reverse scan is left
         if (int e = launch_bwd_scans<T, DK, DV>(pb, sm, p, ps, gchain.x)) return e;
     } else {
         if (pb.chunks_ub) if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;

@@ -1,9 +1,8 @@
 #!/usr/bin/env python3
 """Turns the rocprofv3 CSVs of the benchmark's profiling runs into the short text summaries under profiles/.
 
-Run the commands below from the repo root on the GPU machine; RAW = a scratch directory for the raw profiler output (each counter pass is a run of its own; rocprofv3 does not
-split counters over passes), RAW being a scratch directory for the raw profiler output, then
-`python3 profile_summary.py $RAW`.
+Run the commands below from the repo root on a machine with the GPU, RAW being a scratch directory for the raw profiler output
+(each counter pass is a run of its own; rocprofv3 does not split counters over passes), then `python3 profile_summary.py $RAW`.
 
   P="python3 bench.py --mode headline --no-cpu-baseline"
   rocprofv3 --kernel-trace --stats -d $RAW/trace -o trace --output-format csv -- $P --steps 20 --warmup 5
@@ -11,10 +10,6 @@ split counters over passes), RAW being a scratch directory for the raw profiler 
   rocprofv3 --pmc WRITE_SIZE --kernel-trace -d $RAW/write -o write --output-format csv -- $P --steps 3 --warmup 1 --copy-calibration
   rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES SQ_INSTS_VALU_MFMA_MOPS_BF16 GRBM_GUI_ACTIVE --kernel-trace -d $RAW/mfma -o mfma --output-format csv -- $P --steps 3 --warmup 1
   rocprofv3 --pmc SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_ACTIVE_INST_LDS SQ_WAVE_CYCLES --kernel-trace -d $RAW/lds -o lds --output-format csv -- $P --steps 3 --warmup 1
-  S="python3 bench.py --mode streamed --no-cpu-baseline"      (the same step under DN_OPT_STREAMED_CHUNK_KERNEL)
-  rocprofv3 --kernel-trace --stats -d $RAW/trace_s -o trace_s --output-format csv -- $S --steps 20 --warmup 5
-  rocprofv3 --pmc FETCH_SIZE --kernel-trace -d $RAW/fetch_s -o fetch_s --output-format csv -- $S --steps 3 --warmup 1 --copy-calibration
-  rocprofv3 --pmc WRITE_SIZE --kernel-trace -d $RAW/write_s -o write_s --output-format csv -- $S --steps 3 --warmup 1 --copy-calibration
 
   rocprofv3 --pmc SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_ACTIVE_INST_LDS SQ_INSTS_LDS --kernel-trace -d $RAW/lds_patterns -o lds_patterns --output-format csv -- python3 bench_lds_patterns.py
 
@@ -25,8 +20,8 @@ split counters over passes), RAW being a scratch directory for the raw profiler 
   rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES SQ_INSTS_VALU_MFMA_MOPS_BF16 GRBM_GUI_ACTIVE --kernel-trace -d $RAW/hs64_mfma -o hs64_mfma --output-format csv -- $H
 
 bench.py --mode headline runs the timed step (deltanet_fwd_save + deltanet_bwd_saved: k_wy_prep, k_scan_fwd_save,
-k_scan_bwd, k_bwd_chunk) and the self-contained pair (deltanet_fwd + deltanet_bwd: k_wy_prep, k_scan_fwd; k_wy_prep,
-k_scan_pair, k_bwd_chunk) and nothing else, so every row below belongs to one of the two.
+k_scan_bwd, k_bwd_local) and the self-contained pair (deltanet_fwd + deltanet_bwd: k_wy_prep, k_scan_fwd; k_wy_prep,
+k_scan_pair, k_bwd_local) and nothing else, so every row below belongs to one of the two.
 """
 from __future__ import annotations
 
@@ -40,16 +35,14 @@ import sys
 ROOT = os.path.dirname(os.path.abspath(__file__))
 PROF = os.path.abspath(sys.argv[1]) if len(sys.argv) > 1 else os.path.join(ROOT, "prof_raw")
 OUT = os.path.join(ROOT, "profiles")
-W = "bench.py --mode headline (configs[2]: bf16 fwd+bwd, B=8, L=2048, H=16, d=128, chunk 64), MI355X"
+W = "bench.py --mode headline (bf16 fwd+bwd, B=8, L=2048, H=16, d=128, chunk 64), MI355X"
 COPY = "__amd_rocclr_copyBuffer"
 ALG_STEP_BYTES = 2824 * 8 * 2048 * 16   # inputs read once, outputs written once: 1026 + 1798 B per token and head
-KEY = """kernel name key: k_wy_prep = T (Eq. 10) and, where a backward pass follows, X per chunk; k_scan_fwd_save = forward chain
-scan (Eq. 8-9) that also leaves Ut and the chunk-initial states in the buffer; k_scan_bwd = reverse scan carrying dS;
-k_bwd_chunk = chunk-local adjoint of Eq. 8-11.  These four are the timed step (deltanet_fwd_save + deltanet_bwd_saved).
-The self-contained pair runs k_wy_prep twice (forward: T only; backward: T and X), k_scan_fwd (forward scan without the
-stores), k_scan_pair (the backward pass's recompute scan and reverse scan in one grid) and k_bwd_chunk.  k_wy_prep rows are
-split by what follows them in the dispatch order.  k_bwd_stream (streamed runs) = the chunk kernel that reads S and dS'
-in blocks of 32 state columns and rebuilds Ut, dUt on chip; under that option the scans do not store Ut, dUt.
+KEY = """kernel name key: k_wy_prep = T (Eq. 10) per chunk; k_scan_fwd_save = forward chain scan (Eq. 8-9) that also leaves Ut and
+the chunk-initial states in the buffer; k_scan_bwd = reverse scan carrying dS, stores dV and dS'; k_bwd_local = the rest of the
+adjoint, local to a chunk.  These four are the timed step (deltanet_fwd_save + deltanet_bwd_saved).  The self-contained pair runs
+k_wy_prep twice, k_scan_fwd (forward scan without the stores), k_scan_pair (the backward pass's recompute scan and reverse
+scan in one grid) and k_bwd_local.  k_wy_prep rows are split by what follows them in the dispatch order.
 """
 
 
@@ -74,7 +67,7 @@ def labelled(rows, name_key):
         nm = r[name_key]
         if "k_wy_prep" in nm:
             nxt = next((short(x[name_key]) for x in rows[i + 1:] if x[name_key].startswith("_ZN2dn") and "k_wy_prep" not in x[name_key]), "")
-            lab = {"k_scan_fwd_save": "k_wy_prep", "k_scan_fwd": "k_wy_prep(fwd, T only)", "k_scan_pair": "k_wy_prep(bwd, T and X)"}.get(nxt, "k_wy_prep")
+            lab = {"k_scan_fwd_save": "k_wy_prep", "k_scan_fwd": "k_wy_prep(fwd)", "k_scan_pair": "k_wy_prep(bwd)"}.get(nxt, "k_wy_prep")
         elif nm.startswith("_ZN2dn"):
             lab = short(nm)
         elif COPY in nm:
@@ -113,9 +106,8 @@ def trace_means(sub: str):
     return {k: (len(v), sum(v) / len(v), min(v), max(v)) for k, v in acc.items()}
 
 
-STEP = ["k_wy_prep", "k_scan_fwd_save", "k_scan_bwd", "k_bwd_chunk"]
-STEP_S = ["k_wy_prep", "k_scan_fwd_save", "k_scan_bwd", "k_bwd_stream"]
-PAIR = ["k_wy_prep(fwd, T only)", "k_scan_fwd", "k_wy_prep(bwd, T and X)", "k_scan_pair", "k_bwd_chunk"]
+STEP = ["k_wy_prep", "k_scan_fwd_save", "k_scan_bwd", "k_bwd_local"]
+PAIR = ["k_wy_prep(fwd)", "k_scan_fwd", "k_wy_prep(bwd)", "k_scan_pair", "k_bwd_local"]
 
 
 def write_trace():
@@ -123,7 +115,7 @@ def write_trace():
     if tr is None:
         return
     with open(os.path.join(OUT, "kernel_trace_cfg2_fwd_bwd.txt"), "w") as f:
-        f.write("rocprofv3 kernel-trace summary: %s\n\ncommand (from the repo root on the GPU box; RAW = a scratch directory for the raw profiler output), then python3 profile_summary.py $RAW:\n"
+        f.write("rocprofv3 kernel-trace summary: %s\n\ncommand (from the repo root; RAW = a scratch directory for the raw profiler output), then python3 profile_summary.py $RAW:\n"
                 "  rocprofv3 --kernel-trace --stats -d $RAW/trace -o trace --output-format csv -- python3 bench.py --mode headline --no-cpu-baseline --steps 20 --warmup 5\n\n" % W)
         f.write("%-28s %7s %12s %10s %10s\n" % ("kernel", "calls", "avg_ns", "min_ns", "max_ns"))
         for k, (n, avg, lo, hi) in tr.items():
@@ -131,13 +123,6 @@ def write_trace():
                 f.write("%-28s %7d %12.0f %10d %10d\n" % (k, n, avg, lo, hi))
         f.write("\nsum of kernel time per step (deltanet_fwd_save + deltanet_bwd_saved): %.1f us; per self-contained fwd+bwd: %.1f us\n"
                 % (sum(tr[k][1] for k in STEP if k in tr) / 1e3, sum(tr[k][1] for k in PAIR if k in tr) / 1e3))
-        ts = trace_means("trace_s")
-        if ts is not None:
-            f.write("\nthe same step under DN_OPT_STREAMED_CHUNK_KERNEL (bench.py --mode streamed, same flags, -d $RAW/trace_s -o trace_s):\n")
-            for k in STEP_S:
-                if k in ts:
-                    f.write("%-28s %7d %12.0f %10d %10d\n" % ((k,) + ts[k]))
-            f.write("sum of kernel time per step: %.1f us\n" % (sum(ts[k][1] for k in STEP_S if k in ts) / 1e3))
         f.write("\n" + KEY)
 
 
@@ -157,7 +142,7 @@ def write_traffic():
         return
     tab, (cf, cw, ff, wf) = res
     with open(os.path.join(OUT, "hbm_traffic_cfg2_fwd_bwd.txt"), "w") as f:
-        f.write("rocprofv3 --pmc HBM traffic per launch: %s\n\ncommands (from the repo root on the GPU box; RAW = a scratch directory for the raw profiler output; one counter per run), then python3 profile_summary.py $RAW:\n"
+        f.write("rocprofv3 --pmc HBM traffic per launch: %s\n\ncommands (from the repo root; RAW = a scratch directory for the raw profiler output; one counter per run), then python3 profile_summary.py $RAW:\n"
                 "  rocprofv3 --pmc FETCH_SIZE --kernel-trace -d $RAW/fetch -o fetch --output-format csv -- python3 bench.py --mode headline --no-cpu-baseline --steps 3 --warmup 1 --copy-calibration\n"
                 "  rocprofv3 --pmc WRITE_SIZE --kernel-trace -d $RAW/write -o write --output-format csv -- python3 bench.py --mode headline --no-cpu-baseline --steps 3 --warmup 1 --copy-calibration\n\n" % W)
         f.write("calibration: a plain 256 MiB device copy (%s) reads FETCH_SIZE = %.1f and WRITE_SIZE = %.1f (KiB);\n"
@@ -172,24 +157,10 @@ def write_traffic():
         f.write("\nHBM bytes per step (deltanet_fwd_save + deltanet_bwd_saved): %.1f MB; per self-contained fwd+bwd: %.1f MB;\n"
                 "the algorithmic minimum (inputs read once, outputs written once) is 2824 B per token per head = %.1f MB.\n"
                 % (step, pair, ALG_STEP_BYTES / 1e6))
-        res_s = traffic_table("fetch_s", "write_s")
-        if res_s is not None:
-            tab_s = res_s[0]
-            f.write("\nthe same step under DN_OPT_STREAMED_CHUNK_KERNEL (bench.py --mode streamed; -d $RAW/fetch_s -o fetch_s, write_s likewise):\n")
-            tot = 0.0
-            for k in STEP_S:
-                if k in tab_s:
-                    m = (tab_s[k][0] + tab_s[k][1]) * 1024 / 1e6
-                    tot += m
-                    f.write("%-28s %14.0f %14.0f %12.1f\n" % (k, tab_s[k][0], tab_s[k][1], m))
-            f.write("HBM bytes per step: %.1f MB\n" % tot)
         f.write("\nbytes per launch as bench.py reads them (the headline step's kernels, and the self-contained pair's own two):\n")
         for k in STEP + ["k_scan_fwd", "k_scan_pair"]:
             if k in mb:
                 f.write("traffic_bytes %s %d\n" % (k, round(mb[k] * 1e6)))
-        if res_s is not None and "k_bwd_stream" in res_s[0]:
-            a, b = res_s[0]["k_bwd_stream"]
-            f.write("traffic_bytes k_bwd_stream %d\n" % round((a + b) * 1024))
         f.write("\n" + KEY)
 
 
@@ -198,7 +169,7 @@ def write_counters():
     if mf is None or ld is None:
         return
     with open(os.path.join(OUT, "mfma_lds_counters_cfg2_fwd_bwd.txt"), "w") as f:
-        f.write("rocprofv3 --pmc MFMA and LDS counters per launch: %s\n\ncommands (from the repo root on the GPU box; RAW = a scratch directory for the raw profiler output; one pass per run), then python3 profile_summary.py $RAW:\n"
+        f.write("rocprofv3 --pmc MFMA and LDS counters per launch: %s\n\ncommands (from the repo root; RAW = a scratch directory for the raw profiler output; one pass per run), then python3 profile_summary.py $RAW:\n"
                 "  rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES SQ_INSTS_VALU_MFMA_MOPS_BF16 GRBM_GUI_ACTIVE --kernel-trace -d $RAW/mfma -o mfma --output-format csv -- python3 bench.py --mode headline --no-cpu-baseline --steps 3 --warmup 1\n"
                 "  rocprofv3 --pmc SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_ACTIVE_INST_LDS SQ_WAVE_CYCLES --kernel-trace -d $RAW/lds -o lds --output-format csv -- python3 bench.py --mode headline --no-cpu-baseline --steps 3 --warmup 1\n\n" % W)
         f.write("Averages per launch.  GRBM_GUI_ACTIVE is summed over the 8 XCDs; SQ_VALU_MFMA_BUSY_CYCLES over the 1024 SIMDs.\n"
@@ -233,7 +204,7 @@ def write_lds_patterns():
     with open(os.path.join(OUT, "lds_conflicts_by_access_pattern.txt"), "w") as f:
         f.write("LDS counters of the access patterns the kernels are built from, one probe kernel per pattern (deltanet_lds_probe: the\n"
                 "kernels' own helpers at the kernels' own leading dimensions, 8 wavefronts per workgroup, bf16 tiles), MI355X\n\n"
-                "command (from the repo root on the GPU box; RAW = a scratch directory for the raw profiler output), then python3 profile_summary.py $RAW:\n"
+                "command (from the repo root; RAW = a scratch directory for the raw profiler output), then python3 profile_summary.py $RAW:\n"
                 "  rocprofv3 --pmc SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_ACTIVE_INST_LDS SQ_INSTS_LDS --kernel-trace -d $RAW/lds_patterns -o lds_patterns --output-format csv -- python3 bench_lds_patterns.py\n\n"
                 "conflict = SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE (the ratio profiles/mfma_lds_counters_cfg2_fwd_bwd.txt gives per kernel);\n"
                 "idx/inst = SQ_LDS_IDX_ACTIVE / SQ_INSTS_LDS: cycles the LDS spends indexing one instruction of the pattern.  An instruction\n"
@@ -265,7 +236,7 @@ def write_head_sizes():
     with open(os.path.join(OUT, "tiling_head_size_counters.txt"), "w") as f:
         f.write("Tiling study, head size: the training step that keeps the forward pass's tiles (deltanet_fwd_save + deltanet_bwd_saved) on\n"
                 "16384 tokens of model width 2048 (B = 8, L = 2048, H = 2048 / d, bf16, chunk 64), per kernel, MI355X\n\n"
-                "commands (from the repo root on the GPU box; RAW = a scratch directory for the raw profiler output; d = 64 and 256 shown, one pass per run; d = 128 is the headline step, whose\n"
+                "commands (from the repo root; RAW = a scratch directory for the raw profiler output; d = 64 and 256 shown, one pass per run; d = 128 is the headline step, whose\n"
                 "passes are listed in profiles/kernel_trace_cfg2_fwd_bwd.txt and its neighbours), then python3 profile_summary.py $RAW:\n"
                 "  P=\"python3 bench_speedup_sweep.py --head-sizes 64 --lengths 2048 --only-kept --steps 20\"     (and --head-sizes 256, hs256_*)\n"
                 "  rocprofv3 --kernel-trace --stats -d $RAW/hs64_trace -o hs64_trace --output-format csv -- $P\n"
@@ -278,7 +249,7 @@ def write_head_sizes():
         for d in (64, 128, 256):
             tr = trace_means(subs[d] % "trace")
             fe, wr, mf = counter_means(subs[d] % "fetch"), counter_means(subs[d] % "write"), counter_means(subs[d] % "mfma")
-            step = ["k_wy_prep", "k_scan_fwd_save", "k_scan_bwd", "k_bwd_chunk_wide" if d == 256 else "k_bwd_chunk"]
+            step = ["k_wy_prep", "k_scan_fwd_save", "k_scan_bwd", "k_bwd_local"]
             tot_us = tot_mb = 0.0
             for k in step:
                 if k not in tr:
@@ -293,8 +264,8 @@ def write_head_sizes():
                 tot_mb += mb
             f.write("%4d  %-20s %9.1f %9.1f %8.2f\n\n" % (d, "step", tot_us, tot_mb, tot_mb / tot_us))
         f.write("TB/s = HBM_MB / avg_us.  At d = 64 a chain is one scan workgroup (256 chains), at d = 128 two (128 chains), at d = 256 eight\n"
-                "workgroups of 32 state columns (64 chains, 512 workgroups in two rounds); the chunk kernel keeps a chunk's operands in LDS\n"
-                "up to d = 128 and streams S and dS' in blocks of 32 state columns at d = 256 (k_bwd_chunk_wide).  Per token the matrix work\n"
+                "workgroups of 32 state columns (64 chains, 512 workgroups in two rounds); the chunk kernel walks the operands with a\n"
+                "d_v axis in blocks of 64 state columns, of 32 at d = 256.  Per token the matrix work\n"
                 "grows with d (model FLOPs 6 d^2 + ... per token and head, H = 2048 / d heads) while the bytes per token stay the same for\n"
                 "q, k, v, o and grow with d for the per-chunk states.\n")
 
