@@ -660,6 +660,12 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
     const Map m(wave);
     const bool loader = wave >= 4;
     const int lt = threadIdx.x - NTL;
+    // The dV tiles belong to the waves whose accumulators hold dUt; in fp32 to the two chain waves that own none (a product over
+    // 64 is 32 dependent steps of 64 cycles there, and the owners have one in the same interval; the reverse scan of 3 x 1500
+    // tokens, 8 heads of 64: 212 -> 180 us).
+    static_assert(sizeof(T) == 2 || Map::U_TILES == 2, "fp32 column blocks are 32 wide");
+    const int dvw = sizeof(T) == 2 ? wave : wave - 2, va = (dvw & 3) / Map::NVT, vb2 = (dvw & 3) % Map::NVT; // tile (va, vb2)
+    const bool does_dv = !STATE && dvw >= 0 && dvw < Map::U_TILES;
     // waves 0..3 build the tiles (pmi, pni) = (0,0), (0,1), (1,1), (1,0) of P^T; the last one is all zero
     const int pmi = wave >> 1, pni = (wave == 1) | (wave == 2);
 
@@ -783,20 +789,22 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         }
         // dV = T^T dUt (T^T is upper triangular), formed and sent by the chain waves: the loader waves have the next chunk's
         // tiles to move in this interval
-        if (!STATE && m.does_u) {
+        if (does_dv) {
             f32x16 dv = zero16();
-            if (m.ua == 0) mma<C, true, false, T, true, MB>(dv, sT, SM::LT, sDUT + 32 * m.ub * SM::LT, SM::LT);
-            else mma<32, true, false, T, true, MB>(dv, sT + 32 * SM::LT + 32, SM::LT, sDUT + 32 * m.ub * SM::LT + 32, SM::LT);
+            if (va == 0) mma<C, true, false, T, true, MB>(dv, sT, SM::LT, sDUT + 32 * vb2 * SM::LT, SM::LT);
+            else mma<32, true, false, T, true, MB>(dv, sT + 32 * SM::LT + 32, SM::LT, sDUT + 32 * vb2 * SM::LT + 32, SM::LT);
             if (DIAG) {
-                const float *fa = sDiag + 2 * (ic & 1) * C + 32 * m.ua + 4 * ((threadIdx.x & 63) >> 5), *fr = fa + C;
+                const int hh = (threadIdx.x & 63) >> 5;
+                const float *fa = sDiag + 2 * (ic & 1) * C + 32 * va + 4 * hh, *fr = fa + C;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    dv[e] += fa[8 * (e >> 2) + (e & 3)] * acc[e];
-                    if (sizeof(T) == 2) dv[e] += fr[8 * (e >> 2) + (e & 3)] * to_f32(from_f32<T>(acc[e]));
+                    const int r8 = 8 * (e >> 2) + (e & 3);
+                    if constexpr (sizeof(T) == 2) dv[e] += fa[r8] * acc[e] + fr[r8] * to_f32(from_f32<T>(acc[e]));
+                    else dv[e] += fa[r8] * sDUT[(32 * vb2 + (threadIdx.x & 31)) * SM::LT + 32 * va + 4 * hh + r8]; // (nothing is rounded on the way to LDS)
                 }
             }
-            if (gated) acc_each(dv, [&](int rr, int, float &val) { val *= sGi[(ic & 1) * C + 32 * m.ua + rr]; }); // v_i = gamma_i v~_i
-            acc_store<T, kWholeLines>(stg, (T *)p.dv + (((long)t0 + (long)ic * C) * H + h) * DV + vb, (long)H * DV, 32 * m.ua, 32 * m.ub, min(C, len - ic * C), dv);
+            if (gated) acc_each(dv, [&](int rr, int, float &val) { val *= sGi[(ic & 1) * C + 32 * va + rr]; }); // v_i = gamma_i v~_i
+            acc_store<T, kWholeLines>(stg, (T *)p.dv + (((long)t0 + (long)ic * C) * H + h) * DV + vb, (long)H * DV, 32 * va, 32 * vb2, min(C, len - ic * C), dv);
         }
     }
     if (p.dS0 && m.has_s) {
