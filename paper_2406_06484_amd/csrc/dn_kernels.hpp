@@ -662,7 +662,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
     const int lt = threadIdx.x - NTL;
     // The dV tiles belong to the waves whose accumulators hold dUt; in fp32 to the two chain waves that own none (a product over
     // 64 is 32 dependent steps of 64 cycles there, and the owners have one in the same interval; the reverse scan of 3 x 1500
-    // tokens, 8 heads of 64: 212 -> 180 us).
+    // tokens, 8 heads of 64: 212 -> 170 us).
     static_assert(sizeof(T) == 2 || Map::U_TILES == 2, "fp32 column blocks are 32 wide");
     const int dvw = sizeof(T) == 2 ? wave : wave - 2, va = (dvw & 3) / Map::NVT, vb2 = (dvw & 3) % Map::NVT; // tile (va, vb2)
     const bool does_dv = !STATE && dvw >= 0 && dvw < Map::U_TILES;
@@ -791,20 +791,22 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         // tiles to move in this interval
         if (does_dv) {
             f32x16 dv = zero16();
-            if (va == 0) mma<C, true, false, T, true, MB>(dv, sT, SM::LT, sDUT + 32 * vb2 * SM::LT, SM::LT);
-            else mma<32, true, false, T, true, MB>(dv, sT + 32 * SM::LT + 32, SM::LT, sDUT + 32 * vb2 * SM::LT + 32, SM::LT);
-            if (DIAG) {
-                const int hh = (threadIdx.x & 63) >> 5;
+            int tx = threadIdx.x;
+            if (sizeof(T) == 4) asm volatile("" : "+v"(tx)); // (its addresses are formed here, not carried through the loop: no registers to spare)
+            if (va == 0) mma<C, true, false, T, true, MB>(dv, sT, SM::LT, sDUT + 32 * vb2 * SM::LT, SM::LT, tx);
+            else mma<32, true, false, T, true, MB>(dv, sT + 32 * SM::LT + 32, SM::LT, sDUT + 32 * vb2 * SM::LT + 32, SM::LT, tx);
+            if (DIAG && (sizeof(T) == 2 || __ballot(sDiag[2 * (ic & 1) * C + (tx & 63)] != 0.f))) { // (fp32: without a masked token there is no term)
+                const int hh = (tx & 63) >> 5;
                 const float *fa = sDiag + 2 * (ic & 1) * C + 32 * va + 4 * hh, *fr = fa + C;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int r8 = 8 * (e >> 2) + (e & 3);
                     if constexpr (sizeof(T) == 2) dv[e] += fa[r8] * acc[e] + fr[r8] * to_f32(from_f32<T>(acc[e]));
-                    else dv[e] += fa[r8] * sDUT[(32 * vb2 + (threadIdx.x & 31)) * SM::LT + 32 * va + 4 * hh + r8]; // (nothing is rounded on the way to LDS)
+                    else dv[e] += fa[r8] * sDUT[(32 * vb2 + (tx & 31)) * SM::LT + 32 * va + 4 * hh + r8]; // (nothing is rounded on the way to LDS)
                 }
             }
-            if (gated) acc_each(dv, [&](int rr, int, float &val) { val *= sGi[(ic & 1) * C + 32 * va + rr]; }); // v_i = gamma_i v~_i
-            acc_store<T, kWholeLines>(stg, (T *)p.dv + (((long)t0 + (long)ic * C) * H + h) * DV + vb, (long)H * DV, 32 * va, 32 * vb2, min(C, len - ic * C), dv);
+            if (gated) acc_each(dv, [&](int rr, int, float &val) { val *= sGi[(ic & 1) * C + 32 * va + rr]; }, tx); // v_i = gamma_i v~_i
+            acc_store<T, kWholeLines>(stg, (T *)p.dv + (((long)t0 + (long)ic * C) * H + h) * DV + vb, (long)H * DV, 32 * va, 32 * vb2, min(C, len - ic * C), dv, tx);
         }
     }
     if (p.dS0 && m.has_s) {
