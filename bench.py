@@ -46,13 +46,13 @@ def kernel_flops_per_chunk_head(name: str, d: int, c: int = C) -> float:
     if "k_wy_prep" in name:      # K K^T, forward substitution
         return 2 * c * c * d + (2.0 / 3.0) * c ** 3
     if "k_scan_fwd_save" in name:  # as k_scan_fwd
-        return 6 * c * d * d + 8 * c * c * d
-    if "k_scan_bwd" in name:     # T K, K Q^T, P^T dO, T^T dUt (4 x 2C^2 d); K dS, Q^T dO, W^T dUt (3 x 2Cd^2)
-        return 6 * c * d * d + 8 * c * c * d
-    if "k_scan_pair" in name:    # recompute scan: T K, T V, W S, K^T Ut; reverse scan as above
-        return (4 * c * d * d + 4 * c * c * d) + (6 * c * d * d + 8 * c * c * d)
-    if "k_scan_fwd" in name:     # T K, T V, Q K^T, P Ut (4 x 2C^2 d); W S, Q S, K^T Ut (3 x 2Cd^2)
-        return 6 * c * d * d + 8 * c * c * d
+        return 6 * c * d * d + 6 * c * c * d
+    if "k_scan_bwd" in name:     # K Q^T, P^T dO, T^T dUt (3 x 2C^2 d); K dS, Q^T dO, K^T dV (3 x 2Cd^2)
+        return 6 * c * d * d + 6 * c * c * d
+    if "k_scan_pair" in name:    # recompute scan: K S, T (V - K S), K^T Ut; reverse scan as above
+        return (4 * c * d * d + 2 * c * c * d) + (6 * c * d * d + 6 * c * c * d)
+    if "k_scan_fwd" in name:     # T (V - K S), Q K^T, P Ut (3 x 2C^2 d); K S, Q S, K^T Ut (3 x 2Cd^2)
+        return 6 * c * d * d + 6 * c * c * d
     if "k_bwd_local" in name:
         # K S, dO S^T, dV S^T, Ut dS'^T (4 x 2Cd^2); K K^T, dO Ut^T, dV Ut^T, dP K, dP^T Q, (Ah + Ah^T) K (6 x 2C^2 d)
         return 8 * c * d * d + 12 * c * c * d

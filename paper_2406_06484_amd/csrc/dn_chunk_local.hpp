@@ -75,6 +75,42 @@ template <typename T, int DK, int DV> struct LocalSmem {
 
 struct NoTile {};
 
+// A block of a tile that a scan left in the order of its operands (see dn_scan.hpp): COLS state columns of ROWS entries, in the
+// LDS as COLS rows of ROWS like every other tile
+template <typename T, int COLS, int ROWS, int NT> struct FragRegs {
+    static constexpr int KS = Op<T>::KS, VEC = Op<T>::VEC, NS = ROWS / KS, N = COLS * ROWS / VEC, NIT = N / NT;
+    static_assert(N % NT == 0, "whole rounds");
+    uint4 v[NIT];
+    __device__ inline void load_once(const T *src, int live, int t) {
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src);
+        const int voff = live ? 16 * t : kBufRange;
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) v[it] = buf_load16<kAuxOnce>(rs, voff, it * NT * 16);
+    }
+    template <bool SIGN = false> __device__ inline void store(T *dst, int ld, int t) const { // SIGN: with the sign of every element flipped
+        constexpr unsigned S = !SIGN ? 0u : sizeof(T) == 2 ? 0x80008000u : 0x80000000u;
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int e = it * NT + t, l = e & 63, s = (e >> 6) % NS, col16 = (e >> 6) / NS;
+            *reinterpret_cast<uint4 *>(dst + (16 * col16 + (l & 15)) * ld + KS * s + VEC * (l >> 4)) = make_uint4(v[it].x ^ S, v[it].y ^ S, v[it].z ^ S, v[it].w ^ S);
+        }
+    }
+    __device__ inline float dot(const FragRegs &o) const { // sum of the products of the elements held
+        float s = 0.f;
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            alignas(16) T a[VEC], b[VEC];
+            *reinterpret_cast<uint4 *>(a) = v[it];
+            *reinterpret_cast<uint4 *>(b) = o.v[it];
+            float d = 0.f;
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) d += to_f32(a[u]) * to_f32(b[u]);
+            s += d;
+        }
+        return s;
+    }
+};
+
 template <typename T, int DK, int DV, int VAR>
 __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSmem<T, DK, DV>::WPC))) void k_bwd_local(SeqMap sm, int H, Ptrs p, int chunks_total) {
     using SM = LocalSmem<T, DK, DV>;
@@ -116,10 +152,10 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
     typedef TileRegs<T, C, BVB, HALF ? 256 : NTC> TokTile; // a block of dO, dV or V
     static_assert(TokTile::NIT == 1 || sizeof(T) == 4 || !HALF, "one row per thread");
     struct Blk {
-        TileRegs<T, BVB, DK, NTC> s, ds;
+        FragRegs<T, BVB, DK, NTC> s, ds;
         TokTile a;                                            // dO (HALF: first half dO, second half dV)
         std::conditional_t<HALF, NoTile, TokTile> b;          // dV
-        TileRegs<T, BVB, C, HALF ? 256 : NTC> ut;             // (HALF: both halves hold a copy, the first one stores it)
+        FragRegs<T, BVB, C, HALF ? 256 : NTC> ut;             // (HALF: both halves hold a copy, the first one stores it)
         TokTile v;                                            // V, for v_i . dv_i (HALF: in the second half, beside dV)
         float gr[TokTile::NIT];                               // gated: gamma of this thread's rows
     } r[NS];
@@ -134,14 +170,14 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
     auto fetch_blk = [&](Blk &x, const TilePos &tp, int vb, int live) __attribute__((always_inline)) {
         const int v0 = vb * BVB, tt = HALF ? (tq & 255) : tq;
         const long row = (tp.row0 * H + tp.h) * DV + v0, tv = tp.tile * DV + v0;
-        x.s.load_once((const T *)p.Sc + tv * DK, DK, BVB * live, tq);
-        x.ds.load_once((const T *)p.dSc + tv * DK, DK, BVB * live, tq);
+        x.s.load_once((const T *)p.Sc + tv * DK, live, tq);
+        x.ds.load_once((const T *)p.dSc + tv * DK, live, tq);
         if constexpr (HALF) x.a.load_once((first_half ? (const T *)p.d_o : (const T *)p.dv) + row, (long)H * DV, tp.nvalid * live, tt);
         else {
             x.a.load_once((const T *)p.d_o + row, (long)H * DV, tp.nvalid * live, tq);
             x.b.load_once((const T *)p.dv + row, (long)H * DV, tp.nvalid * live, tq);
         }
-        x.ut.load_once((const T *)p.Ut + tv * C, C, BVB * live, tt);
+        x.ut.load_once((const T *)p.Ut + tv * C, live, tt);
         x.v.load_once((const T *)p.v + row, (long)H * DV, HALF && first_half ? 0 : tp.nvalid * live, tt);
         if constexpr (GATED) x.a.load_row_factors(x.gr, p.gam + tp.tile * 2 * C, tt);
     };
@@ -297,11 +333,11 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
             }
             // gated: the chunk is the plain rule on v_i / gamma_i with outputs gamma_i o~_i, so dO and dV rows come in scaled by gamma_i
             if constexpr (GATED) {
-                zs += x.ds.dot(x.s);
+                zs -= x.ds.dot(x.s);
                 x.a.scale_rows(x.gr);
                 if constexpr (!HALF) x.b.scale_rows(x.gr);
             }
-            x.s.store(sS, SM::LK, tq); x.ds.store(sDS, SM::LK, tq);
+            x.s.store(sS, SM::LK, tq); x.ds.template store<true>(sDS, SM::LK, tq); // (the reverse scan leaves -dS')
             if constexpr (HALF) {
                 if (first_half) { x.a.store(sDO, SM::LB, tq & 255); x.ut.store(sUt, SM::LU, tq & 255); }
                 else x.a.store_neg(sDV, SM::LB, tq & 255);

@@ -409,13 +409,6 @@ template <typename T, int ROWS, int COLS, int NT = NTHR> struct TileRegs {
         for (int u = 0; u < VEC; ++u) s += to_f32(a[u]) * to_f32(b[u]);
         return s;
     }
-    // sum over the elements this lane holds of (this tile) * (another held tile of the same shape)
-    __device__ inline float dot(const TileRegs &o) const {
-        float s = 0.f;
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) s += dot_row(o, it);
-        return s;
-    }
     // The query/key feature map of section 3.3 on the held tile, in place: every row x becomes
     // SiLU(x) / ||SiLU(x)||_2 (a row whose image is exactly zero, such as a row past the end, stays zero).
     // The TPR lanes that share a row are adjacent, so the row sum is a butterfly over them.
@@ -440,12 +433,6 @@ template <typename T, int ROWS, int COLS, int NT = NTHR> struct TileRegs {
             v[it] = *reinterpret_cast<const uint4 *>(e);
             __builtin_amdgcn_sched_barrier(0); // one step at a time: interleaved, the steps' temporaries do not fit
         }
-    }
-    // the same map, written to an LDS tile; the held tile keeps the pre-activations for feature_map_bwd_store
-    __device__ inline void feature_map_to(T *dst, int ld, float (&inv)[NIT], int t = threadIdx.x) const {
-        TileRegs y = *this;
-        y.feature_map(inv);
-        y.store(dst, ld, t);
     }
     // Gradient through the map, for a tile whose pre-activations x this object holds: src = dy in LDS
     // (same shape, leading dimension ld);
@@ -519,31 +506,6 @@ template <typename T, int ROWS, int COLS, int NT = NTHR> struct TileRegs {
         }
     }
 };
-// ---------------------------------------------------------------------------------------------
-// Global -> LDS: ROWS x COLS tile, 16-byte loads, rows >= nvalid become zero.
-template <typename T, int ROWS, int COLS>
-__device__ inline void load_tile(T *dst, int ld, const T *src, long row_stride, int nvalid) {
-    constexpr int VEC = El<T>::VEC, TPR = COLS / VEC, RPI = NTHR / TPR;
-    static_assert(COLS % VEC == 0 && NTHR % TPR == 0 && ROWS % RPI == 0, "tile shape");
-    TileRegs<T, ROWS, COLS> regs;
-    regs.load(src, row_stride, nvalid);
-    regs.store(dst, ld);
-}
-// LDS -> global copy of a ROWS x COLS tile by NT cooperating threads (t = index among them); the
-// destination is a contiguous row-major block
-template <typename T, int ROWS, int COLS, int NT, bool ONCE = false>
-__device__ inline void copy_out(T *dst, const T *src, int ld, int t) {
-    constexpr int VEC = El<T>::VEC, TPR = COLS / VEC, RPI = NT / TPR;
-    static_assert(COLS % VEC == 0 && NT % TPR == 0 && ROWS % RPI == 0, "tile shape");
-    const int tr = t / TPR, tc = (t % TPR) * VEC;
-#pragma unroll
-    for (int r0 = 0; r0 < ROWS; r0 += RPI) {
-        const u32x4 val = *reinterpret_cast<const u32x4 *>(src + (r0 + tr) * ld + tc);
-        u32x4 *to = reinterpret_cast<u32x4 *>(dst + (long)(r0 + tr) * COLS + tc);
-        if (ONCE) __builtin_nontemporal_store(val, to);
-        else *to = val;
-    }
-}
 // ---------------------------------------------------------------------------------------------
 // X = (I + A)^{-1} for a 64x64 strictly-lower-triangular A (section 3.2: the inverse of the unit
 // lower-triangular matrix of Eq. 10 by forward substitution), blockwise, fp32 throughout.

@@ -55,58 +55,47 @@ static inline int launch_offsets(const Problem &pb) {
     return 0;
 }
 
+// chain waves of the widest scan workgroup: 64 state columns
+template <typename T, int DV> constexpr int kMostChainWaves = sizeof(T) == 4 ? 2 : DV < 64 ? DV / 16 : 4; // (fp32: 32 columns)
+
 template <typename T, int DK, int DV> size_t max_lds_bytes() {
+    constexpr size_t scan = ScanSmem<T, DK, kMostChainWaves<T, DV>>::bytes;
     static_assert(PrepSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_wy_prep LDS");
-    static_assert(ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes <= kLdsPerWorkgroup, "k_scan_fwd LDS");
-    static_assert(ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes <= kLdsPerWorkgroup, "k_scan_bwd LDS");
-    static_assert(ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::NARROW>::bytes <= ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes &&
-                  ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::NARROW>::bytes <= ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes, "narrow blocks");
+    static_assert(scan <= kLdsPerWorkgroup, "scan LDS");
     size_t m = PrepSmem<T, DK, DV>::bytes;
-    if (ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes > m) m = ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes;
-    if (ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes > m) m = ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes;
+    if (scan > m) m = scan;
     static_assert(LocalSmem<T, DK, DV>::bytes_pro <= kLdsPerWorkgroup && LocalSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_bwd_local LDS");
     if (LocalSmem<T, DK, DV>::bytes > m) m = LocalSmem<T, DK, DV>::bytes;
     if (LocalSmem<T, DK, DV>::bytes_pro > m) m = LocalSmem<T, DK, DV>::bytes_pro;
     return m;
 }
 
-// launches kernel<T, DK, DV, variant> for the variant the pointers ask for.  The scans know two variants
-// (for the prologue they run the plain one on the q, k that k_wy_prep mapped), the chunk kernel and the reverse scan three.
-#define DN_LAUNCH_SCAN(kernel, grid, nthreads, lds, ...)                                                    \
-    do {                                                                                                    \
-        if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED>), grid, nthreads, lds, __VA_ARGS__);            \
-        else DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PLAIN>), grid, nthreads, lds, __VA_ARGS__);                \
-    } while (0)
-// ... with BV state columns per workgroup
-#define DN_LAUNCH_SCAN_BV(kernel, grid, BV, lds, ...)                                                       \
-    do {                                                                                                    \
-        if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_GATED, BV>), grid, NTS, lds, __VA_ARGS__);             \
-        else DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PLAIN, BV>), grid, NTS, lds, __VA_ARGS__);                 \
-    } while (0)
-// ... of the reverse scan, whose dV depends on how beta was rounded and on which tokens are masked
-#define DN_LAUNCH_SCAN_DV(kernel, grid, BV, lds, ...)                                                       \
-    do {                                                                                                    \
-        if (p.pro) DN_LAUNCH_NT((kernel<T, DK, DV, VAR_PROLOGUE, BV>), grid, NTS, lds, __VA_ARGS__);        \
-        else DN_LAUNCH_SCAN_BV(kernel, grid, BV, lds, __VA_ARGS__);                                         \
-    } while (0)
-// Scans of few chains (`wide` = workgroups of the grid with the ordinary column blocks) run with blocks half as wide: the
-// workgroups still fit the chip at once, and the step of each, whose length is the longest of a chain of products, is shorter.
-// The tiles are formed by the same products in the same order, so the results are the same bits.
-// Measured, d = 128, 16 heads, wide and narrow: forward pass of 1 x 1000 tokens 43.5 and 38.7 us, 4 x 2000 (the line, half the
-// chip) 84.0 and 81.4, training step 101 and 92, 266 and 247; beyond the line two rounds (8 x 2048: 104 and 155 us).
-// With d_k = 64 a forward pass that keeps no tiles has its line at a quarter of the chip.  Between the two, 4 x 2000 of 32 heads,
-// wide and narrow: alone it is 72.7 and 69.5 us (gated 84.1 and 86.1), but a backward pass behind it loses what it gains (its
-// output, in half lines, is written back then): gated, with recomputation, 275 and 276 us.  Segmented scans (sm.N > pb.N) keep
-// the ordinary blocks: little to gain in their short steps (1 x 1024: forward pass 52.8 and 51.1 us, training step 112.2 and
-// 113.0).  The line of the segments themselves (segment_count) is older than the narrow blocks and lies too low for short
-// sequences: 1 x 1024 takes 51.5, 113 and 130 us (forward, training step, with recomputation), the uncut 1 x 1000 38.7, 92 and 97.
-static inline bool narrow_blocks(const Problem &pb, const SeqMap &sm, unsigned wide, int share) {
-    return sm.N == pb.N && (long)wide * share <= pb.num_cus;
+// A scan over `passes` grids of nchains chains takes the fewest chain waves per workgroup (columns over 16) with which the
+// workgroups still fit the chip at once: the fewer share a CU's LDS, the shorter a step.
+template <typename T, int DV> static inline int chain_waves(const Problem &pb, long nchains, int passes) {
+    for (int w = 1; w < kMostChainWaves<T, DV>; w *= 2)
+        if ((long)chain_grid((int)nchains, DV / (16 * w)) * passes <= pb.num_cus) return w;
+    return kMostChainWaves<T, DV>;
 }
-// what the scans see: with the prologue, the mapped q and k in the workspace
+// launches the scan kernel<T, DK, DV, gated, ncw> over `passes` grids; half_ = workgroups of one pass, the last
+// argument of the kernels of several passes
+#define DN_LAUNCH_SCAN_W(kernel, DIR, W, passes, ...)                                                                                  \
+    do {                                                                                                                          \
+        const int half_ = chain_grid(sm.N * pb.H, DV / (16 * (W)));                                                               \
+        if (p.g) DN_LAUNCH_NT((kernel<T, DK, DV, true, W>), dim3(half_ * (passes)), (kScanThreads<T, DK, DIR, W>), (ScanSmem<T, DK, W>::bytes), __VA_ARGS__); \
+        else DN_LAUNCH_NT((kernel<T, DK, DV, false, W>), dim3(half_ * (passes)), (kScanThreads<T, DK, DIR, W>), (ScanSmem<T, DK, W>::bytes), __VA_ARGS__);    \
+    } while (0)
+#define DN_LAUNCH_SCAN(kernel, DIR, passes, ...)                                                \
+    do {                                                                                   \
+        const int ncw_ = chain_waves<T, DV>(pb, (long)sm.N * pb.H, passes);                       \
+        if (ncw_ == 1) DN_LAUNCH_SCAN_W(kernel, DIR, 1, passes, __VA_ARGS__);                   \
+        else if (kMostChainWaves<T, DV> == 2 || ncw_ == 2) DN_LAUNCH_SCAN_W(kernel, DIR, 2, passes, __VA_ARGS__); \
+        else DN_LAUNCH_SCAN_W(kernel, DIR, (kMostChainWaves<T, DV>), passes, __VA_ARGS__);          \
+    } while (0)
+// what the scans see: with the prologue, the mapped q and k in the workspace (beta stays the logit)
 static inline Ptrs scan_ptrs(const Ptrs &p) {
     Ptrs ps = p;
-    if (p.pro) { ps.q = p.Qm; ps.k = p.Km; ps.pro = 0; }
+    if (p.pro) { ps.q = p.Qm; ps.k = p.Km; }
     return ps;
 }
 
@@ -128,94 +117,65 @@ template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs 
     }
     SeqMap sm = make_map(pb);
     if (int e = launch_offsets(pb)) return e;
-    dim3 gchain(chain_grid(pb.N * pb.H, VBlock<T, DV, DK>::NV));
     if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;
     Ptrs ps = scan_ptrs(p);
     if constexpr (DK == DV && DK <= 128) {
         // few long chains: cut the sequences into G segments, get every segment's start state from a first pass
         // (k_scan_state, k_seg_combine), then run the scan below over the segments side by side
-        const int G = segment_count(pb.N, pb.L, pb.H, DK, DV, VBlock<T, DV, DK>::NV, pb.cu != nullptr);
+        const int G = segment_count(pb.N, pb.L, pb.H, DK, DV, DV / scan_vblock_cols((int)sizeof(T), DK, DV), pb.cu != nullptr);
         if (G > 1 && p.Sin) {
             sm.N = pb.N * G; sm.L = pb.L / G; sm.ncd = sm.L / C;
-            const dim3 gseg(chain_grid(sm.N * pb.H, VBlock<T, DV, DK>::NV));
-            const dim3 gstate(2 * gseg.x);
-            DN_LAUNCH_SCAN(k_scan_state, gstate, NTS, (ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes), sm, pb.H, ps, (int)gseg.x);
+            DN_LAUNCH_SCAN(k_scan_state, DIR_BWD, 2, sm, pb.H, ps, half_);
             const CombineArgs ca{p.Mseg, p.Nseg, p.S0, p.Sin, p.ST, nullptr, nullptr, nullptr, nullptr, G, pb.H, 0};
             DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 1), NTHR, (CombineSmem<DK, DV>::bytes), ca);
             ps.S0 = p.Sin; ps.ST = nullptr;
-            gchain = gseg;
         }
     }
-    constexpr int WB = VBlock<T, DV, DK>::BV, NB = VBlock<T, DV, DK>::NARROW;
-    if constexpr (NB < WB) {
-        if (narrow_blocks(pb, sm, gchain.x, DK <= 64 && !pb.save ? 4 : 2)) {
-            gchain.x *= WB / NB;
-            if (pb.save) DN_LAUNCH_SCAN_BV(k_scan_fwd_save, gchain, NB, (ScanFwdSmem<T, DK, DV, NB>::bytes), sm, pb.H, ps);
-            else DN_LAUNCH_SCAN_BV(k_scan_fwd, gchain, NB, (ScanFwdSmem<T, DK, DV, NB>::bytes), sm, pb.H, ps);
-            return 0;
-        }
-    }
-    if (pb.save) DN_LAUNCH_SCAN_BV(k_scan_fwd_save, gchain, WB, (ScanFwdSmem<T, DK, DV, WB>::bytes), sm, pb.H, ps);
-    else DN_LAUNCH_SCAN_BV(k_scan_fwd, gchain, WB, (ScanFwdSmem<T, DK, DV, WB>::bytes), sm, pb.H, ps);
+    if (pb.save) DN_LAUNCH_SCAN(k_scan_fwd_save, DIR_FWD, 1, sm, pb.H, ps);
+    else DN_LAUNCH_SCAN(k_scan_fwd, DIR_FWD, 1, sm, pb.H, ps);
     return 0;
 }
 
 // the reverse scan of a backward pass, with the recompute scan in the same grid unless the forward pass left its tiles
-// (gscan: the ordinary grid of one scan)
-template <typename T, int DK, int DV> int launch_bwd_scans(const Problem &pb, const SeqMap &sm, const Ptrs &p, const Ptrs &ps, unsigned gscan) {
-    constexpr int WB = VBlock<T, DV, DK>::BV, NB = VBlock<T, DV, DK>::NARROW;
-    constexpr size_t lds_w = cmax(ScanFwdSmem<T, DK, DV, WB>::bytes, ScanBwdSmem<T, DK, DV, WB>::bytes);
-    if constexpr (NB < WB) {
-        if (narrow_blocks(pb, sm, pb.save ? gscan : 2 * gscan, 2)) {
-            constexpr size_t lds_n = cmax(ScanFwdSmem<T, DK, DV, NB>::bytes, ScanBwdSmem<T, DK, DV, NB>::bytes);
-            const unsigned half = gscan * (WB / NB);
-            if (pb.save) DN_LAUNCH_SCAN_DV(k_scan_bwd, dim3(half), NB, (ScanBwdSmem<T, DK, DV, NB>::bytes), sm, pb.H, ps);
-            else DN_LAUNCH_SCAN_DV(k_scan_pair, dim3(2 * half), NB, lds_n, sm, pb.H, ps, (int)half);
-            return 0;
-        }
-    }
-    if (pb.save) DN_LAUNCH_SCAN_DV(k_scan_bwd, dim3(gscan), WB, (ScanBwdSmem<T, DK, DV, WB>::bytes), sm, pb.H, ps);
-    else DN_LAUNCH_SCAN_DV(k_scan_pair, dim3(2 * gscan), WB, lds_w, sm, pb.H, ps, (int)gscan);
+template <typename T, int DK, int DV> int launch_bwd_scans(const Problem &pb, const SeqMap &sm, const Ptrs &p, const Ptrs &ps) {
+    if (pb.save) DN_LAUNCH_SCAN(k_scan_bwd, DIR_BWD, 1, sm, pb.H, ps);
+    else DN_LAUNCH_SCAN(k_scan_pair, DIR_BWD, 2, sm, pb.H, ps, half_);
     return 0;
 }
 
 template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs &p) {
     if (pb.N == 0) return 0;
-    const SeqMap sm = make_map(pb);
+    const SeqMap sm0 = make_map(pb);
     if (int e = launch_offsets(pb)) return e;
-    const dim3 gchain(chain_grid(pb.N * pb.H, VBlock<T, DV, DK>::NV));
     Ptrs ps = scan_ptrs(p);
-    constexpr size_t lds_pair = cmax(ScanFwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes, ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes);
     // few long chains: the scans run over G segments of the sequences side by side (see k_scan_state)
     int G = 1;
-    if constexpr (DK == DV && DK <= 128) G = segment_count_bwd(pb.N, pb.L, pb.H, DK, DV, VBlock<T, DV, DK>::NV, pb.cu != nullptr);
+    if constexpr (DK == DV && DK <= 128) G = segment_count_bwd(pb.N, pb.L, pb.H, DK, DV, DV / scan_vblock_cols((int)sizeof(T), DK, DV), pb.cu != nullptr);
     if (G > 1 && p.Sin && pb.chunks_ub) {
         if constexpr (DK == DV && DK <= 128) {
-            SeqMap sg = sm;
-            sg.N = pb.N * G; sg.L = pb.L / G; sg.ncd = sg.L / C;
-            const dim3 gseg(chain_grid(sg.N * pb.H, VBlock<T, DV, DK>::NV));
+            SeqMap sm = sm0;
+            sm.N = pb.N * G; sm.L = pb.L / G; sm.ncd = sm.L / C;
             if (pb.save) { // the forward pass left its tiles and the segments' transition matrices
-                DN_LAUNCH_SCAN(k_scan_bwd_state, gseg, NTS, (ScanBwdSmem<T, DK, DV, VBlock<T, DV, DK>::BV>::bytes), sg, pb.H, ps);
+                DN_LAUNCH_SCAN(k_scan_bwd_state, DIR_BWD, 1, sm, pb.H, ps);
                 const CombineArgs ca{p.Mseg, nullptr, nullptr, nullptr, nullptr, p.Rseg, p.dST, p.dSout, p.dS0, G, pb.H, 1};
                 DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 1), NTHR, (CombineSmem<DK, DV>::bytes), ca);
-                ps.dST = p.dSout; ps.dS0 = nullptr;
-                if (int e = launch_bwd_scans<T, DK, DV>(pb, sg, p, ps, gseg.x)) return e;
             } else {
-                if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;
-                DN_LAUNCH_SCAN(k_scan_state, dim3(3 * gseg.x), NTS, lds_pair, sg, pb.H, ps, (int)gseg.x);
+                if (int e = launch_prep<T, DK, DV>(pb, sm0, p)) return e;
+                DN_LAUNCH_SCAN(k_scan_state, DIR_BWD, 3, sm, pb.H, ps, half_);
                 const CombineArgs ca{p.Mseg, p.Nseg, p.S0, p.Sin, nullptr, p.Rseg, p.dST, p.dSout, p.dS0, G, pb.H, 0};
                 DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 2), NTHR, (CombineSmem<DK, DV>::bytes), ca);
-                ps.S0 = p.Sin; ps.dST = p.dSout; ps.dS0 = nullptr;
-                if (int e = launch_bwd_scans<T, DK, DV>(pb, sg, p, ps, gseg.x)) return e;
+                ps.S0 = p.Sin;
             }
+            ps.dST = p.dSout; ps.dS0 = nullptr;
+            if (int e = launch_bwd_scans<T, DK, DV>(pb, sm, p, ps)) return e;
         }
-    } else if (pb.save) { // T, Ut and the chunk-initial states are the forward pass's: only the reverse scan is left
-        if (int e = launch_bwd_scans<T, DK, DV>(pb, sm, p, ps, gchain.x)) return e;
     } else {
-        if (pb.chunks_ub) if (int e = launch_prep<T, DK, DV>(pb, sm, p)) return e;
-        // both scans of the backward pass as one grid: reverse scan first, recompute scan behind it
-        if (int e = launch_bwd_scans<T, DK, DV>(pb, sm, p, ps, gchain.x)) return e;
+        // kept tiles: T, Ut and the chunk-initial states are the forward pass's, only the reverse scan is left; otherwise both
+        // scans of the backward pass as one grid: reverse scan first, recompute scan behind it
+        if (!pb.save && pb.chunks_ub) if (int e = launch_prep<T, DK, DV>(pb, sm0, p)) return e;
+        if (int e = launch_bwd_scans<T, DK, DV>(pb, sm0, p, ps)) return e;
     }
+    const SeqMap &sm = sm0;
     if (pb.chunks_ub) {
         using SM = LocalSmem<T, DK, DV>;
         const long tiles = (long)pb.chunks_ub * pb.H, slots = (long)pb.num_cus * SM::WPC;
