@@ -38,8 +38,8 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 //   every tile store of the scans, k_wy_prep and the chunk kernel: non-temporal (nothing is read back by the same launch)
 constexpr int kAuxOnce = 2, kAuxKeep = 0;
 constexpr int kBufRange = 0x40000000; // bytes covered by a descriptor; offsets >= this read as zero
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, kBufRange, 0x00020000);
+__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, int range = kBufRange) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, range, 0x00020000);
 }
 // AUX = the instruction's cache-policy bits: 0 = default, 2 = non-temporal (data that this launch reads once)
 template <int AUX = 0> __device__ inline uint4 buf_load16(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {

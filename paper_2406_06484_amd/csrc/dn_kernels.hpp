@@ -248,10 +248,12 @@ __global__ __launch_bounds__((kScanThreads<T, DK, DIR_BWD, NCW>)) void k_scan_bw
 // S_in(0) = the caller's initial state (or zero); S_in(g + 1) = M_g S_in(g) + N_g; the state after the last segment is
 // the final state.  Backward (blockIdx.z = 1): D(G) = the caller's gradient with respect to the final state (or zero);
 // every segment's end gradient dSout(g) = D(g + 1), D(g) = M_g^T D(g + 1) + R_g; D(0) is the gradient with respect to the
-// initial state.  One workgroup per (chain, block of 32 state columns, direction): the columns evolve independently.
+// initial state.  One workgroup per (chain, block of 16 state columns, direction): the columns evolve independently.
 // fp32 on the matrix cores; the next segment's M and N (R) tile travel from global memory while the current product runs.
+// A wave owns 16 rows of the product, in 16 x 16 x 4 matrix instructions: DK / 4 dependent ones a segment (1 K cycles at d = 128).
+constexpr int kCombineCols = 16, kCombineThreads = 512;
 template <int DK, int DV> struct CombineSmem {
-    static constexpr int LM = DK + 4, LSB = 32 + 4;
+    static constexpr int LM = DK + 4, LSB = 16 + 4;
     static constexpr size_t oM = 0, oS = sizeof(float) * DK * LM, bytes = oS + sizeof(float) * DK * LSB;
 };
 struct CombineArgs {
@@ -262,54 +264,63 @@ struct CombineArgs {
     int G, H, first_dir;           // grid.z directions run from first_dir: 0 = forward, 1 = backward
 };
 template <int DK, int DV>
-__global__ __launch_bounds__(NTHR) void k_seg_combine(CombineArgs a) {
+__global__ __launch_bounds__(kCombineThreads) void k_seg_combine(CombineArgs a) {
     using SM = CombineSmem<DK, DV>;
-    static_assert(DK % 32 == 0 && DK / 32 <= NTHR / 64, "one 32-row tile per wave");
+    constexpr int NT = kCombineThreads, NB = kCombineCols;
+    static_assert(DK % 16 == 0 && DK / 16 <= NT / 64, "one tile of 16 rows per wave");
     extern __shared__ __align__(16) unsigned char smem[];
     float *sM = reinterpret_cast<float *>(smem + SM::oM), *sS = reinterpret_cast<float *>(smem + SM::oS);
-    const int chain = blockIdx.x, b = chain / a.H, h = chain - b * a.H, c0 = 32 * blockIdx.y;
+    const int chain = blockIdx.x, b = chain / a.H, h = chain - b * a.H, c0 = NB * blockIdx.y;
     const bool bwd = (int)blockIdx.z + a.first_dir == 1;
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const bool act = wave < DK / 32;
+    const int tid = threadIdx.x, wave = tid >> 6, j = tid & 15, g4 = 4 * ((tid & 63) >> 4);
+    const bool act = wave < DK / 16;
+    const int row0 = 16 * wave + g4; // the first of this lane's four rows, column j
     const float *init = bwd ? a.dST : a.S0, *add = bwd ? a.Rseg : a.Nseg;
     float *start = bwd ? a.dSout : a.Sin, *last = bwd ? a.dS0 : a.ST;
     auto seg_of = [&](int i) __attribute__((always_inline)) { return ((long)(b * a.G + (bwd ? a.G - 1 - i : i)) * a.H + h); };
-    TileRegs<float, DK, DK, NTHR> mreg;
-    f32x16 nreg = zero16();
+    TileRegs<float, DK, DK, NT> mreg;
+    f32x4 nreg = {0.f, 0.f, 0.f, 0.f}, cur = nreg; // cur: the current value of this lane's rows
     auto request = [&](int i) __attribute__((always_inline)) { // M and the additive tile of step i, into registers
         const long seg = seg_of(i);
         mreg.load(a.Mseg + seg * DK * DK, DK, DK);
-        if (act) acc_each(nreg, [&](int r, int c, float &val) { val = add[(seg * DK + 32 * wave + r) * DV + c0 + c]; });
+        if (act)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) nreg[e] = add[(seg * DK + row0 + e) * DV + c0 + j];
     };
     request(0);
-    for (int e = tid; e < DK * 32; e += NTHR) {
-        const int i = e >> 5, j = e & 31;
-        sS[i * SM::LSB + j] = init ? init[((long)chain * DK + i) * DV + c0 + j] : 0.f;
-    }
-    lds_barrier(); // (LDS only: the requests and stores in flight are not waited for)
+    if (act && init)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cur[e] = init[((long)chain * DK + row0 + e) * DV + c0 + j];
     for (int i = 0; i < a.G; ++i) {
         const long seg = seg_of(i);
-        for (int e = tid; e < DK * 32; e += NTHR) { // this segment starts from (backward: ends with) the current value
-            const int r = e >> 5, j = e & 31;
-            start[(seg * DK + r) * DV + c0 + j] = sS[r * SM::LSB + j];
-        }
+        if (act) // this segment starts from (backward: ends with) the current value
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                start[(seg * DK + row0 + e) * DV + c0 + j] = cur[e];
+                sS[(row0 + e) * SM::LSB + j] = cur[e];
+            }
         mreg.store(sM, SM::LM);
-        f32x16 acc = nreg;
-        lds_barrier();
+        f32x4 acc[2] = {nreg, {0.f, 0.f, 0.f, 0.f}};
+        lds_barrier(); // (LDS only: the requests and stores in flight are not waited for)
         if (i + 1 < a.G) request(i + 1);
         if (act) {
-            if (bwd) mma<DK, true, true, float>(acc, sM + 32 * wave, SM::LM, sS, SM::LSB); // M^T D: down the rows of M
-            else mma<DK, false, true, float>(acc, sM + 32 * wave * SM::LM, SM::LM, sS, SM::LSB);
+#pragma unroll
+            for (int k = 0; k < DK; k += 16) { // lane group g feeds the contraction indices k + 4 g + e in step e
+                f32x4 m;
+                if (bwd)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) m[e] = sM[(k + g4 + e) * SM::LM + 16 * wave + j]; // M^T D: down the rows of M
+                else m = *reinterpret_cast<const f32x4 *>(sM + (16 * wave + j) * SM::LM + k + g4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e & 1] = mfma16(acc[e & 1], m[e], sS[(k + g4 + e) * SM::LSB + j]);
+            }
+            cur = acc[0] + acc[1];
         }
         lds_barrier(); // every wave has read the old value
-        if (act) acc_to_lds<float>(sS, SM::LSB, 32 * wave, 0, acc);
-        lds_barrier();
     }
-    if (last)
-        for (int e = tid; e < DK * 32; e += NTHR) {
-            const int r = e >> 5, j = e & 31;
-            last[((long)chain * DK + r) * DV + c0 + j] = sS[r * SM::LSB + j];
-        }
+    if (last && act)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) last[((long)chain * DK + row0 + e) * DV + c0 + j] = cur[e];
 }
 
 // The backward pass's two scans in one launch.  They do not depend on each other (the recompute

@@ -127,7 +127,7 @@ template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs 
             sm.N = pb.N * G; sm.L = pb.L / G; sm.ncd = sm.L / C;
             DN_LAUNCH_SCAN(k_scan_state, DIR_BWD, 2, sm, pb.H, ps, half_);
             const CombineArgs ca{p.Mseg, p.Nseg, p.S0, p.Sin, p.ST, nullptr, nullptr, nullptr, nullptr, G, pb.H, 0};
-            DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 1), NTHR, (CombineSmem<DK, DV>::bytes), ca);
+            DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / kCombineCols, 1), kCombineThreads, (CombineSmem<DK, DV>::bytes), ca);
             ps.S0 = p.Sin; ps.ST = nullptr;
         }
     }
@@ -158,12 +158,12 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
             if (pb.save) { // the forward pass left its tiles and the segments' transition matrices
                 DN_LAUNCH_SCAN(k_scan_bwd_state, DIR_BWD, 1, sm, pb.H, ps);
                 const CombineArgs ca{p.Mseg, nullptr, nullptr, nullptr, nullptr, p.Rseg, p.dST, p.dSout, p.dS0, G, pb.H, 1};
-                DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 1), NTHR, (CombineSmem<DK, DV>::bytes), ca);
+                DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / kCombineCols, 1), kCombineThreads, (CombineSmem<DK, DV>::bytes), ca);
             } else {
                 if (int e = launch_prep<T, DK, DV>(pb, sm0, p)) return e;
                 DN_LAUNCH_SCAN(k_scan_state, DIR_BWD, 3, sm, pb.H, ps, half_);
                 const CombineArgs ca{p.Mseg, p.Nseg, p.S0, p.Sin, nullptr, p.Rseg, p.dST, p.dSout, p.dS0, G, pb.H, 0};
-                DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / 32, 2), NTHR, (CombineSmem<DK, DV>::bytes), ca);
+                DN_LAUNCH_NT((k_seg_combine<DK, DV>), dim3(pb.N * pb.H, DV / kCombineCols, 2), kCombineThreads, (CombineSmem<DK, DV>::bytes), ca);
                 ps.S0 = p.Sin;
             }
             ps.dST = p.dSout; ps.dS0 = nullptr;

@@ -181,20 +181,22 @@ template <int TPS> __host__ __device__ constexpr TilePair upper_pair(int e) {
 
 // ---- pieces of a tile between global memory, registers and the LDS ------------------------------------------------------
 // A 64 x COLS tile as 16-byte pieces, piece numbers t, t + NTL, ... of thread t; consecutive threads hold consecutive pieces.
-// Requests of rows at or past nvalid return zeros and touch no memory (the lanes point past the descriptor's range), so that no
-// branch stands around a request and the compiler knows how many are in flight.
+// Requests of rows at or past nvalid return zeros and touch no memory: the descriptor's range ends at that row, or (SELECT) their lanes
+// point past a range that does not depend on the chunk.  No branch stands around a request, and the compiler knows how many are in
+// flight.  Which form: forward scan that keeps its tiles, 8 x 2048 tokens of 16 heads of 128, 106 us with the select and 101 without,
+// reverse scan 87 and 91 (d = 256: 157 and 168).
 template <typename T, int COLS> struct Pieces {
     using L = LdsTile<T, COLS>;
     static constexpr int PPR = L::SLOTS, N = C * PPR, NIT = (N + NTL - 1) / NTL;
     static_assert(N % NTL == 0 || N < NTL, "whole rounds");
     uint4 v[NIT];
-    template <int AUX> __device__ __forceinline__ void load(const T *src, long row_stride, int nvalid, int t) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src);
+    template <int AUX, bool SELECT = false> __device__ __forceinline__ void load(const T *src, long row_stride, int nvalid, int t) {
         const int stride = (int)row_stride * (int)sizeof(T);
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, SELECT ? kBufRange : nvalid * stride);
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int e = it * NTL + t, r = e / PPR, p = e % PPR;
-            v[it] = buf_load16<AUX>(rs, r < nvalid ? r * stride + 16 * p : kBufRange, 0);
+            v[it] = buf_load16<AUX>(rs, !SELECT || r < nvalid ? r * stride + 16 * p : kBufRange, 0);
         }
     }
     // SIGN: with the sign of every element flipped
@@ -219,11 +221,11 @@ template <typename T, int COLS> struct Pieces {
         }
     }
 };
-// LDS tile -> global rows (rows at or past nvalid are dropped, again by the descriptor's range)
+// LDS tile -> global rows (rows at or past nvalid are dropped: their lanes point past the descriptor's range)
 template <typename T, int COLS, int AUX> __device__ __forceinline__ void tile_out(T *dst, long row_stride, int nvalid, const unsigned char *tile, int t) {
     using P = Pieces<T, COLS>;
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(dst);
     const int stride = (int)row_stride * (int)sizeof(T);
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(dst);
 #pragma unroll
     for (int it = 0; it < P::NIT; ++it) {
         const int e = it * NTL + t, r = e / P::PPR, p = e % P::PPR;
@@ -349,12 +351,12 @@ template <typename T, int COLS> struct OwnRows {
     __device__ static int at(int n, int piece) { return n * L::RB + ((piece ^ L::swz(row16<T>(0, n))) << 4); }
     __device__ static int token(int w, int n) { return (Op<T>::TPS == 2 ? 32 * (w >> 1) + 4 * (w & 1) : 16 * w) + row16<T>(0, n); }
     template <int AUX> __device__ __forceinline__ void load(const T *src, long row_stride, int nvalid, int w, int lane) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src);
         const int stride = (int)row_stride * (int)sizeof(T);
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, nvalid * stride);
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
-            const int e = it * 64 + lane, n = e / PPR & 15, p = e % PPR, r = token(w, n);
-            v[it] = buf_load16<AUX>(rs, e < N && r < nvalid ? r * stride + 16 * p : kBufRange, 0);
+            const int e = it * 64 + lane, n = e / PPR & 15, p = e % PPR;
+            v[it] = buf_load16<AUX>(rs, N % 64 == 0 || e < N ? token(w, n) * stride + 16 * p : kBufRange, 0);
         }
     }
     __device__ __forceinline__ void store(unsigned char *mine, int lane) const {
@@ -365,13 +367,13 @@ template <typename T, int COLS> struct OwnRows {
         }
     }
     template <int AUX> __device__ static __forceinline__ void out(T *dst, long row_stride, int nvalid, const unsigned char *mine, int w, int lane) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(dst);
         const int stride = (int)row_stride * (int)sizeof(T);
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(dst, nvalid * stride);
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
-            const int e = it * 64 + lane, n = e / PPR & 15, p = e % PPR, r = token(w, n);
+            const int e = it * 64 + lane, n = e / PPR & 15, p = e % PPR;
             const u32x4 x = *reinterpret_cast<const u32x4 *>(mine + at(n, p));
-            __builtin_amdgcn_raw_buffer_store_b128(x, rs, e < N && r < nvalid ? r * stride + 16 * p : kBufRange, 0, AUX);
+            __builtin_amdgcn_raw_buffer_store_b128(x, rs, N % 64 == 0 || e < N ? token(w, n) * stride + 16 * p : kBufRange, 0, AUX);
         }
     }
 };
@@ -679,15 +681,15 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             const int ii = max(ic, 0), nvalid = ic < 0 ? 0 : min(C, len - ic * C);
             const long row0 = (long)t0 + (long)ii * C, tile = (long)(cb + ii) * H + h;
             if (!MOVES) return;
-            x.k.template load<kAuxKeep>((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, lt);
-            x.q.template load<kAuxKeep>((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid, lt);
-            x.d.template load<kAuxKeep>((const T *)p.d_o + (row0 * H + h) * DV + vb, (long)H * DV, nvalid, lt);
+            x.k.template load<kAuxKeep, true>((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, lt);
+            x.q.template load<kAuxKeep, true>((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid, lt);
+            x.d.template load<kAuxKeep, true>((const T *)p.d_o + (row0 * H + h) * DV + vb, (long)H * DV, nvalid, lt);
             if (GATED)
 #pragma unroll
                 for (int it = 0; it < Pieces<T, BV>::NIT; ++it) x.gm[it] = p.gam[tile * 2 * C + ((it * NTL + lt) / Pieces<T, BV>::PPR & (C - 1))];
         };
         auto fetch_t = [&](Pieces<T, C> &x, int ic) __attribute__((always_inline)) {
-            if (MOVES) x.template load<kAuxKeep>((const T *)p.Tm + ((long)(cb + max(ic, 0)) * H + h) * C * C, C, ic < 0 ? 0 : C, lt);
+            if (MOVES) x.template load<kAuxKeep, true>((const T *)p.Tm + ((long)(cb + max(ic, 0)) * H + h) * C * C, C, ic < 0 ? 0 : C, lt);
         };
         auto fetch_tab = [&](TabRegs<T, GATED> &x, int ic) __attribute__((always_inline)) {
             const int ii = max(ic, 0);
