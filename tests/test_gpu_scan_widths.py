@@ -34,3 +34,28 @@ def test_every_width_gives_the_same_bits(dtype, dk, dv, H, L):
     for n in chains:
         for i, (a, b) in enumerate(zip(one, passes(n // H))):
             assert torch.equal(a.expand_as(b), b), (n, i)
+
+
+@pytest.mark.parametrize("rule", ["plain", "gated", "fused"])
+@pytest.mark.parametrize("dtype,d,L", [("bf16", 128, 4096), ("bf16", 64, 4096), ("f32", 64, 512)])
+def test_cut_sequence_equals_the_uncut_one(dtype, d, L, rule):
+    """A long dense sequence of few heads is cut into segments; the same tokens as a packed batch of one sequence are not.  The two
+    differ by the rounding of the segments' start states: each tensor within four times the error it has against 64 bits."""
+    H = 2
+    x = dev_inputs(make_inputs(8, B=1, L=L, H=H, dk=d, dv=d, dtype=dtype, with_initial_state=True, with_dfinal_state=True))
+    args = [x[k] for k in ("q", "k", "v", "beta")]
+    if rule == "gated":
+        args.append(torch.log(0.9 + 0.1 * torch.rand(1, L, H, generator=torch.Generator().manual_seed(3))).cuda())
+    f = lambda n: getattr(dn, "deltanet_" + {"plain": "", "gated": "gated_", "fused": "fused_"}[rule] + n)
+    flat, cu = [a[0] for a in args], torch.tensor([0, L], dtype=torch.int32, device="cuda")
+    o, ST, saved = f("fwd_save")(*args, x["S0"])
+    cut = [o[0], ST, *[t[0] if t.dim() > 2 and t.shape[0] == 1 and t.shape[1] == L else t for t in f("bwd_saved")(*args, x["d_o"], saved, x["dST"])]]
+    again = [t[0] if t.dim() > 2 and t.shape[0] == 1 and t.shape[1] == L else t for t in f("bwd")(*args, x["d_o"], x["S0"], x["dST"])]
+    whole = [*f("fwd")(*flat, x["S0"], cu_seqlens=cu), *f("bwd")(*flat, x["d_o"][0], x["S0"], x["dST"], cu_seqlens=cu)]
+    torch.cuda.synchronize()
+    bound = 3e-2 if dtype == "bf16" and rule == "gated" else 2e-2 if dtype == "bf16" else 4e-6
+    for i, (a, b) in enumerate(zip(cut, whole)):
+        a, b = a.double().reshape(b.shape), b.double()
+        assert (a - b).norm() <= bound * b.norm(), (i, float((a - b).norm() / b.norm()))
+    for i, (a, b) in enumerate(zip(cut[2:], again)):
+        assert torch.equal(a, b), i
