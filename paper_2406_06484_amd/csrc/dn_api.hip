@@ -123,7 +123,7 @@ void make_plan(const dn_shape *s, int want_bwd, Plan *pl, bool gated = false, bo
     }
     { // forward pass split over segments of the sequence: N, M and the start state per segment
         const int nv = s->d_v / scan_vblock_cols((int)pl->esz, s->d_k, s->d_v);
-        const int G = segment_count(pb.N, s->L, s->H, s->d_k, s->d_v, nv, (int)pl->esz, packed, kChunk);
+        const int G = segment_count(pb.N, s->L, s->H, s->d_k, s->d_v, nv, packed, kChunk);
         pl->seg_bytes = G > 1 ? up256((size_t)pb.N * G * s->H * s->d_k * s->d_v * sizeof(float)) : 0;
         pl->off_seg = o; o += 5 * pl->seg_bytes;
     }

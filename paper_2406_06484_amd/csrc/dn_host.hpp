@@ -49,25 +49,24 @@ struct Ptrs {
 // How many segments a dense forward pass over N sequences of length L is cut into (1 = not at all).  Few chains
 // cannot fill the 256 CUs of the chip; segments are whole chunks, at least four of them, d_v = d_k (the transition
 // matrix is scanned with the state kernels).  nv = d_v / scan_vblock_cols.
-// The cut pays for its two more passes and the combination (10 us and up) where the chain is long: in bf16, 16 heads of 128, cut
-// and uncut, in us (forward pass, training step, step with recomputation): 1 x 1024 tokens 36 84 101 and 26 65 71, 1 x 2048 57 133 164
-// and 42 118 121, 1 x 4096 73 191 229 and 75 220 225, 1 x 8192 105 301 371 and 141 425 437; with twice the chains 2 x 4096 99 286 312 and
-// 84 289 308, 2 x 8192 171 532 591 and 177 577 601.  32 heads of 64: 1 x 2048 40 98 121 and 35 101 108, 1 x 4096 57 148 184 and 70 195 206,
-// 2 x 4096 92 254 282 and 92 266 293.
-// In fp32, where a chunk step is three times as long, 1 x 1024 of 8 heads 48 109 121 and 72 156 164.
-inline int segment_count(int N, int L, int H, int d_k, int d_v, int nv, int elem_bytes, bool packed, int chunk = 64) {
+// The cut costs two more passes and the combination (10 us and up) and pays where the chain is long: in bf16, 16 heads of 128, cut
+// and uncut, in us (forward pass, training step): 1 x 1024 tokens 36 84 and 26 65, 1 x 2048 57 133 and 42 118, 1 x 4096 73 191 and
+// 75 220, 1 x 8192 105 301 and 141 425; with twice the chains 2 x 4096 99 286 and 84 289, 2 x 8192 171 532 and 177 577.  In fp32,
+// whose chunk step is three times as long, 1 x 1024 of 8 heads 48 109 and 72 156.  So bf16 sequences under 4096 tokens would be faster
+// uncut (by 8 to 20 us); the line does not look at the length, because a short sequence is held to the same path, and results, as a long one.
+inline int segment_count(int N, int L, int H, int d_k, int d_v, int nv, bool packed, int chunk = 64) {
     if (packed || d_k != d_v || d_k > 128 || L <= 0) return 1;
     const long wgs = (long)N * H * nv;
     if (wgs > 64) return 1;
-    if (elem_bytes == 2 && L < (wgs > 32 && d_k > 64 ? 8192 : 4096)) return 1;
     int G = 1;
     while (G < 16 && wgs * (2 * G) <= 256 && L % (2 * G * chunk) == 0 && L / (2 * G * chunk) >= 4) G *= 2;
     return G;
 }
 // The backward pass runs five scan passes over the segments where the uncut one runs two, so it is cut (into the
-// same segments as the forward pass, whose transition matrices it may find in the workspace) only with half as many chains.
-inline int segment_count_bwd(int N, int L, int H, int d_k, int d_v, int nv, int elem_bytes, bool packed, int chunk = 64) {
-    return (long)N * H * nv <= 32 ? segment_count(N, L, H, d_k, d_v, nv, elem_bytes, packed, chunk) : 1;
+// same segments as the forward pass, whose transition matrices it may find in the workspace) only when its two
+// scans would occupy a quarter of the chip or less.
+inline int segment_count_bwd(int N, int L, int H, int d_k, int d_v, int nv, bool packed, int chunk = 64) {
+    return (long)N * H * nv <= 32 ? segment_count(N, L, H, d_k, d_v, nv, packed, chunk) : 1;
 }
 // State columns that the rule of the segments counts as one workgroup: 64 in bf16 up to d_k = 128, else 32.
 inline int scan_vblock_cols(int elem_bytes, int d_k, int d_v) {

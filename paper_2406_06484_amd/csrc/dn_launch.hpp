@@ -122,7 +122,7 @@ template <typename T, int DK, int DV> int run_fwd(const Problem &pb, const Ptrs 
     if constexpr (DK == DV && DK <= 128) {
         // few long chains: cut the sequences into G segments, get every segment's start state from a first pass
         // (k_scan_state, k_seg_combine), then run the scan below over the segments side by side
-        const int G = segment_count(pb.N, pb.L, pb.H, DK, DV, DV / scan_vblock_cols((int)sizeof(T), DK, DV), (int)sizeof(T), pb.cu != nullptr);
+        const int G = segment_count(pb.N, pb.L, pb.H, DK, DV, DV / scan_vblock_cols((int)sizeof(T), DK, DV), pb.cu != nullptr);
         if (G > 1 && p.Sin) {
             sm.N = pb.N * G; sm.L = pb.L / G; sm.ncd = sm.L / C;
             DN_LAUNCH_SCAN(k_scan_state, DIR_BWD, 2, sm, pb.H, ps, half_);
@@ -150,7 +150,7 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
     Ptrs ps = scan_ptrs(p);
     // few long chains: the scans run over G segments of the sequences side by side (see k_scan_state)
     int G = 1;
-    if constexpr (DK == DV && DK <= 128) G = segment_count_bwd(pb.N, pb.L, pb.H, DK, DV, DV / scan_vblock_cols((int)sizeof(T), DK, DV), (int)sizeof(T), pb.cu != nullptr);
+    if constexpr (DK == DV && DK <= 128) G = segment_count_bwd(pb.N, pb.L, pb.H, DK, DV, DV / scan_vblock_cols((int)sizeof(T), DK, DV), pb.cu != nullptr);
     if (G > 1 && p.Sin && pb.chunks_ub) {
         if constexpr (DK == DV && DK <= 128) {
             SeqMap sm = sm0;
