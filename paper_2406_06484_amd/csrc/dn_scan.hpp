@@ -14,7 +14,7 @@
 // reads alone filled the LDS for 3 K of them.  Now 2.9 K beside one chain wave and 4.1 K beside four.)
 // Scan times before and now: forward pass of 1 x 1000 tokens, 16 heads of 128, 34.7 -> 21.6 us; 16 384 tokens of width 2048, d = 128,
 // forward 85.9 -> 68, forward that keeps its tiles 102.7 -> 104, reverse 100.6 -> 84 (both at 5 TB/s: HBM bounds them); gated 144 -> 98
-// and 112 -> 96; d = 256 229 -> 195 and 236 -> 153; fp32, 2 x 1500 tokens, 8 heads of 64, 184 -> 99 and 170 -> 97.
+// and 112 -> 96; d = 256 229 -> 168 and 236 -> 137; fp32, 2 x 1500 tokens, 8 heads of 64, 184 -> 99 and 170 -> 97.
 //
 // A workgroup is NCW such chain waves (16 NCW columns) and four helper waves.  What bounds a chain wave is the rate at which ONE wave
 // can read the LDS (24 cycles for 16 bytes a lane, 13 for 8; four waves together reach four times that), not its products (16
@@ -284,8 +284,9 @@ template <typename T, int DK, int DIR, int NCW> __device__ inline int helper_num
     return wave - NCW;
 }
 template <typename T, int DK, int DIR, int NCW> constexpr int kScanThreads = 64 * NCW + (kSplitHelpers<T, DK, DIR> ? 2 : 1) * NTL;
-// how many chunks the helpers' registers hold on their way to the LDS (at d_k = 256, and in fp32, there is room for one)
-template <typename T, int DK> constexpr int kScanSets = DK > 128 || sizeof(T) == 4 ? 1 : 2;
+// How many chunks the helpers' registers hold on their way to the LDS: two (16 384 tokens of 8 heads of 256: forward scan that keeps its
+// tiles 196 us with one and 168 with two, reverse scan 155 and 137); in fp32, whose steps are long and whose tiles are twice as large, one.
+template <typename T, int DK> constexpr int kScanSets = sizeof(T) == 4 ? 1 : 2;
 // what one chunk's row of the tables is made from, per thread lt < 64 (the others hold copies)
 template <typename T, bool GATED> struct TabRegs {
     float gm, gi;
