@@ -342,8 +342,7 @@ def main() -> int:
                                      "vs_plain": round(fms / ms_per_step, 3)}
     del wsf, qp, kp, bp
 
-    # The same number of tokens and the same model width at head size 256 (H / 2 heads): the scans own 32 state columns
-    # per workgroup.
+    # The same number of tokens and the same model width at head size 256 (H / 2 heads).
     H2, d2 = max(1, H // 2), 2 * d
     gen = torch.Generator(device="cpu").manual_seed(7)
     unit2 = lambda: torch.nn.functional.normalize(torch.randn(B, L, H2, d2, generator=gen), dim=-1).bfloat16().to(dev)

@@ -263,8 +263,8 @@ def write_head_sizes():
                 tot_us += us
                 tot_mb += mb
             f.write("%4d  %-20s %9.1f %9.1f %8.2f\n\n" % (d, "step", tot_us, tot_mb, tot_mb / tot_us))
-        f.write("TB/s = HBM_MB / avg_us.  At d = 64 a chain is one scan workgroup (256 chains), at d = 128 two (128 chains), at d = 256 eight\n"
-                "workgroups of 32 state columns (64 chains, 512 workgroups in two rounds); the chunk kernel walks the operands with a\n"
+        f.write("TB/s = HBM_MB / avg_us.  A scan workgroup owns 64 state columns here: at d = 64 a chain is one workgroup (256 chains), at\n"
+                "d = 128 two (128 chains), at d = 256 four (64 chains); the chunk kernel walks the operands with a\n"
                 "d_v axis in blocks of 64 state columns, of 32 at d = 256.  Per token the matrix work\n"
                 "grows with d (model FLOPs 6 d^2 + ... per token and head, H = 2048 / d heads) while the bytes per token stay the same for\n"
                 "q, k, v, o and grow with d for the per-chunk states.\n")
