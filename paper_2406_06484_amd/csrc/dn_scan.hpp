@@ -27,8 +27,8 @@
 //   reverse  A  chain: K dS'                                helpers: P, P^T dO, Q^T dO, this chunk's T, the dV of the chunk before to memory
 //            B  chain: dUt, dV = T^T dUt, dS -= K^T dV      helpers: the next chunk's K, Q, dO
 //
-// Rounding points in bf16: S, X, Ut, P, T (dS', dUt, dV) as operands.  The diagonal of T, the largest term of a row of T X, is not
-// in the tile: Ut = beta X + (T - diag(beta)) bf16(X) with the fp32 beta and X; in the same way dV = T^T dUt.
+// Rounding points in bf16: S, Ut, P, T (dS', dV) as operands; X and dUt go in as two of them (kTwoTerms).  The diagonal of T, the largest
+// term of a row of T X, is not in the tile: Ut = beta X + (T - diag(beta)) X with the fp32 beta and X; in the same way dV = T^T dUt.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -65,9 +65,14 @@ __device__ inline bf16x8 as_operand(const f32x4 *t, int s, bf16) {
     return f;
 }
 __device__ inline f32x4 as_operand(const f32x4 *t, int s, float) { return t[s]; }
-// element i of tile t in the operands made from it, as fp32
-__device__ inline float operand_value(const bf16x8 *f, int t, int i) { return (float)f[t >> 1][4 * (t & 1) + i]; }
-__device__ inline float operand_value(const f32x4 *f, int t, int i) { return f[t][i]; }
+// ... of what the rounding left out of it (bf16; fp32 operands are not rounded)
+__device__ inline bf16x8 rest_operand(const f32x4 *t, const bf16x8 &rounded, int s) {
+    bf16x8 f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { f[i] = (bf16)(t[2 * s][i] - (float)rounded[i]); f[4 + i] = (bf16)(t[2 * s + 1][i] - (float)rounded[4 + i]); }
+    return f;
+}
+__device__ inline f32x4 rest_operand(const f32x4 *, const f32x4 &, int) { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 __device__ inline f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 
 // ---- LDS tiles ---------------------------------------------------------------------------------------------------------
@@ -124,6 +129,12 @@ template <typename T, int COLS> __device__ inline typename Op<T>::frag read_ks(c
 // fp32: products that meet a larger term are summed from zero and added at the end, which keeps every partial sum's rounding
 // to its own size (summed onto V and dS the results are 10 to 60 % further from the exact ones); bf16 rounds their sum to 8 bits anyway
 template <typename T> constexpr bool kSumFirst = sizeof(T) == 4;
+// bf16: X and dUt, the right factors of the products with T and T^T, as two bf16 operands, the rounded value and the rest, that
+// meet the same reads of T (six more products each).  Where keys are alike X = V - K S and dV are differences of large terms, and a
+// factor rounded to 8 bits in between was 9 to 20 % of error in o, 15 to 20 in the state, 7 to 8 in dv and 13 to 23 in dbeta (mean cosine of
+// the keys 0.8 to 0.9, against products that take V and dUt apart); with the second term every tensor is below those products.  It costs 1.3 us
+// of 26.7 (1 x 1000 tokens, 16 heads of 128), 2 of 68 (forward scan, 8 x 2048) and 2 of 82 (reverse scan).
+template <typename T> constexpr bool kTwoTerms = sizeof(T) == 2;
 // four elements of accumulator tile t in storage format
 template <typename T, int COLS> __device__ inline auto read_ac(const unsigned char *tile, int ac0, int t, int lane, int c) {
     using L = LdsTile<T, COLS>;
@@ -177,6 +188,10 @@ template <int TPS> __host__ __device__ constexpr TilePair upper_pair(int e) {
     int s = 0;
     while (e >= (s + 1) * TPS) { e -= (s + 1) * TPS; ++s; }
     return {e, s};
+}
+// acc[pair(e).t] += f[e] b[pair(e).s] for every e
+template <typename F, typename PAIR, int... I> __device__ __forceinline__ void second_terms(f32x4 *acc, const F *f, const F *b, PAIR pair, std::integer_sequence<int, I...>) {
+    (mma16(acc[pair(Num<I>{}).t], f[I], b[pair(Num<I>{}).s]), ...);
 }
 
 // ---- pieces of a tile between global memory, registers and the LDS ------------------------------------------------------
@@ -567,7 +582,7 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
             const long tile = (long)(cb + ic) * H + h;
             // A: X' = K S - V, Ut = -T X'
             f32x4 x[NCT], xv[NCT], ut[NCT], nb[NCT];
-            frag xb[NC], ub[NC];
+            frag xb[NC], tf[NTX], ub[NC];
 #pragma unroll
             for (int t = 0; t < NCT; ++t) {
                 f32x4 v = widen(read_ac<T, BV>(sV, vc, t, lane, wave));
@@ -599,8 +614,18 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
                         for (int t = 0; t < NCT; ++t) ut[t] = kSumFirst<T> ? zero4() : nb[t] * x[t]; // the diagonal of T, which the tile leaves out
                     }
                     if constexpr (e < NKS) mma16(x[e % NCT], f, Sb[e / NCT]);
-                    else { constexpr TilePair b = lower_pair<NC, TPS>(e - NKS); mma16(ut[b.t], f, xb[b.s]); }
+                    else {
+                        constexpr TilePair b = lower_pair<NC, TPS>(e - NKS);
+                        mma16(ut[b.t], f, xb[b.s]);
+                        if (kTwoTerms<T>) tf[e - NKS] = f;
+                    }
                 });
+            if constexpr (kTwoTerms<T>) {
+                frag xr[NC];
+#pragma unroll
+                for (int s = 0; s < NC; ++s) xr[s] = rest_operand(x, xb[s], s);
+                second_terms(ut, tf, xr, [](auto E) { return lower_pair<NC, TPS>(E); }, std::make_integer_sequence<int, NTX>{});
+            }
             if (kSumFirst<T>)
 #pragma unroll
                 for (int t = 0; t < NCT; ++t) ut[t] += nb[t] * x[t];
@@ -851,7 +876,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             lds_barrier();
             // B: dUt' += P^T (-dO), D += Q^T (-dO), dV = (-T)^T dUt', D += K^T dV
             f32x4 dv[NCT], kd[NKT];
-            frag db[NC], nb[NC], vo[NC];
+            frag db[NC], tf[NTX], nb[NC], vo[NC];
 #pragma unroll
             for (int t = 0; t < NCT; ++t) {
                 du[t] += take<f32x4>(sE, wave * NCT + t, lane);
@@ -873,6 +898,12 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
                 [&](auto E, const frag &f) __attribute__((always_inline)) {
                     constexpr int e = E, ku = e - NTX;
                     if constexpr (ku == 0) {
+                        if constexpr (kTwoTerms<T>) {
+                            frag dr[NC];
+#pragma unroll
+                            for (int c = 0; c < NC; ++c) dr[c] = rest_operand(du, db[c], c);
+                            second_terms(dv, tf, dr, [](auto E) { return upper_pair<TPS>(E); }, std::make_integer_sequence<int, NTX>{});
+                        }
                         if (kSumFirst<T>)
 #pragma unroll
                             for (int c = 0; c < NCT; ++c) dv[c] += tab4(tab + 2 * C, row4<T>(c, g)) * du[c];
@@ -893,8 +924,11 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
                             for (int c = 0; c < NC; ++c) vo[c] = GATED || masked ? as_operand(dv, c, T()) : nb[c];
                         }
                     }
-                    if constexpr (ku < 0) { constexpr TilePair b = upper_pair<TPS>(e); mma16(dv[b.t], f, db[b.s]); }
-                    else mma16(kSumFirst<T> ? kd[ku % NKT] : D[ku % NKT], f, nb[ku / NKT]);
+                    if constexpr (ku < 0) {
+                        constexpr TilePair b = upper_pair<TPS>(e);
+                        mma16(dv[b.t], f, db[b.s]);
+                        if (kTwoTerms<T>) tf[e] = f;
+                    } else mma16(kSumFirst<T> ? kd[ku % NKT] : D[ku % NKT], f, nb[ku / NKT]);
                 });
             if constexpr (kSumFirst<T>)
 #pragma unroll

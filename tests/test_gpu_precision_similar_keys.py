@@ -1,0 +1,88 @@
+"""The error against 64 bits where keys (and queries) resemble each other: what a chunk writes is then a difference of large terms
+(v - S^T k, and dUt likewise backward), and a factor rounded once more than the method needs shows, which it does not on the
+independent random keys of the other tests."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2406_06484_amd as dn
+from paper_2406_06484_amd.synth import make_gate, make_inputs, round_to_bf16, round_to_f32
+from tests.gpu_util import dev_inputs
+
+pytestmark = pytest.mark.gpu
+C = 64
+
+
+def _similar(seed, cos, queries, **kw):
+    """inputs whose unit keys (and queries) have a mean cosine `cos`: a direction per head and an independent part"""
+    inp = make_inputs(seed, with_initial_state=True, with_dfinal_state=True, **kw)
+    rnd = round_to_bf16 if inp.dtype == "bf16" else round_to_f32
+    u = np.random.default_rng(seed + 991).standard_normal(inp.k.shape[-2:])
+    u /= np.linalg.norm(u, axis=-1, keepdims=True)
+
+    def mix(x):
+        y = np.sqrt(cos) * u + np.sqrt(1 - cos) * x
+        return rnd(y / np.linalg.norm(y, axis=-1, keepdims=True))
+
+    inp.k = mix(inp.k)
+    if queries:
+        inp.q = mix(inp.q)
+    return inp
+
+
+def _rms(x, ref):
+    return float(np.linalg.norm(np.asarray(x, dtype=np.float64) - ref) / np.linalg.norm(ref))
+
+
+def _passes(inp, rule, g=None):
+    """({name: output of the library}, {name: the oracle's})"""
+    d = dev_inputs(inp)
+    args, host = [d[n] for n in ("q", "k", "v", "beta")], [inp.q, inp.k, inp.v, inp.beta]
+    if rule == "gated":
+        args, host = args + [torch.from_numpy(g).float().cuda()], host + [g]
+    pre = {"plain": "", "gated": "gated_"}[rule]
+    o, ST, saved = getattr(dn, "deltanet_" + pre + "fwd_save")(*args, d["S0"])
+    grads = getattr(dn, "deltanet_" + pre + "bwd_saved")(*args, d["d_o"], saved, d["dST"])
+    ref = getattr(oracle, pre + "fwd")(*host, inp.initial_state) + getattr(oracle, pre + "bwd")(*host, inp.d_o, inp.initial_state, inp.dfinal_state)
+    names = ["o", "ST", "dq", "dk", "dv", "dbeta"] + (["dg"] if rule == "gated" else []) + ["dS0"]
+    return {n: x.double().cpu().numpy() for n, x in zip(names, (o, ST) + tuple(grads))}, dict(zip(names, ref))
+
+
+def _rounded_once(inp):
+    """The plain rule in 64 bits with what bf16 matrix products have to round: S, T off its diagonal, P, Ut and, backward, dS', dV as
+    operands, and the stored outputs.  The factors of T (V - K S) and T^T dUt are not rounded."""
+    r = lambda x: x.to(torch.bfloat16).to(torch.float64)
+    t = lambda x: x.transpose(-1, -2)
+    heads = lambda x: torch.from_numpy(x).movedim(-2, 1).reshape(x.shape[0], x.shape[-2], -1, C, x.shape[-1])  # [B, H, n, C, d]
+    q, k, v, do = (heads(x) for x in (inp.q, inp.k, inp.v, inp.d_o))
+    beta = heads(inp.beta[..., None])
+    T = torch.linalg.inv(torch.eye(C, dtype=torch.float64) + torch.tril(beta * (k @ t(k)), -1)) * t(beta)
+    T = r(T - torch.diag_embed(torch.diagonal(T, dim1=-2, dim2=-1)))
+    P = r(torch.tril(q @ t(k)))
+    S, D, o, dv = torch.from_numpy(inp.initial_state), torch.from_numpy(inp.dfinal_state), torch.zeros_like(v), torch.zeros_like(v)
+    for i in range(q.shape[2]):
+        x = v[:, :, i] - k[:, :, i] @ r(S)
+        ut = r(beta[:, :, i] * x + T[:, :, i] @ x)
+        o[:, :, i] = q[:, :, i] @ r(S) + P[:, :, i] @ ut
+        S = S + t(k[:, :, i]) @ ut
+    for i in reversed(range(q.shape[2])):
+        du = t(P[:, :, i]) @ do[:, :, i] + k[:, :, i] @ r(D)
+        dv[:, :, i] = r(beta[:, :, i] * du + t(T[:, :, i]) @ du)
+        D = D + t(q[:, :, i]) @ do[:, :, i] - t(k[:, :, i]) @ dv[:, :, i]
+    tokens = lambda x: x.flatten(2, 3).movedim(1, 2).numpy()
+    return {"o": tokens(r(o)), "ST": S.numpy(), "dv": tokens(dv), "dS0": D.numpy()}
+
+
+@pytest.mark.parametrize("rule", ["plain", "gated"])
+@pytest.mark.parametrize("cos,queries", [(0.8, False), (0.9, True)])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128), (256, 256)])
+def test_bf16_rounds_no_factor_twice(dk, dv, cos, queries, rule):
+    """At most 4 % above the emulation (which differs by the order of its sums and by 64-bit accumulators).  With the factors of T (V - K S)
+    and T^T dUt in bf16: o 9 and 20 % above it at the two settings, ST 18 and 21 %, dv 11 and 22 %, dS0 14 and 37 %."""
+    inp = _similar(5, cos, queries, B=2, L=960, H=4, dk=dk, dv=dv, dtype="bf16")  # (not cut into segments)
+    got, ref = _passes(inp, rule, np.zeros(inp.beta.shape, dtype=np.float32))  # (gated without decay: the same rule)
+    em = _rounded_once(inp)
+    ratio = {n: _rms(got[n], ref[n]) / _rms(em[n], ref[n]) for n in em}
+    print(rule, dk, dv, cos, queries, ratio, flush=True)
+    assert all(x <= 1.04 for x in ratio.values()), ratio
