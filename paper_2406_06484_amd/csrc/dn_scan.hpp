@@ -127,7 +127,9 @@ template <typename T, int COLS> __device__ inline typename Op<T>::frag read_ks(c
     }
 }
 // fp32: products that meet a larger term are summed from zero and added at the end, which keeps every partial sum's rounding
-// to its own size (summed onto V and dS the results are 10 to 60 % further from the exact ones); bf16 rounds their sum to 8 bits anyway
+// to its own size (summed onto V, S and dS the results are 10 to 60 % further from the exact ones); bf16 rounds their sum to 8 bits anyway.
+// The sums over T^T walk the tokens from the chunk's end: the near ones, whose terms are the large ones, then the diagonal (from its near end,
+// where keys and queries are alike, the large terms stand in the partial sum while the rest is added, and dv is 31 % further off)
 template <typename T> constexpr bool kSumFirst = sizeof(T) == 4;
 // bf16: X and dUt, the right factors of the products with T and T^T, as two bf16 operands, the rounded value and the rest, that
 // meet the same reads of T (six more products each).  Where keys are alike X = V - K S and dV are differences of large terms, and a
@@ -641,8 +643,15 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
 #pragma unroll
                 for (int s = 0; s < NC; ++s) store_frag<T>(to, s, ub[s], lane);
             }
+            f32x4 ku[NKT];
+            if constexpr (kSumFirst<T>)
+#pragma unroll
+                for (int t = 0; t < NKT; ++t) ku[t] = zero4();
             stream<NKU, DEPTH, frag>([&](auto E) __attribute__((always_inline)) { return read_ks<T, DK>(sK, ks, E % NKT, E / NKT); },
-                                         [&](auto E, const frag &f) __attribute__((always_inline)) { mma16(S[E % NKT], f, ub[E / NKT]); });
+                                         [&](auto E, const frag &f) __attribute__((always_inline)) { mma16(kSumFirst<T> ? ku[E % NKT] : S[E % NKT], f, ub[E / NKT]); });
+            if constexpr (kSumFirst<T>)
+#pragma unroll
+                for (int t = 0; t < NKT; ++t) S[t] += ku[t];
             if (GATED) { // from this chunk's coordinates to the state itself, then to the next chunk's (one factor at a time: their product may leave the fp32 range)
                 scale(ic);
                 if (ic + 1 < nchunks) scale(ic + 1);
@@ -892,7 +901,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             stream<NTX + NKU, DEPTH, frag>(
                 [&](auto E) __attribute__((always_inline)) {
                     constexpr int e = E, ku = e - NTX;
-                    if constexpr (ku < 0) { constexpr TilePair b = upper_pair<TPS>(e); return read_ks<T, C>(sT, cs, b.t, b.s); }
+                    if constexpr (ku < 0) { constexpr TilePair b = upper_pair<TPS>(kSumFirst<T> ? NTX - 1 - e : e); return read_ks<T, C>(sT, cs, b.t, b.s); }
                     else return read_ks<T, DK>(sK, ks, ku % NKT, ku / NKT);
                 },
                 [&](auto E, const frag &f) __attribute__((always_inline)) {
@@ -925,7 +934,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
                         }
                     }
                     if constexpr (ku < 0) {
-                        constexpr TilePair b = upper_pair<TPS>(e);
+                        constexpr TilePair b = upper_pair<TPS>(kSumFirst<T> ? NTX - 1 - e : e);
                         mma16(dv[b.t], f, db[b.s]);
                         if (kTwoTerms<T>) tf[e] = f;
                     } else mma16(kSumFirst<T> ? kd[ku % NKT] : D[ku % NKT], f, nb[ku / NKT]);
