@@ -708,7 +708,10 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         auto fresh = [&]() __attribute__((always_inline)) { if (DK > 128) asm volatile("" : "+v"(lt), "+v"(lane)); }; // (see scan_fwd_body)
         constexpr int SETS = kScanSets<T, DK>;
         struct Set { Pieces<T, DK> q, k; Pieces<T, BV> d; float gm[Pieces<T, BV>::NIT]; } r[SETS];
-        Pieces<T, C> rt[2];
+        // (of T, which is needed half a step later than the rest, one chunk at d_k = 256: with two the gated scan of 64 columns spills 14
+        // registers and takes 168 us for 156, the plain one 140 for 137; 16 384 tokens of 8 heads)
+        constexpr int TSETS = DK > 128 ? 1 : 2;
+        Pieces<T, C> rt[TSETS];
         const int kc = LdsTile<T, DK>::kc0(lane);
         TabRegs<T, GATED> tb[2];
         // (chunks are walked from the last one down; a number below zero asks for nothing)
@@ -747,7 +750,8 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         fetch_tab(tb[0], last); fetch_tab(tb[1], last - 1);
         fetch(r[0], last);
         if (SETS == 2) fetch(r[SETS - 1], last - 1);
-        fetch_t(rt[0], last); fetch_t(rt[1], last - 1);
+        fetch_t(rt[0], last);
+        if (TSETS == 2) fetch_t(rt[TSETS - 1], last - 1);
         store_tab(tb[0], last);
         stash(r[0], last);
         fetch_tab(tb[0], last - 2);
@@ -773,7 +777,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
                 }
             }
             if (MOVES) ht.template store<true>(sT, lt);
-            fetch_t(ht, ic - 2);
+            fetch_t(ht, ic - TSETS);
             store_tab(nt, ic - 1);
             fetch_tab(nt, ic - 3);
             if (SETS == 2) fetch(cu, ic - 2); // (here rather than in B, where the LDS takes the next chunk)
@@ -811,7 +815,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         for (int ic = last;;) {
             step(r[SETS - 1], r[0], rt[0], tb[1], ic);
             if (--ic < 0) break;
-            step(r[0], r[SETS - 1], rt[1], tb[0], ic);
+            step(r[0], r[SETS - 1], rt[TSETS - 1], tb[0], ic);
             if (--ic < 0) break;
         }
         if (!STATE) flush(0);
