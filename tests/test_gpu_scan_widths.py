@@ -5,29 +5,42 @@ import pytest
 import torch
 
 import paper_2406_06484_amd as dn
-from paper_2406_06484_amd.synth import make_inputs
+from paper_2406_06484_amd.synth import make_gate, make_inputs, make_pre_activations
 from tests.gpu_util import check_fwd_bwd, dev_inputs
+from tests.test_gpu_fused import run_fused
+from tests.test_gpu_gated import run_gated
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("L", [1, 63, 64, 65, 200])
+@pytest.mark.parametrize("rule,L", [("plain", 1), ("plain", 63), ("plain", 64), ("plain", 65), ("plain", 200),
+                                    ("gated", 64), ("gated", 200), ("fused", 64), ("fused", 200)])
 @pytest.mark.parametrize("dtype,dk,dv,H", [("f32", 64, 64, 2), ("f32", 32, 64, 3), ("f32", 64, 32, 2), ("bf16", 64, 64, 2), ("bf16", 64, 128, 2),
                                            ("bf16", 128, 64, 2), ("bf16", 128, 128, 2), ("bf16", 256, 256, 1)])
-def test_every_width_gives_the_same_bits(dtype, dk, dv, H, L):
-    kw = dict(B=1, L=L, H=H, dk=dk, dv=dv, dtype=dtype, with_initial_state=True, with_dfinal_state=True)
-    check_fwd_bwd(make_inputs(77 + L, **kw), label="width %s %dx%d L=%d" % (dtype, dk, dv, L))
-    d = dev_inputs(make_inputs(77 + L, **kw))
+def test_every_width_gives_the_same_bits(dtype, dk, dv, H, L, rule):
+    inp = make_inputs(77 + L, B=1, L=L, H=H, dk=dk, dv=dv, dtype=dtype, with_initial_state=True, with_dfinal_state=True)
+    label = "width %s %s %dx%d L=%d" % (rule, dtype, dk, dv, L)
+    g = make_gate(3, inp.beta.shape)
+    if rule == "plain":
+        check_fwd_bwd(inp, label=label)
+    elif rule == "gated":
+        run_gated(inp, g, label=label)
+    else:
+        inp = make_pre_activations(3, inp)
+        run_fused(inp, label)
+    d = dev_inputs(inp)
+    d["g"] = torch.from_numpy(g).cuda()
+    f = lambda n: getattr(dn, "deltanet_" + {"plain": "", "gated": "gated_", "fused": "fused_"}[rule] + n)
 
     def passes(n):
         x = {k: v.expand(n, *v.shape[1:]).contiguous() for k, v in d.items() if v is not None}
-        args = [x[k] for k in ("q", "k", "v", "beta")]
-        o, ST = dn.deltanet_fwd(*args, x["S0"])
-        g = dn.deltanet_bwd(*args, x["d_o"], x["S0"], x["dST"])
-        o2, ST2, saved = dn.deltanet_fwd_save(*args, x["S0"])
-        g2 = dn.deltanet_bwd_saved(*args, x["d_o"], saved, x["dST"])
+        args = [x[k] for k in ("q", "k", "v", "beta") + (("g",) if rule == "gated" else ())]
+        o, ST = f("fwd")(*args, x["S0"])
+        grads = f("bwd")(*args, x["d_o"], x["S0"], x["dST"])
+        o2, ST2, saved = f("fwd_save")(*args, x["S0"])
+        grads2 = f("bwd_saved")(*args, x["d_o"], saved, x["dST"])
         torch.cuda.synchronize()
-        return [o, ST, *g, o2, ST2, *g2]
+        return [o, ST, *grads, o2, ST2, *grads2]
 
     one = passes(1)
     chains = [256 * 32 // dv, 256 * 64 // dv]  # as many as fill the chip with 32, and with 64, columns per workgroup
