@@ -74,7 +74,8 @@ template <typename T, int DK, int DV> size_t max_lds_bytes() {
 // workgroups still fit the chip at once: the fewer share a CU's LDS, the shorter a step.  With the fewest and with the most waves, scan
 // alone, in us: bf16, 16 heads of 128, 1 x 1000 tokens 21.7 and 29.8, 2 x 500 forward 15.4 and 19.1, reverse 16.2 and 20.3; 8 heads,
 // 1 x 300 10.1 and 13.3; fp32, 1 x 256 of 2 heads of 64, 21.3 and 24.0.  Past one round of the chip the widest is taken: q and k
-// are then read by the fewest workgroups (not timed against narrower ones).
+// are then read by the fewest workgroups, and a CU holds one workgroup of any width.  With 64, 32 and 16 columns, at 32 x 512 tokens of width 2048: d = 64,
+// forward 64 101 184, reverse 81 120 207; d = 128 72 116 199 and 99 151 257; at 32 x 128: d = 64 27 37 63 and 32 43 76, d = 128 34 44 79 and 40 53 94.
 template <typename T, int DV> static inline int chain_waves(const Problem &pb, long nchains, int passes) {
     for (int w = 1; w < kMostChainWaves<T, DV>; w *= 2)
         if ((long)chain_grid((int)nchains, DV / (16 * w)) * passes <= pb.num_cus) return w;

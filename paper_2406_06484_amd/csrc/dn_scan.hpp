@@ -476,11 +476,14 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
         };
         fetch_tab(tb[0], 0); fetch_tab(tb[1], 1);
         fetch(r[0], 0);
-        if (SETS == 2) fetch(r[SETS - 1], 1);
         store_tab(tb[0], 0);
         stash(r[0], 0);
+        // The second chunk is not asked for before the first one is there: past one round of the chip all workgroups of a round begin
+        // together, and the first step waits for both chunks of all of them.  64 x 128 tokens of width 2048, d = 64 and 128: forward that keeps its
+        // tiles 59.0 -> 55.3 and 77.6 -> 71.8 us, reverse 60.6 -> 53.9 and 74 -> 69.5, pair 100 -> 94 and 136 -> 130; few or long chains do not change.
+        __builtin_amdgcn_sched_barrier(0);
         fetch_tab(tb[0], 2);
-        if (SETS == 1) fetch(r[0], 1);
+        fetch(r[SETS - 1], 1);
         lds_barrier();
         if (GATED) lds_barrier(); // (the chain waves read the tables before they hand over the state)
         auto step = [&](Set &nx, Set &cu, TabRegs<T, GATED> &nt, int ic) __attribute__((always_inline)) { // nx, nt: of chunk ic + 1
@@ -749,13 +752,13 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         const int last = nchunks - 1;
         fetch_tab(tb[0], last); fetch_tab(tb[1], last - 1);
         fetch(r[0], last);
-        if (SETS == 2) fetch(r[SETS - 1], last - 1);
         fetch_t(rt[0], last);
-        if (TSETS == 2) fetch_t(rt[TSETS - 1], last - 1);
         store_tab(tb[0], last);
         stash(r[0], last);
+        __builtin_amdgcn_sched_barrier(0);
         fetch_tab(tb[0], last - 2);
-        if (SETS == 1) fetch(r[0], last - 1);
+        fetch(r[SETS - 1], last - 1); // (not before the first chunk is there, see scan_fwd_body)
+        if (TSETS == 2) fetch_t(rt[TSETS - 1], last - 1);
         lds_barrier();
         auto step = [&](Set &nx, Set &cu, Pieces<T, C> &ht, TabRegs<T, GATED> &nt, int ic) __attribute__((always_inline)) { // nx, nt: of chunk ic - 1; ht: of chunk ic
             fresh();
