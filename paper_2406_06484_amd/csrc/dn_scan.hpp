@@ -689,6 +689,11 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
     constexpr bool OFF = kOffloadQdO<T>;
     static_assert(!OFF || (kSplitHelpers<T, DK, DIR_BWD> && NKT <= 4), "one tile of Q^T dO per helper that moves tiles");
     constexpr int kAuxV = BV * sizeof(T) >= 128 ? kAuxOnce : kAuxKeep; // see scan_fwd_body
+    // fp32: ten waves leave each one 168 registers.  With the addresses of the waves that move tiles and the chain wave's into T carried through
+    // the loop, 10 to 27 of two chain waves spilled (2 or 3 of one in the passes over segments), and a step waited for them behind its stores; so
+    // these are formed in every step.  8 x 1024 tokens of 32 heads of 64, reverse scan 168 -> 164 us, gated 200 -> 167, pair 288 -> 275 and 324 -> 280; all
+    // addresses of a lane formed anew take 180 and 185.  One chain wave (97 us as it is, 109 so) and d_k = 32 (112 and 114) have the registers.
+    constexpr bool kFreshAddresses = sizeof(T) == 4 && DK > 32 && (NCW > 1 || STATE);
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char *sQ = smem + SM::oQ, *sD = smem + SM::oV, *sT = smem + SM::oT, *sE = smem + SM::oE, *sF = smem + SM::oF, *sO = smem + SM::oO;
 
@@ -708,7 +713,11 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
         constexpr bool FORMS = decltype(forms)::value, MOVES = decltype(moves)::value;
         int lane = threadIdx.x & 63, lt = 64 * (hw & 3) + lane;
         const int w = !FORMS ? hw & 3 : NCW == 1 ? (hw == 3 ? 3 : (hw + 2) % 3) : hw < 2 ? hw : 5 - hw; // (as in the forward scan)
-        auto fresh = [&]() __attribute__((always_inline)) { if (DK > 128) asm volatile("" : "+v"(lt), "+v"(lane)); }; // (see scan_fwd_body)
+        // (see scan_fwd_body)
+        auto fresh = [&]() __attribute__((always_inline)) {
+            if (DK > 128) asm volatile("" : "+v"(lt), "+v"(lane));
+            else if (kFreshAddresses) asm volatile("" : "+v"(lt));
+        };
         constexpr int SETS = kScanSets<T, DK>;
         struct Set { Pieces<T, DK> q, k; Pieces<T, BV> d; float gm[Pieces<T, BV>::NIT]; } r[SETS];
         // (of T, which is needed half a step later than the rest, one chunk at d_k = 256: with two the gated scan of 64 columns spills 14
@@ -845,7 +854,8 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             for (int i = 0; i < 4; ++i) D[t][i] = 0.f - src[(long)(row4<T>(t, g) + i) * DV];
     }
     if (nchunks > 0) {
-        const int kc = LdsTile<T, DK>::kc0(lane), ks = LdsTile<T, DK>::ks0(lane), cs = LdsTile<T, C>::ks0(lane), vc = LdsTile<T, BV>::ac0(lane, wave);
+        const int kc = LdsTile<T, DK>::kc0(lane), ks = LdsTile<T, DK>::ks0(lane), vc = LdsTile<T, BV>::ac0(lane, wave);
+        int cs = LdsTile<T, C>::ks0(lane);
         const int last = nchunks - 1;
         frag Db[NK];
         lds_barrier();
@@ -862,7 +872,8 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             const unsigned char *sK = smem + SM::oK + (ic & 1) * SM::szK;
             const float *tab = reinterpret_cast<const float *>(smem + SM::oTab + (ic & 1) * SM::szTab);
             const long tile = (long)(cb + ic) * H + h;
-            // A: dUt' = K D (for now), (d_k = 256) D += Q^T (-dO)
+            if (kFreshAddresses) asm volatile("" : "+v"(cs));
+            // A: dUt' = K D (for now), D += Q^T (-dO) (in fp32 a helper forms that product and B adds it)
             f32x4 du[NCT];
             decltype(read_ac<T, BV>(sD, 0, 0, 0, 0)) dr[NCT];
             frag ob[NC];
