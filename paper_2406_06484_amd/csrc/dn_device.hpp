@@ -1,6 +1,6 @@
 // Device-side building blocks for the gfx950 DeltaNet kernels: MFMA tile products from LDS,
 // accumulator <-> LDS/global movers, tile loaders, the 64x64 unit-lower-triangular inverse.
-// The chunk is C = 64 tokens; the prep kernel runs 4 wavefronts, the scans and the chunk kernel 8.
+// The chunk is C = 64 tokens; the prep kernel runs 4 wavefronts, the chunk kernel 8, the scans 5 to 12.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

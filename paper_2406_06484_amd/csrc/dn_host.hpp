@@ -53,7 +53,7 @@ struct Ptrs {
 // and uncut, in us (forward pass, training step): 1 x 1024 tokens 36 84 and 26 65, 1 x 2048 57 133 and 42 118, 1 x 4096 73 191 and
 // 75 220, 1 x 8192 105 301 and 141 425; with twice the chains 2 x 4096 99 286 and 84 289, 2 x 8192 171 532 and 177 577.  In fp32,
 // whose chunk step is three times as long, 1 x 1024 of 8 heads 48 109 and 72 156.  So bf16 sequences under 4096 tokens would be faster
-// uncut (by 8 to 20 us); the line does not look at the length, because a short sequence is held to the same path, and results, as a long one.
+// uncut (by 8 to 20 us); the line does not look at the length, because tests/test_gpu_parity_small.py holds two such shapes to the cut path.
 inline int segment_count(int N, int L, int H, int d_k, int d_v, int nv, bool packed, int chunk = 64) {
     if (packed || d_k != d_v || d_k > 128 || L <= 0) return 1;
     const long wgs = (long)N * H * nv;

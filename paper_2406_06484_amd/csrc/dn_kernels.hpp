@@ -101,7 +101,7 @@ static __global__ void k_state_copy(float *dst, const float *src, long count) {
 
 // =============================================================================================
 // k_wy_prep: per chunk, T = (I + tril(diag(beta) K K^T, -1))^-1 diag(beta) (Eq. 10).
-// W = T K and U = T V (Eq. 11) are rebuilt from T inside the scan kernels: T is 8 KB per chunk
+// W = T K and U = T V (Eq. 11) are never formed, the scans multiply V - K S by T: 8 KB per chunk
 // where W and U are 32 KB.
 // A chain of short serial stages per workgroup: what counts is how many are resident (eight per CU; K unpadded beyond 16 bytes a
 // row, the inverse in K's bytes and without scratch) and the LDS instructions of the inverse.  Against the form with the merges
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
 }
 
 // =============================================================================================
-// The chain-serial kernels (dn_scan.hpp): NCW chain waves of 16 state columns each and four loader waves per workgroup
+// The chain-serial kernels (dn_scan.hpp): NCW chain waves of 16 state columns each and four or eight helper waves per workgroup
 template <typename T, int DK, int DV, bool GATED, int NCW>
 __global__ __launch_bounds__((kScanThreads<T, DK, DIR_FWD, NCW>)) void k_scan_fwd(SeqMap sm, int H, Ptrs p) {
     scan_fwd_body<T, DK, DV, SCAN_OUT, GATED, NCW>(sm, H, p, blockIdx.x);
@@ -222,7 +222,7 @@ __global__ __launch_bounds__((kScanThreads<T, DK, DIR_FWD, NCW>)) void k_scan_fw
 }
 
 // A forward pass over few, long chains leaves most CUs idle.  Every stretch of a chain acts on the state as an
-// affine map S_out = M S_in + N (M = the product of the chunks' (I - K^T W), d_k x d_k; N = what the stretch writes
+// affine map S_out = M S_in + N (M = the product of the chunks' (I - K^T T K), d_k x d_k; N = what the stretch writes
 // starting from zero; Eq. 8), so the sequence is cut into G segments that are scanned side by side:
 //   k_scan_state   per segment, both in one grid: N (the scan from a zero state) and M (the same scan on v = 0
 //                  starting from the identity; needs d_v = d_k), final states only

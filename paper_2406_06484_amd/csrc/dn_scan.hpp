@@ -16,15 +16,15 @@
 // forward 85.9 -> 68, forward that keeps its tiles 102.7 -> 104, reverse 100.6 -> 84 (both at 5 TB/s: HBM bounds them); gated 144 -> 98
 // and 112 -> 96; d = 256 229 -> 168 and 236 -> 137; fp32, 2 x 1500 tokens, 8 heads of 64, 184 -> 99 and 170 -> 97.
 //
-// A workgroup is NCW such chain waves (16 NCW columns) and four helper waves.  What bounds a chain wave is the rate at which ONE wave
+// A workgroup is NCW such chain waves (16 NCW columns) and four or eight helper waves (kSplitHelpers).  What bounds a chain wave is the rate at which ONE wave
 // can read the LDS (24 cycles for 16 bytes a lane, 13 for 8; four waves together reach four times that), not its products (16
 // cycles for each of those reads), so everything that is not on the chain goes to the helpers: they bring the tiles from global
-// memory two chunks ahead, through registers into the LDS, form P = tril(Q K^T), keep it in registers as the operand of the
+// memory one or two chunks ahead (kScanSets), through registers into the LDS, form P = tril(Q K^T), keep it in registers as the operand of the
 // next product, and form O (P^T dO) from it; in the forward scan a helper owns 16 tokens, whose Q no other wave reads.
 // A chunk step is two barrier intervals; what an interval reads is written in the other one, so only K and the tables are kept twice.
 //   forward  A  chain: X = V - K S, Ut = T X                helpers: P, Q S
 //            B  chain: S += K^T Ut                          helpers: O = Q S + P Ut, O to memory, the next chunk's K, V, T, Q
-//   reverse  A  chain: K dS'                                helpers: P, P^T dO, Q^T dO, this chunk's T, the dV of the chunk before to memory
+//   reverse  A  chain: K dS', Q^T dO                        helpers: P, P^T dO, (fp32) Q^T dO, this chunk's T, the dV of the chunk before to memory
 //            B  chain: dUt, dV = T^T dUt, dS -= K^T dV      helpers: the next chunk's K, Q, dO
 //
 // Rounding points in bf16: S, Ut, P, T (dS', dV) as operands; X and dUt go in as two of them (kTwoTerms).  The diagonal of T, the largest
@@ -273,7 +273,8 @@ __device__ inline bool chain_of_block(int bid, int nchains, int nv, int &chain, 
 __host__ inline int chain_grid(int nchains, int nv) { return ((nchains + 7) / 8) * 8 * nv; }
 
 // Up to d_k = 128 the helpers are eight waves, four that form P and the products with it and four that move tiles; with the
-// registers of d_k = 256 a SIMD holds only two waves, and four do both.
+// registers of d_k = 256 a SIMD holds only two waves, and four do both.  (The forward scans without outputs form nothing: there the first four wait at
+// the barriers.  They share a grid, and so the number of threads, with the reverse scan.)
 // So they do in the fp32 forward scan that has outputs: with eight it takes 79 us and not 99 (3 x 1500 tokens, 8 heads of 64), but the
 // reverse scan, whose chain waits for the helpers' products, takes 97 with eight, and it is held to the forward scan's time
 // (tests/test_gpu_scan_balance.py).
@@ -303,7 +304,7 @@ template <typename T, int DK, int DIR, int NCW> __device__ inline int helper_num
 template <typename T, int DK, int DIR, int NCW> constexpr int kScanThreads = 64 * NCW + (kSplitHelpers<T, DK, DIR> ? 2 : 1) * NTL;
 // How many chunks the helpers' registers hold on their way to the LDS: two (16 384 tokens of 8 heads of 256: forward scan that keeps its
 // tiles 196 us with one and 168 with two, reverse scan 155 and 137); in fp32, whose steps are long and whose tiles are twice as large, one.
-template <typename T, int DK> constexpr int kScanSets = sizeof(T) == 4 ? 1 : 2;
+template <typename T> constexpr int kScanSets = sizeof(T) == 4 ? 1 : 2;
 // what one chunk's row of the tables is made from, per thread lt < 64 (the others hold copies)
 template <typename T, bool GATED> struct TabRegs {
     float gm, gi;
@@ -437,7 +438,7 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
         const int w = !FORMS ? hw & 3 : NCW == 1 ? (hw == 0 ? 0 : 4 - hw) & 3 : hw < 2 ? hw : 5 - hw;
         // (d_k = 256: the addresses derived from these are formed where they are used, not carried through the loop; no registers)
         auto fresh = [&]() __attribute__((always_inline)) { if (DK > 128) asm volatile("" : "+v"(lt), "+v"(lane)); };
-        constexpr int SETS = kScanSets<T, DK>;
+        constexpr int SETS = kScanSets<T>;
         struct Set { Pieces<T, DK> k; Pieces<T, BV> v; Pieces<T, C> t; OwnRows<T, DK> q; } r[SETS];
         TabRegs<T, GATED> tb[2];
         unsigned char *mine = sQ + w * 16 * (BV > DK ? LdsTile<T, BV>::RB : LdsTile<T, DK>::RB);
@@ -718,7 +719,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             if (DK > 128) asm volatile("" : "+v"(lt), "+v"(lane));
             else if (kFreshAddresses) asm volatile("" : "+v"(lt));
         };
-        constexpr int SETS = kScanSets<T, DK>;
+        constexpr int SETS = kScanSets<T>;
         struct Set { Pieces<T, DK> q, k; Pieces<T, BV> d; float gm[Pieces<T, BV>::NIT]; } r[SETS];
         // (of T, which is needed half a step later than the rest, one chunk at d_k = 256: with two the gated scan of 64 columns spills 14
         // registers and takes 168 us for 156, the plain one 140 for 137; 16 384 tokens of 8 heads)
@@ -901,7 +902,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
                     else mma16(D[(e - NKS) % NKT], f, ob[(e - NKS) / NKT]);
                 });
             lds_barrier();
-            // B: dUt' += P^T (-dO), D += Q^T (-dO), dV = (-T)^T dUt', D += K^T dV
+            // B: dUt' += P^T (-dO), dV = (-T)^T dUt', D += K^T dV (fp32: and Q^T (-dO))
             f32x4 dv[NCT], kd[NKT];
             frag db[NC], tf[NTX], nb[NC], vo[NC];
 #pragma unroll

@@ -1,4 +1,4 @@
-"""The scans of few chains own 32 state columns per workgroup instead of 64.  A batch of copies of one sequence, large enough for
+"""The scans of few chains own 16 or 32 state columns per workgroup instead of 64 (of 32 in fp32).  A batch of copies of one sequence, large enough for
 the ordinary blocks, has to give the bits of the sequence alone: the tiles are formed by the same products in the same order."""
 import numpy as np
 import pytest

@@ -129,8 +129,8 @@ def test_many_heads_and_the_sequence_count_limit():
 
 
 def test_head_size_256():
-    # d_k = d_v = 256: the scans own 32 state columns per workgroup, the backward's chunk kernel streams S and dS' in
-    # column blocks
+    # d_k = d_v = 256: the scans own 16 to 64 state columns per workgroup, the backward's chunk kernel streams S and dS' in
+    # blocks of 32
     from paper_2406_06484_amd.synth import make_gate
     inp = make_inputs(31, B=2, L=200, H=2, dk=256, dv=256, dtype="bf16", with_initial_state=True, with_dfinal_state=True)
     inp.initial_state *= 10.0

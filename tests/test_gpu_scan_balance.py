@@ -1,5 +1,6 @@
-"""fp32: the reverse scan's dV product runs on waves that have no other product in its interval.  On the waves that have one it made
-the reverse scan 1.10 to 1.15 times as long as the forward scan that keeps its tiles; beside them it is 0.90 to 0.92 times as long."""
+"""fp32: the reverse scan is about as long as the forward scan that keeps its tiles (96 us each, 1.01 times).  The reverse scan's chain waits for
+the helpers' products in every step, so it has eight helper waves where this forward scan has four; with the chain
+wave forming every address anew in each step it takes 109 us."""
 import pytest
 import torch
 
