@@ -12,9 +12,9 @@
 // lane exchange between them.  (The form this replaced kept 32 x 32 tiles of the state on eight wavefronts, formed W = T K and
 // U = T V per chunk and passed S, W, P and Ut through the LDS: 5.8 K cycles a step in three barrier intervals, whose operand
 // reads alone filled the LDS for 3 K of them.  Now 2.9 K beside one chain wave and 4.1 K beside four.)
-// Scan times before and now: forward pass of 1 x 1000 tokens, 16 heads of 128, 34.7 -> 21.6 us; 16 384 tokens of width 2048, d = 128,
-// forward 85.9 -> 68, forward that keeps its tiles 102.7 -> 104, reverse 100.6 -> 84 (both at 5 TB/s: HBM bounds them); gated 144 -> 98
-// and 112 -> 96; d = 256 229 -> 168 and 236 -> 137; fp32, 2 x 1500 tokens, 8 heads of 64, 184 -> 99 and 170 -> 97.
+// Scan times before and now, by events on one device: forward pass of 1 x 1000 tokens, 16 heads of 128, 34.7 -> 22.9 us; 8 x 2048 tokens of width 2048,
+// d = 128, forward 85.9 -> 66.9, forward that keeps its tiles 102.3 -> 97.0, reverse 99.0 -> 85.1 (both at 5.2 TB/s: HBM bounds them); gated 147 -> 102
+// and 112 -> 97; d = 256 229 -> 165 and 236 -> 136; 4 x 4096, d = 64, 123 -> 121 and 126 -> 112; fp32, 2 x 1500 tokens, 8 heads of 64, 184 -> 96 and 170 -> 97.
 //
 // A workgroup is NCW such chain waves (16 NCW columns) and four or eight helper waves (kSplitHelpers).  What bounds a chain wave is the rate at which ONE wave
 // can read the LDS (24 cycles for 16 bytes a lane, 13 for 8; four waves together reach four times that), not its products (16
