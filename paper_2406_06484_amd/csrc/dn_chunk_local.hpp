@@ -16,15 +16,12 @@
 // above; see masked_rows in the kernel.  (The prologue variant needs none of it: its gradient is that of the logit,
 // dlogit_i = beta_i (1 - beta_i) G_i . e_i, which has no quotient.)
 //
+// This form holds the tiles on their way in registers; it is the one for fp32 and, in bf16, for d_k = 256 (see kDmaChunk).
 // The operands with a d_v axis (S, dS', dO, dV, Ut) are walked in blocks of BVB state columns, each read from global memory
 // once; K and Q stay in LDS for the chunk.  Every block waits in registers from the moment it is requested; as soon as it has
-// moved to LDS the same registers request the block NS blocks on (of the workgroup's next chunk, at the end), so about one
-// chunk's worth of loads (d = 128; NS blocks at d = 256) is in flight at any time.
-// Per chunk and head 192 KB through HBM at d = 128 in bf16 (read q, k, v, dO, dV, Ut, S, dS'; write dq, dk).  Kernel time at
-// 16 384 tokens of width 2048, with the shorter form of dbeta (no V, no products K S and K K^T) and now, between event records:
-// d = 128 147 -> 171 us, d = 64 116 -> 132, d = 256 200 -> 213, gated 196 -> 218, prologue 187 -> 212.  In a kernel trace d = 128
-// takes 161 us for 836 MB of counted traffic: 5.2 TB/s, the rate of a large copy, which is what bounds it.  (The kernel that went
-// through the inverse, with eleven barrier intervals a chunk where this one has six: 200, 224, 249, 229, 233 us between records.)
+// moved to LDS the same registers request the block NS blocks on (of the workgroup's next chunk, at the end).
+// Kernel time at 16 384 tokens of 8 heads of 256, between event records, with the shorter form of dbeta (no V, no products K S and
+// K K^T) and now: 200 -> 213 us.  (The kernel that went through the inverse, with eleven barrier intervals a chunk where this one has six: 249.)
 #pragma once
 #include <type_traits>
 
@@ -33,12 +30,11 @@
 namespace dn {
 
 template <typename T, int DK, int DV> struct LocalSmem {
-    static constexpr int BVB0 = sizeof(T) == 2 ? (DK > 128 ? 32 : 64) : (DK > 32 ? 32 : 64);
+    static constexpr int BVB0 = DK > 32 ? 32 : 64;
     static constexpr int BVB = DV < BVB0 ? DV : BVB0, NB = DV / BVB; // state columns per block, blocks per chunk
     static constexpr int NS = NB < 2 ? 1 : 2;                        // register sets for the blocks in flight
     static_assert(NB % NS == 0, "blocks alternate between the register sets");
-    // (d_k = 64: rows padded by 8, so that two workgroups fit the LDS of a CU)
-    static constexpr int LK = (sizeof(T) == 2 && DK == 64) ? ldc<T>(DK) : ldn<T>(DK);
+    static constexpr int LK = ldn<T>(DK);
     static constexpr int LB = ldc<T>(BVB), LU = ldc<T>(C), LT = ldn<T>(C), LQO = ldc<T>(DK);
     static constexpr size_t oK = 0;
     static constexpr size_t oQ = oK + align16(sizeof(T) * C * LK);
@@ -56,10 +52,8 @@ template <typename T, int DK, int DV> struct LocalSmem {
     static constexpr size_t oDV = oDO + align16(sizeof(T) * C * LB);
     static constexpr size_t oUt = oDV + align16(sizeof(T) * C * LB);
     static constexpr size_t oL = oUt + align16(sizeof(T) * BVB * LU);
-    // ... and for the chunks with masked rows tril(K K^T, -1) and, where there is room, those rows of the block as they arrived
-    // (dUt, V); with two workgroups per CU there is none, and they are read again from global memory
-    static constexpr bool ROWS = !(sizeof(T) == 2 && DK <= 64 && DV <= 64);
-    static constexpr size_t oMD = oL + align16(sizeof(T) * C * LU), szM = ROWS ? align16(sizeof(T) * C * LB) : 0, oMV = oMD + szM;
+    // ... and for the chunks with masked rows tril(K K^T, -1) and those rows of the block as they arrived (dUt, V)
+    static constexpr size_t oMD = oL + align16(sizeof(T) * C * LU), szM = align16(sizeof(T) * C * LB), oMV = oMD + szM;
     static constexpr size_t endB = oMV + szM;
     // ... and over its bytes, after the last one: dP and Ah + Ah^T, the staging tiles of the waves that own C x d_k tiles
     // (prologue variant: dq and dk as C x d_k matrices instead)
@@ -69,8 +63,6 @@ template <typename T, int DK, int DV> struct LocalSmem {
     static constexpr size_t endS = oStage + NSTG * sizeof(T) * Stage<T>::ELEMS;
     static constexpr size_t oDQm = oStage, oDKm = oDQm + align16(sizeof(T) * C * LQO), endP = oDKm + align16(sizeof(T) * C * LQO);
     static constexpr size_t bytes = cmax(endB, endS), bytes_pro = cmax(oL, endP);
-    // d_k, d_v <= 64 in bf16: two workgroups per CU
-    static constexpr int WPC = (bytes <= 80 * 1024 && bytes_pro <= 80 * 1024 && sizeof(T) == 2 && DK <= 64 && DV <= 64) ? 2 : 1;
 };
 
 struct NoTile {};
@@ -112,16 +104,16 @@ template <typename T, int COLS, int ROWS, int NT> struct FragRegs {
 };
 
 template <typename T, int DK, int DV, int VAR>
-__global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSmem<T, DK, DV>::WPC))) void k_bwd_local(SeqMap sm, int H, Ptrs p, int chunks_total) {
+__device__ __forceinline__ void bwd_local_regs(SeqMap sm, int H, Ptrs p, int chunks_total) {
     using SM = LocalSmem<T, DK, DV>;
     constexpr bool GATED = VAR == VAR_GATED, PRO = VAR == VAR_PROLOGUE;
     constexpr int BVB = SM::BVB, NB = SM::NB;
     constexpr int NS = GATED || (PRO && DK > 128) ? 1 : SM::NS; // (the gated kernels, and the prologue's at d_k = 256, have no registers for a second set)
     constexpr int KT = SM::TILES, KW = (KT + NWC - 1) / NWC; // 32 x 32 tiles of a C x d_k matrix, and per wave
-    // operand fragments per request batch (one where registers are short: two workgroups per CU, the gated kernels)
-    constexpr int MB = (SM::WPC == 2 || (GATED && sizeof(T) == 2)) ? 1 : 2;
+    // operand fragments per request batch (one where registers are short)
+    constexpr int MB = GATED && sizeof(T) == 2 ? 1 : 2;
     // ... of the products that only dbeta needs, and of those that only masked rows need (few registers are live there)
-    constexpr int MX = sizeof(T) == 4 ? 8 : DK > 128 ? 1 : MB, MM = sizeof(T) == 4 ? 8 : SM::WPC == 2 ? 1 : 4;
+    constexpr int MX = sizeof(T) == 4 ? 8 : 1, MM = sizeof(T) == 4 ? 8 : 4;
     // a C x BVB tile of dO, dV: 512 pieces of 16 bytes, or 256 (then each half of the workgroup fetches one of the two)
     constexpr bool HALF = C * BVB / El<T>::VEC < NTC;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -277,8 +269,8 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         T du[4], vv[4], out[4];
-                        ld4(du, SM::ROWS ? sMD + i * SM::LB + v0 + 8 * u : (const T *)p.dv + at + 8 * u);
-                        ld4(vv, SM::ROWS ? sMV + i * SM::LB + v0 + 8 * u : (const T *)p.v + at + 8 * u);
+                        ld4(du, sMD + i * SM::LB + v0 + 8 * u);
+                        ld4(vv, sMV + i * SM::LB + v0 + 8 * u);
 #pragma unroll
                         for (int w = 0; w < 4; ++w) {
                             const int el = 4 * u + w;
@@ -311,10 +303,8 @@ __global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * LocalSm
                             uint4 *d;
                             if constexpr (HALF) d = x.a.v + i;
                             else d = x.b.v + i;
-                            if (SM::ROWS) {
-                                *reinterpret_cast<uint4 *>(sMD + row * SM::LB + (tt % TokTile::TPR) * El<T>::VEC) = *d;
-                                *reinterpret_cast<uint4 *>(sMV + row * SM::LB + (tt % TokTile::TPR) * El<T>::VEC) = x.v.v[i];
-                            }
+                            *reinterpret_cast<uint4 *>(sMD + row * SM::LB + (tt % TokTile::TPR) * El<T>::VEC) = *d;
+                            *reinterpret_cast<uint4 *>(sMV + row * SM::LB + (tt % TokTile::TPR) * El<T>::VEC) = x.v.v[i];
                             *d = make_uint4(0, 0, 0, 0);
                         }
                     }

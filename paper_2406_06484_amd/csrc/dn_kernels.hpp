@@ -7,7 +7,7 @@
 //                                     scan (dUt = P^T dO + K dS'; dV = T^T dUt; dS = dS' + Q^T dO - K^T dV) as one grid (dn_scan.hpp)
 //   k_scan_fwd_save / k_scan_bwd      the forward scan that also stores what the recompute scan would, and the reverse
 //                                     scan alone, for a backward pass that keeps the forward pass's tiles
-//   k_bwd_local  per chunk            given S, dS', Ut, dV: the chunk-local rest of the adjoint, dQ, dK, dbeta (dn_chunk_local.hpp)
+//   k_bwd_local  per chunk            given S, dS', Ut, dV: the chunk-local rest of the adjoint, dQ, dK, dbeta (dn_chunk_bf16.hpp, dn_chunk_local.hpp)
 //
 // State S is [d_k][d_v] (orientation of the paper's pseudocode listing), fp32 in registers.
 #pragma once
@@ -347,7 +347,7 @@ __global__ __launch_bounds__((kScanThreads<T, DK, DIR_BWD, NCW>)) void k_scan_bw
 }
 
 // =============================================================================================
-// The chunk-parallel backward kernel (dn_chunk_local.hpp).  Workgroups are persistent: each walks over
+// The chunk-parallel backward kernel (dn_chunk_bf16.hpp, dn_chunk_local.hpp).  Workgroups are persistent: each walks over
 // (chunk, head) tiles with a grid stride.
 constexpr int NTC = 512, NWC = 8;
 

@@ -6,6 +6,7 @@
 
 #include "dn_host.hpp"
 #include "dn_kernels.hpp"
+#include "dn_chunk_bf16.hpp"
 #include "dn_chunk_local.hpp"
 
 namespace dn {
@@ -58,15 +59,33 @@ static inline int launch_offsets(const Problem &pb) {
 // chain waves of the widest scan workgroup: 64 state columns
 template <typename T, int DV> constexpr int kMostChainWaves = sizeof(T) == 4 ? 2 : DV < 64 ? DV / 16 : 4; // (fp32: 32 columns)
 
+// Which chunk kernel: in bf16 up to d_k = 128 the one whose tiles travel straight to the LDS; fp32, and d_k = 256, where the masked rows'
+// extra work per block of 32 state columns costs that kernel more than it gains (16 384 tokens of 8 heads, none / a tenth / padding masked: tiles
+// through registers 215, 250, 247 us, straight to the LDS 204, 326, 305), keep the one that holds them in registers.
+template <typename T, int DK> constexpr bool kDmaChunk = sizeof(T) == 2 && DK <= 128;
+template <typename T, int DK, int DV> constexpr size_t local_lds() {
+    if constexpr (kDmaChunk<T, DK>) return ChunkSmem<DK, DV>::bytes;
+    else return cmax(LocalSmem<T, DK, DV>::bytes, LocalSmem<T, DK, DV>::bytes_pro);
+}
+template <typename T, int DK, int DV> constexpr size_t LocalLds = local_lds<T, DK, DV>();
+template <typename T, int DK, int DV> constexpr int local_wpc() {
+    if constexpr (kDmaChunk<T, DK>) return ChunkSmem<DK, DV>::WPC;
+    else return 1;
+}
+template <typename T, int DK, int DV, int VAR>
+__global__ __launch_bounds__(NTC) __attribute__((amdgpu_waves_per_eu(2 * local_wpc<T, DK, DV>(), 2 * local_wpc<T, DK, DV>()))) void k_bwd_local(SeqMap sm, int H, Ptrs p, int chunks_total) {
+    if constexpr (kDmaChunk<T, DK>) bwd_local_bf16<DK, DV, VAR>(sm, H, p, chunks_total);
+    else bwd_local_regs<T, DK, DV, VAR>(sm, H, p, chunks_total);
+}
+
 template <typename T, int DK, int DV> size_t max_lds_bytes() {
     constexpr size_t scan = ScanSmem<T, DK, kMostChainWaves<T, DV>>::bytes;
     static_assert(PrepSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_wy_prep LDS");
     static_assert(scan <= kLdsPerWorkgroup, "scan LDS");
     size_t m = PrepSmem<T, DK, DV>::bytes;
     if (scan > m) m = scan;
-    static_assert(LocalSmem<T, DK, DV>::bytes_pro <= kLdsPerWorkgroup && LocalSmem<T, DK, DV>::bytes <= kLdsPerWorkgroup, "k_bwd_local LDS");
-    if (LocalSmem<T, DK, DV>::bytes > m) m = LocalSmem<T, DK, DV>::bytes;
-    if (LocalSmem<T, DK, DV>::bytes_pro > m) m = LocalSmem<T, DK, DV>::bytes_pro;
+    static_assert(LocalLds<T, DK, DV> <= kLdsPerWorkgroup, "k_bwd_local LDS");
+    if (LocalLds<T, DK, DV> > m) m = LocalLds<T, DK, DV>;
     return m;
 }
 
@@ -181,12 +200,12 @@ template <typename T, int DK, int DV> int run_bwd(const Problem &pb, const Ptrs 
     }
     const SeqMap &sm = sm0;
     if (pb.chunks_ub) {
-        using SM = LocalSmem<T, DK, DV>;
-        const long tiles = (long)pb.chunks_ub * pb.H, slots = (long)pb.num_cus * SM::WPC;
+        const long tiles = (long)pb.chunks_ub * pb.H, slots = (long)pb.num_cus * local_wpc<T, DK, DV>();
         const dim3 gpers((unsigned)(tiles < slots ? tiles : slots)); // persistent: as many workgroups as the chip holds
-        if (p.g) DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_GATED>), gpers, NTC, SM::bytes, sm, pb.H, p, pb.chunks_ub);
-        else if (p.pro) DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_PROLOGUE>), gpers, NTC, SM::bytes_pro, sm, pb.H, p, pb.chunks_ub);
-        else DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_PLAIN>), gpers, NTC, SM::bytes, sm, pb.H, p, pb.chunks_ub);
+        constexpr size_t lds = LocalLds<T, DK, DV>;
+        if (p.g) DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_GATED>), gpers, NTC, lds, sm, pb.H, p, pb.chunks_ub);
+        else if (p.pro) DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_PROLOGUE>), gpers, NTC, lds, sm, pb.H, p, pb.chunks_ub);
+        else DN_LAUNCH_NT((k_bwd_local<T, DK, DV, VAR_PLAIN>), gpers, NTC, lds, sm, pb.H, p, pb.chunks_ub);
         if (p.dv_out) { // the inputs have been read
             const long words = (long)(pb.cu ? 1 : pb.N) * pb.L * pb.H * DV * (long)sizeof(T) / 4; // (rows are at least 64 bytes)
             DN_LAUNCH(k_state_copy, dim3((unsigned)((words + 4 * NTHR - 1) / (4 * NTHR))), 0, static_cast<float *>(p.dv_out), static_cast<const float *>(p.dv), words);

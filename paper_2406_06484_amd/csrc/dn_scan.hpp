@@ -252,13 +252,15 @@ template <typename T, int COLS, int AUX> __device__ __forceinline__ void tile_ou
 }
 
 // The S, dS' and Ut tiles in the workspace stand in the order of the operands: for every 16 columns of d_v and every
-// contraction step s (over d_k, or over the chunk's tokens for Ut) the 16 bytes of lane l at 16 l.  They leave (and arrive)
-// from registers in whole kilobytes.
+// contraction step s (over d_k, or over the chunk's tokens for Ut) the 16 bytes of lane l at 16 frag_place(l).  They leave from registers in
+// whole kilobytes.  In bf16 up to d_k = 128 the chunk kernel reads its operands from the tile as it stands here (dn_chunk_bf16.hpp); the
+// lanes are permuted so that these reads find different banks of the LDS.
 template <typename T, int ROWS> __device__ inline T *frag_tile(void *ws, long tile, int dv, int col16) {
     return (T *)ws + (tile * dv + 16 * col16) * ROWS;
 }
-template <typename T> __device__ inline void store_frag(T *tile, int s, const typename Op<T>::frag &f, int lane) {
-    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, f), reinterpret_cast<u32x4 *>(tile) + 64 * s + lane);
+template <typename T, int DK> __device__ inline int frag_place(int lane) { return sizeof(T) == 2 && DK <= 128 ? lane ^ (lane >> 4 << 2) : lane; }
+template <typename T> __device__ inline void store_frag(T *tile, int s, const typename Op<T>::frag &f, int place) {
+    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, f), reinterpret_cast<u32x4 *>(tile) + 64 * s + place);
 }
 
 // ---- shared by the two scans -------------------------------------------------------------------------------------------
@@ -600,7 +602,7 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
             if (SAVE) {
                 T *to = frag_tile<T, DK>(p.Sc, tile, DV, col16);
 #pragma unroll
-                for (int s = 0; s < NK; ++s) store_frag<T>(to, s, Sb[s], lane);
+                for (int s = 0; s < NK; ++s) store_frag<T>(to, s, Sb[s], frag_place<T, DK>(lane));
             }
             stream<NKS + NTX, DEPTH, frag>(
                 [&](auto E) __attribute__((always_inline)) {
@@ -645,7 +647,7 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
             if (SAVE) {
                 T *to = frag_tile<T, C>(p.Ut, tile, DV, col16);
 #pragma unroll
-                for (int s = 0; s < NC; ++s) store_frag<T>(to, s, ub[s], lane);
+                for (int s = 0; s < NC; ++s) store_frag<T>(to, s, ub[s], frag_place<T, DK>(lane));
             }
             f32x4 ku[NKT];
             if constexpr (kSumFirst<T>)
@@ -886,7 +888,7 @@ __device__ __forceinline__ void scan_bwd_body(const SeqMap &sm, int H, const Ptr
             if (!STATE) {
                 T *to = frag_tile<T, DK>(p.dSc, tile, DV, col16);
 #pragma unroll
-                for (int s = 0; s < NK; ++s) store_frag<T>(to, s, Db[s], lane);
+                for (int s = 0; s < NK; ++s) store_frag<T>(to, s, Db[s], frag_place<T, DK>(lane));
             }
 #pragma unroll
             for (int s = 0; s < NC; ++s) if (!OFF) ob[s] = join(dr, s);
