@@ -106,7 +106,8 @@ static __global__ void k_state_copy(float *dst, const float *src, long count) {
 // A chain of short serial stages per workgroup: what counts is how many are resident (eight per CU; K unpadded beyond 16 bytes a
 // row, the inverse in K's bytes and without scratch) and the LDS instructions of the inverse.  Against the form with the merges
 // on the vector ALU (six per CU, chunks fastest): 16 384 tokens of width 2048, d = 128 34 -> 25 us (100 MB, 4 TB/s), d = 64
-// 59 -> 43 us, d = 256 30 -> 24 us.  The prologue variant (two tiles mapped on the way, five per CU) takes 67 us for 300 MB as before.
+// 59 -> 43 us, d = 256 30 -> 24 us.  (The Gram product is formed transposed, so that a lane's four elements of A are neighbours and have one beta: with a
+// read of beta and a store for each of the 16 the kernel took 27.7 us for 26.6, at d = 64 39.1 for 37.0, on 1 x 1000 tokens 8.1 for 7.4.)  The prologue variant (two tiles mapped on the way, five per CU) takes 67 us for 300 MB as before.
 template <typename T, int DK, int DV> struct PrepSmem {
     static constexpr int LD = ldc<T>(DK), LF = C + 4;
     // K while the Gram product runs, then the fp32 matrix that is inverted in place
@@ -179,13 +180,20 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
     }
     lds_barrier();
     f32x16 g = zero16();
-    if (!upper) mma<DK, false, false, T, true, sizeof(T) == 2 ? 2 : 0>(g, sK + 32 * mi * SM::LD, SM::LD, sK + 32 * ni * SM::LD, SM::LD); // K K^T
+    if (!upper) mma<DK, false, false, T, true, sizeof(T) == 2 ? 2 : 0>(g, sK + 32 * ni * SM::LD, SM::LD, sK + 32 * mi * SM::LD, SM::LD); // (K K^T)^T
     lds_barrier(); // K is dead from here on; its bytes take the fp32 matrix
-    if (!upper)
-        acc_each(g, [&](int r, int c, float &val) { // A = tril(diag(beta) K K^T, -1)
-            const int i = 32 * mi + r, j = 32 * ni + c;
-            sX[i * SM::LF + j] = j < i ? sBeta[i] * val : 0.f;
-        });
+    if (!upper) { // A = tril(diag(beta) K K^T, -1): a lane has 16 columns j of its row i, four at a time next to each other
+        const int lane = tid & 63, i = 32 * mi + (lane & 31), below = i - 32 * ni - 4 * (lane >> 5); // i - j of element 0
+        const float b = sBeta[i];
+        float *row = sX + i * SM::LF + 32 * ni + 4 * (lane >> 5);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            f32x4 a;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a[u] = below > 8 * e + u ? b * g[4 * e + u] : 0.f;
+            *reinterpret_cast<f32x4 *>(row + 8 * e) = a;
+        }
+    }
     lds_barrier();
     tri_inverse_64(sX, SM::LF);
     // T = X diag(beta), converted and written 16 bytes at a time (X21 stands in the upper right block).  The diagonal, which is beta,
