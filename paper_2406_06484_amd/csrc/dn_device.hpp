@@ -409,6 +409,12 @@ template <typename T, int ROWS, int COLS, int NT = NTHR> struct TileRegs {
         for (int u = 0; u < VEC; ++u) s += to_f32(a[u]) * to_f32(b[u]);
         return s;
     }
+    // sum over the TPR lanes that share a row (they are adjacent; the additions are those of a butterfly)
+    __device__ static inline float row_sum(float x) {
+        static_assert(TPR == 8 || TPR == 16 || TPR == 32, "lanes per row");
+        x = lane_sum<(TPR < 16 ? TPR : 16)>(x);
+        return TPR == 32 ? x + __shfl_xor(x, 16) : x;
+    }
     // The query/key feature map of section 3.3 on the held tile, in place: every row x becomes
     // SiLU(x) / ||SiLU(x)||_2 (a row whose image is exactly zero, such as a row past the end, stays zero).
     // The TPR lanes that share a row are adjacent, so the row sum is a butterfly over them.
@@ -425,8 +431,7 @@ template <typename T, int ROWS, int COLS, int NT = NTHR> struct TileRegs {
                 sv[u] = __fmul_rn(x, sigmoid_f32(x));
                 ss = __fmaf_rn(sv[u], sv[u], ss);
             }
-#pragma unroll
-            for (int d = 1; d < TPR; d <<= 1) ss = __fadd_rn(ss, __shfl_xor(ss, d));
+            ss = row_sum(ss);
             inv[it] = ss > 0.f ? __frsqrt_rn(ss) : 0.f;
 #pragma unroll
             for (int u = 0; u < VEC; ++u) e[u] = from_f32<T>(__fmul_rn(sv[u], inv[it]));
@@ -454,8 +459,7 @@ template <typename T, int ROWS, int COLS, int NT = NTHR> struct TileRegs {
                 const float sv = __fmul_rn(xv, sg[it][u]);
                 ss = __fmaf_rn(sv, sv, ss);
             }
-#pragma unroll
-            for (int d = 1; d < TPR; d <<= 1) ss = __fadd_rn(ss, __shfl_xor(ss, d));
+            ss = row_sum(ss);
             inv[it] = ss > 0.f ? __frsqrt_rn(ss) : 0.f;
         }
 #pragma unroll
@@ -471,8 +475,7 @@ template <typename T, int ROWS, int COLS, int NT = NTHR> struct TileRegs {
                 dsl[u] = s1 * (1.f + xv * (1.f - s1)) * inv[it];
                 dot += to_f32(a[u]) * y[u];
             }
-#pragma unroll
-            for (int d = 1; d < TPR; d <<= 1) dot += __shfl_xor(dot, d);
+            dot = row_sum(dot);
 #pragma unroll
             for (int u = 0; u < VEC; ++u) a[u] = from_f32<T>((to_f32(a[u]) - y[u] * dot) * dsl[u]);
             if (it * RPI + tr < nvalid)

@@ -107,7 +107,7 @@ static __global__ void k_state_copy(float *dst, const float *src, long count) {
 // row, the inverse in K's bytes and without scratch) and the LDS instructions of the inverse.  Against the form with the merges
 // on the vector ALU (six per CU, chunks fastest): 16 384 tokens of width 2048, d = 128 34 -> 25 us (100 MB, 4 TB/s), d = 64
 // 59 -> 43 us, d = 256 30 -> 24 us.  (The Gram product is formed transposed, so that a lane's four elements of A are neighbours and have one beta: with a
-// read of beta and a store for each of the 16 the kernel took 27.7 us for 26.6, at d = 64 39.1 for 37.0, on 1 x 1000 tokens 8.1 for 7.4.)  The prologue variant (two tiles mapped on the way, five per CU) takes 67 us for 300 MB as before.
+// read of beta and a store for each of the 16 the kernel took 27.7 us for 26.6, at d = 64 39.1 for 37.0, on 1 x 1000 tokens 8.1 for 7.4.)  The prologue variant (two tiles mapped on the way, four per CU) takes 64 us for 300 MB.
 template <typename T, int DK, int DV> struct PrepSmem {
     static constexpr int LD = ldc<T>(DK), LF = C + 4;
     // K while the Gram product runs, then the fp32 matrix that is inverted in place
@@ -116,9 +116,9 @@ template <typename T, int DK, int DV> struct PrepSmem {
     static constexpr size_t bytes = oBeta + sizeof(float) * C;
 };
 
-// (bf16 up to d_k = 128: held to the registers of eight workgroups per CU, which is what its LDS allows, five with the
+// (bf16 up to d_k = 128: held to the registers of eight workgroups per CU, which is what its LDS allows, four with the
 // prologue's registers; the other instantiations would spill under such a cap)
-template <typename T, int DK, bool PRO> struct PrepWaves { static constexpr int lo = (sizeof(T) == 2 && DK <= 128) ? (PRO ? 5 : 8) : 1, hi = lo > 1 ? lo : 8; };
+template <typename T, int DK, bool PRO> struct PrepWaves { static constexpr int lo = (sizeof(T) == 2 && DK <= 128) ? (PRO ? 4 : 8) : 1, hi = lo > 1 ? lo : 8; };
 template <typename T, int DK, int DV, bool PRO>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<T, DK, PRO>::lo, PrepWaves<T, DK, PRO>::hi))) void k_wy_prep(SeqMap sm, int H, Ptrs p) {
     using SM = PrepSmem<T, DK, DV>;
@@ -143,10 +143,12 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
 
     {
         TileRegs<T, C, DK> kr;
-        kr.template load_aux<kAuxKeep>((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, threadIdx.x);
+        // (prologue variant: the raw tiles are not needed again before the chunk kernel; not kept in the caches, they leave those to the mapped ones,
+        // which the scan reads next: forward scan that keeps its tiles 95.8 -> 92.4 us, 8 x 2048 tokens of 16 heads of 128)
+        kr.template load_aux<PRO ? kAuxOnce : kAuxKeep>((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, threadIdx.x);
         if constexpr (PRO) { // prologue variant: q and k arrive before the feature map of section 3.3
             TileRegs<T, C, DK> qr;
-            qr.load((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid);
+            qr.load_once((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid);
             float inv[TileRegs<T, C, DK>::NIT];
             kr.feature_map(inv);
             kr.store_global((T *)p.Km + (row0 * H + h) * DK, (long)H * DK, nvalid);
