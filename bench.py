@@ -55,6 +55,7 @@ def kernel_flops_per_chunk_head(name: str, d: int, c: int = C) -> float:
         return 6 * c * d * d + 6 * c * c * d
     if "k_bwd_local" in name:
         # K S, dO S^T, dV S^T, Ut dS'^T (4 x 2Cd^2); K K^T, dO Ut^T, dV Ut^T, dP K, dP^T Q, (Ah + Ah^T) K (6 x 2C^2 d)
+        # (the form through registers; the bf16 one up to d = 128 does not form K S and multiplies by two triangles instead of Ah + Ah^T: 7 % fewer there)
         return 8 * c * d * d + 12 * c * c * d
     return 0.0
 
