@@ -74,8 +74,12 @@ __device__ inline bf16x8 lds_tr16(const unsigned char *lo, const unsigned char *
 // 64 lanes' 16 bytes from global memory to a kilobyte of the LDS, without registers in between (M0 holds the place, lane l lands 16 l
 // behind it; lanes past the descriptor's range leave zeros).  The compiler does not know of the transfer: wait_dma before the
 // barrier that makes the data readable.
+// The hardware does not hold back a buffer access that reads a scalar register written on the vector unit (readlane, readfirstlane: so come
+// spilled descriptors and offsets back) fewer than five wait states before, and the compiler, which keeps that distance for its own accesses, does not
+// look into an asm: the move and the s_nop are five by themselves (M0 needs one), whatever stands ahead of them.  The compiler does not know that M0 is
+// written either: nothing else in a kernel with these transfers may use it.  tests/test_dma_hazards_host.py reads both from the compiled code.
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t rs, int voff, int soff, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rs), "s"(soff) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rs), "s"(soff) : "memory");
 }
 // N: how many requests this wave has certainly made after the transfers it waits for
 template <int N> __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
