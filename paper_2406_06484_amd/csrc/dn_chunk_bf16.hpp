@@ -300,6 +300,19 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
                 sBeta[lane] = b;
                 if (GATED) sGam[lane] = rh.gm;
             }
+            // Gated rule under strong decay: gamma runs from e^h to e^-h over the chunk (it is relative to the chunk's middle), Ut as stored from e^-h to
+            // e^h, S and dS' stand at e^-h.  A product with a row that is scaled only afterwards can leave fp32 where the scaled row's would not, and where
+            // scaled rows become subnormal the scans have lost what dq would still hold, which dg takes for a gradient.  So from h = 60 on the rows of dO and
+            // dV are scaled in the tiles, rounded as in the scans.  (h = 78: dO ~ 1e4 overflowed, at dO ~ 1e-6 dg was off by its own size instead
+            // of a tenth.  h = 51: dO from 1e-10 to 1e4 shows no difference but that of the rounding, dq 3.0e-3 off instead of 3.3e-3.)
+            const bool strong = GATED && __builtin_amdgcn_readlane(__float_as_uint(GATED ? rh.gm : 0.f), C - 1) < (int)__float_as_uint(0x1p-87f);
+            auto gamma = [&](int i) __attribute__((always_inline)) { return strong ? 1.f : sGam[i]; }; // what row i of a product still has to be multiplied by
+            auto scale_piece = [&](unsigned char *at, float g) __attribute__((always_inline)) {
+                bf16x8 t = lds16(at);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) t[u] = (bf16)((float)t[u] * g);
+                *reinterpret_cast<bf16x8 *>(at) = t;
+            };
 
             f32x16 x[RB], y[RB], dp = zero16(), ah = zero16(); // x: dO S^T or dV S^T;  y: -Ut dS'^T
 #pragma unroll
@@ -413,6 +426,12 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
                 if (masked) { masked_rows(blk, blk + SM::bDV, vb); fresh(); }
                 // v_i . dv_i
                 cv = dot8(v_of(vb), *reinterpret_cast<const uint4 *>(blk + SM::bDV + VT::at(vr(), vp())), cv);
+                if (strong) { // (a thread scales the piece that it has just taken its sum from)
+                    const float g = sGam[vr()];
+                    scale_piece(blk + SM::bDO + VT::at(vr(), vp()), g);
+                    scale_piece(blk + SM::bDV + VT::at(vr(), vp()), g);
+                    lds_barrier(); fresh();
+                }
                 if (vb + 1 < NB) fetch_v(rv[1], cur, vb + 1, 1);
                 if (vb == 0) {
                     fetch_v(rv[0], nf, 0, nl);
@@ -481,7 +500,7 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
                 float gm[RB];
 #pragma unroll
                 for (int r = 0; r < RB; ++r) {
-                    gm[r] = GATED ? sGam[32 * (r ^ ti) + li] : 1.f;
+                    gm[r] = GATED ? gamma(32 * (r ^ ti) + li) : 1.f;
                     float pr = 0.f;
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
@@ -511,12 +530,12 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
                         mfma32(l, a[s & 1], c[s & 1]);
                     }
                 }
-                const float gi = GATED ? sGam[32 * ti + li] : 1.f;
+                const float gi = GATED ? gamma(32 * ti + li) : 1.f;
                 if (GATED) { // the rows of dO and dV count gamma_i times
                     dp *= gi; ah *= gi;
 #pragma unroll
                     for (int r = 0; r < RB; ++r) {
-                        x[r] *= sGam[32 * (r ^ ti) + li];
+                        x[r] *= gamma(32 * (r ^ ti) + li);
 #pragma unroll
                         for (int g = 0; g < 4; ++g) {
                             const f32x4 q = row4k(sQ, r ^ ti, g);

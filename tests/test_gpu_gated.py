@@ -59,6 +59,25 @@ def test_gated_strong_decay_within_the_documented_bound(dtype, d, lo, hi):
               label="gated strong decay %s d=%d alpha in (%.2f, %.2f)" % (dtype, d, lo, hi))
 
 
+@pytest.mark.parametrize("dk,dv", [(128, 128), (64, 64), (64, 128), (128, 64), (256, 256)])
+@pytest.mark.parametrize("scale", [2.0 ** 13, 2.0 ** -13, 2.0 ** -20])
+def test_gated_strongest_decay_with_large_and_small_output_gradients(dk, dv, scale):
+    """alpha ~ U(0.075, 0.1): sum|g| is about 157 per chunk, just inside the documented bound, and the rows' factors run from e^78 to e^-78.  Products of
+    dO or dV with tiles that carry such factors have to stay inside fp32 whatever the size of the output gradient; masked rows among them."""
+    inp = make_inputs(29, B=2, L=200, H=2, dk=dk, dv=dv, dtype="bf16", with_initial_state=True, with_dfinal_state=True)
+    inp.d_o *= scale
+    inp.dfinal_state *= scale
+    inp.beta[:, 60:66] = 0.0
+    inp.beta[:, 130] = 2.0 ** -50
+    # dg: see the test above; its errors reach 6.0e-2, 1.3e-1 and 2.3e-1 here: twice that.  At 2^-20 the rows of dO times their factors e^-78 are subnormal in
+    # bf16 (1e-40, where it has steps of 9e-41) for the last tokens of a chunk, in the scans as in the chunk kernel, and their part of the gradients is lost:
+    # largest errors 1.4e-1 (dq) and 4.8e-2, RMS 2.6e-2, the median entry as elsewhere: twice that.
+    tol_of = {"dg": (0.12, 0.26, 0.46)}
+    if scale < 2.0 ** -16:
+        tol_of.update({n: (0.28 if n == "dq" else 0.1, 5.2e-2, 2e-2) for n in ("dq", "dk", "dv", "dbeta")})
+    run_gated(inp, make_gate(5, inp.beta.shape, lo=0.075, hi=0.1), tol_of=tol_of, label="gated strongest decay %dx%d, do * %g" % (dk, dv, scale))
+
+
 def test_zero_gate_equals_the_plain_path_on_the_gpu():
     inp = make_inputs(9, B=1, L=150, H=2, dk=128, dv=128, dtype="bf16", with_initial_state=True, with_dfinal_state=True)
     d = dev_inputs(inp)
