@@ -106,8 +106,8 @@ __device__ inline float dot8(const uint4 &a, const uint4 &b, float s) {
 }
 
 // Gradient through the feature map of section 3.3 for eight neighbouring elements x of a row that LANES lanes hold: with y = SiLU(x) / n,
-// n = ||SiLU(x)||,   dx = SiLU'(x) (dy - y (y . dy)) / n,   SiLU'(x) = s + x s (1 - s).   The norm and y . dy are summed in one pass (the
-// fast sigmoid: y need not have the bits of the mapped tile here).
+// n = ||SiLU(x)||,   dx = SiLU'(x) (dy - y (y . dy)) / n,   SiLU'(x) = s + x s (1 - s), in this order: s + x s - x s^2 loses the one next to a large x.
+// The norm and y . dy are summed in one pass (the fast sigmoid: y need not have the bits of the mapped tile here).
 template <int LANES> __device__ __forceinline__ u32x4 map_gradient(const uint4 &xr, const u32x4 &dyr) {
     const bf16x8 x = __builtin_bit_cast(bf16x8, xr), dy = __builtin_bit_cast(bf16x8, dyr);
     float sg[8], sv[8], ss = 0.f, d = 0.f;
@@ -126,7 +126,7 @@ template <int LANES> __device__ __forceinline__ u32x4 map_gradient(const uint4 &
     const float inv = ss > 0.f ? __frsqrt_rn(ss) : 0.f, t = (d * inv) * inv; // (a row whose image is exactly zero has no gradient)
     bf16x8 o;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) o[u] = (bf16)(__fmaf_rn(-sv[u], t, (float)dy[u]) * (__fmaf_rn(-sv[u], sg[u], sg[u] + sv[u]) * inv));
+    for (int u = 0; u < 8; ++u) o[u] = (bf16)(__fmaf_rn(-sv[u], t, (float)dy[u]) * (__fmaf_rn(sv[u], 1.f - sg[u], sg[u]) * inv));
     return __builtin_bit_cast(u32x4, o);
 }
 

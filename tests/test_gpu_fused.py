@@ -54,6 +54,14 @@ def test_fused_large_and_small_pre_activations():
         run_fused(make_pre_activations(3, base, scale=scale), "fused scale %g" % scale)
 
 
+@pytest.mark.parametrize("dk,dv", [(128, 128), (64, 64), (64, 128), (128, 64), (256, 256)])
+@pytest.mark.parametrize("scale", [0.01, 6.0, 2.0 ** 30])
+def test_fused_large_and_small_pre_activations_in_bf16(dk, dv, scale):
+    # (2^30: far past the point where 1 + x is x in fp32)
+    base = make_inputs(34, B=1, L=130, H=2, dk=dk, dv=dv, dtype="bf16", with_initial_state=True, with_dfinal_state=True)
+    run_fused(make_pre_activations(3, base, scale=scale), "fused bf16 %dx%d scale %g" % (dk, dv, scale))
+
+
 def test_fused_equals_the_plain_path_on_the_mapped_inputs():
     # feeding the plain entry points with the oracle's mapped q, k, beta must give the same outputs up to the
     # rounding of q, k to the element type (fp32 here, so to 1e-5)
