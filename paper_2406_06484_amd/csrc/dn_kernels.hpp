@@ -116,9 +116,9 @@ template <typename T, int DK, int DV> struct PrepSmem {
     static constexpr size_t bytes = oBeta + sizeof(float) * C;
 };
 
-// (bf16 up to d_k = 128: held to the registers of eight workgroups per CU, which is what its LDS allows, four with the
-// prologue's registers; the other instantiations would spill under such a cap)
-template <typename T, int DK, bool PRO> struct PrepWaves { static constexpr int lo = (sizeof(T) == 2 && DK <= 128) ? (PRO ? 4 : 8) : 1, hi = lo > 1 ? lo : 8; };
+// (bf16 up to d_k = 128: held to the registers of eight workgroups per CU, which is what its LDS allows, with the prologue's registers
+// four, at d_k = 64 five: with four the forward pass took 144.6 us for 141 there, 8 x 2048 tokens of 32 heads; the other instantiations would spill under such a cap)
+template <typename T, int DK, bool PRO> struct PrepWaves { static constexpr int lo = (sizeof(T) == 2 && DK <= 128) ? (PRO ? (DK > 64 ? 4 : 5) : 8) : 1, hi = lo > 1 ? lo : 8; };
 template <typename T, int DK, int DV, bool PRO>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<T, DK, PRO>::lo, PrepWaves<T, DK, PRO>::hi))) void k_wy_prep(SeqMap sm, int H, Ptrs p) {
     using SM = PrepSmem<T, DK, DV>;
@@ -144,11 +144,14 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(PrepWaves<
     {
         TileRegs<T, C, DK> kr;
         // (prologue variant: the raw tiles are not needed again before the chunk kernel; not kept in the caches, they leave those to the mapped ones,
-        // which the scan reads next: forward scan that keeps its tiles 95.8 -> 92.4 us, 8 x 2048 tokens of 16 heads of 128)
-        kr.template load_aux<PRO ? kAuxOnce : kAuxKeep>((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, threadIdx.x);
+        // which the scan reads next: forward scan that keeps its tiles 95.8 -> 92.4 us, 8 x 2048 tokens of 16 heads of 128.  At d_k = 64 a batch
+        // whose inputs fit the caches loses more by it: forward pass on 5 x 1500 tokens of 32 heads, run repeatedly, 73.3 us with the raw tiles
+        // kept, 79.2 without, on new inputs 77.2 either way)
+        constexpr int kAuxRaw = PRO && DK > 64 ? kAuxOnce : kAuxKeep;
+        kr.template load_aux<kAuxRaw>((const T *)p.k + (row0 * H + h) * DK, (long)H * DK, nvalid, threadIdx.x);
         if constexpr (PRO) { // prologue variant: q and k arrive before the feature map of section 3.3
             TileRegs<T, C, DK> qr;
-            qr.load_once((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid);
+            qr.template load_aux<kAuxRaw>((const T *)p.q + (row0 * H + h) * DK, (long)H * DK, nvalid, threadIdx.x);
             float inv[TileRegs<T, C, DK>::NIT];
             kr.feature_map(inv);
             kr.store_global((T *)p.Km + (row0 * H + h) * DK, (long)H * DK, nvalid);
