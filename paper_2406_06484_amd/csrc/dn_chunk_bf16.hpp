@@ -408,8 +408,11 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
                     if (mine)
 #pragma unroll
                         for (int u = 0; u < 4; ++u) *reinterpret_cast<s16x4 *>(sDV + VT::at(i, 4 * ub + u) + 8 * hh) = du[u];
+                    lds_barrier();
+                } else if (strong) {
+                    lds_barrier(); // (the tile is about to be scaled)
                 }
-                lds_barrier();
+                // (no barrier otherwise: waves 4 .. 7 go on with their products.  V of the masked rows is not overwritten before the next barrier)
             };
 
             auto block = [&](int vb) __attribute__((always_inline)) {
@@ -486,6 +489,7 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
             for (int vb = 0; vb < NB; ++vb) block(vb);
 
             // ---- what the blocks leave
+            if (masked) lds_barrier(); // dP and Ah take the bytes of V of the masked rows
             fresh();
             float zk = 0.f, z0 = 0.f; // gated: shares of <K, Ut dS~'^T> and of <Q, dO S^T> + <K, Ut dS~'^T - dV S^T>
             { // v_i . dv_i: the lanes that hold a row are adjacent
