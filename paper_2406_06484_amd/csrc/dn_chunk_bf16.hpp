@@ -345,7 +345,7 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
                         // rows of an accumulator in the order that makes it the operand of a product over these rows
                         const int perm = 16 * (li >> 4) + 8 * ((li >> 2) & 1) + 4 * ((li >> 3) & 1) + (li & 3);
                         f32x16 near = zero16(), far = zero16();
-#pragma unroll 2
+#pragma unroll
                         for (int s = 0; s < DK / 16; ++s) {
                             const bf16x8 k = lds16(sK + KT::kc(kc_k, 32 * ua, s));
                             mfma32(near, lds16(sK + KT::at(32 * ua + perm, 2 * s + hh)), k);
@@ -364,7 +364,7 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
                         }
                     }
                     f32x16 ks = zero16(), g = zero16(); // (K S)^T
-#pragma unroll 4
+#pragma unroll
                     for (int s = 0; s < DK / 16; ++s)
                         mfma32(ks, lds16(blk + SM::bS + 2 * ub * (DK / 32) * 1024 + frag_kc<DK>(lane, s)), lds16(sK + KT::kc(kc_k, 32 * ua, s)));
                     auto below = [&](const bf16x8 &l, int s) __attribute__((always_inline)) { // + (tril(K K^T, -1) Ut)^T over tokens 16 s ..
