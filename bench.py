@@ -54,8 +54,11 @@ def kernel_flops_per_chunk_head(name: str, d: int, c: int = C) -> float:
     if "k_scan_fwd" in name:     # T (V - K S), Q K^T, P Ut (3 x 2C^2 d); K S, Q S, K^T Ut (3 x 2Cd^2)
         return 6 * c * d * d + 6 * c * c * d
     if "k_bwd_local" in name:
+        # in bf16 up to d = 128: dO S^T, dV S^T, Ut dS'^T (3 x 2Cd^2); K K^T, dO Ut^T, dV Ut^T (3 x 2C^2 d) and dP K, dP^T Q, Ah K, Ah^T K over
+        # three of a triangle's four 32 x 32 blocks (4 x 3/4 x 2C^2 d): what the counter of the matrix operations shows
+        if d <= 128:
+            return 6 * c * d * d + 12 * c * c * d
         # K S, dO S^T, dV S^T, Ut dS'^T (4 x 2Cd^2); K K^T, dO Ut^T, dV Ut^T, dP K, dP^T Q, (Ah + Ah^T) K (6 x 2C^2 d)
-        # (the form through registers; the bf16 one up to d = 128 does not form K S and multiplies by two triangles instead of Ah + Ah^T: 7 % fewer there)
         return 8 * c * d * d + 12 * c * c * d
     return 0.0
 

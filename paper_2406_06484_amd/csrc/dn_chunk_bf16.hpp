@@ -16,16 +16,18 @@
 // sum_{j<i} (k_i . k_j) Ut_j; see masked_rows.  (The prologue variant needs none of it: its gradient is that of the logit,
 // dlogit_i = beta_i (1 - beta_i) G_i . e_i, which has no quotient.)
 // Gated rule: the chunk is the plain rule on v_i / gamma_i with outputs gamma_i o~_i, so rows of dO and dV count gamma_i times.  The
-// tiles stay as they are and the rows of the products are scaled, in fp32.
+// tiles stay as they are and the rows of the products are scaled, in fp32, but for strongly decaying chunks (see `strong`).
 //
-// What bounds it and why it is cut as it is.  A tile is 160 KB in and 32 KB out at d = 128: 133 us for 4096 of them with nothing else done
-// (16 384 tokens of 16 heads; 256 workgroups that read and write tiles in this pattern reach 6.0 TB/s, reads alone 7.0).  The form that holds the tiles on their way in
-// registers (dn_chunk_local.hpp) takes 161 us there, 131 of them also when every tile is found in the L2: 19 K cycles a tile, 5.3 K of them
-// moving registers to the LDS while the matrix cores wait, 3.8 K in K K^T and the triangles on three of eight waves.  Here the tiles travel
-// straight to the LDS (no registers, no moves, one barrier interval per block instead of two), an operand of a C x d_k product
-// serves both token blocks, K S is not formed, and the results leave four or eight at a time.  Between event records, before and now:
-// d = 128 161 -> 138 us, gated 216 -> 153, prologue 216 -> 172, d = 64 131 -> 118, 5 x 1500 tokens 86 -> 71, 32 768 tokens 313 -> 270.  With the second
-// block of a chunk requested at the start of the chunk, not when the chunk before it is done with its own: 147, 166, 174.
+// What bounds it and why it is cut as it is.  A tile is 160 KB in and 32 KB out at d = 128: 818 MB of counted traffic for 4096 of them (16 384 tokens of
+// 16 heads), 134 us at the 6.1 TB/s of a large copy.  The form that holds the tiles on their way in registers (dn_chunk_local.hpp) takes 161 us there, 131 of
+// them also when every tile is found in the L2: 19 K cycles a tile, 5.3 K of them moving registers to the LDS while the matrix cores wait, 3.8 K in K K^T
+// and the triangles on three of eight waves.  Here the tiles travel straight to the LDS (no registers, no moves, one barrier interval per block instead
+// of two), an operand of a C x d_k product serves both token blocks, K S is not formed, and the results leave four or eight at a time.  Between event
+// records, the form through registers and this one, us, 16 384 tokens of width 2048: d = 128 163 -> 138, gated 214 -> 157, prologue 214 -> 173, d = 64 131 -> 115,
+// its prologue 168 -> 147; of 16 heads of 128 x 64 116 -> 103; of 32 heads of 64 x 128 215 -> 176; 5 x 1500 tokens of d = 128 85 -> 70, 32 768 tokens 311 -> 267.
+// A tenth of the tokens masked: d = 128 189 -> 168, gated 246 -> 205, d = 64 160 -> 130, 128 x 64 131 -> 127, 64 x 128 274 -> 236.
+// With the second block of a chunk requested at the start of the chunk, not when the chunk before it is done with its own, d = 128, gated and prologue
+// took 147, 166 and 174 for 138, 153 and 172.
 #pragma once
 #include <type_traits>
 
@@ -119,10 +121,8 @@ template <int LANES> __device__ __forceinline__ u32x4 map_gradient(const uint4 &
         ss = __fmaf_rn(sv[u], sv[u], ss);
         d = __fmaf_rn(sv[u], (float)dy[u], d);
     }
-    constexpr int ROW = LANES < 16 ? LANES : 16;
-    ss = lane_sum<ROW>(ss);
-    d = lane_sum<ROW>(d);
-    if (LANES > 16) { ss += __shfl_xor(ss, 16); d += __shfl_xor(d, 16); }
+    ss = lane_sum<LANES>(ss);
+    d = lane_sum<LANES>(d);
     const float inv = ss > 0.f ? __frsqrt_rn(ss) : 0.f, t = (d * inv) * inv; // (a row whose image is exactly zero has no gradient)
     bf16x8 o;
 #pragma unroll
@@ -142,7 +142,7 @@ template <int DK, int DV> struct ChunkSmem {
     // a block: S, -dS', dO, dV, Ut
     static constexpr size_t szS = (size_t)BVB * DK * 2, szU = (size_t)BVB * C * 2;
     static constexpr size_t bS = 0, bDS = bS + szS, bDO = bDS + szS, bDV = bDO + VT::bytes, bUt = bDV + VT::bytes, szB = bUt + szU;
-    // two blocks, one worked on and one on its way; at 64 x 64 one, and two workgroups per CU that work while the other one waits
+    // two blocks, one worked on and one on its way (where that holds: see settle); at 64 x 64 one, and two workgroups per CU that work while the other one waits
     static constexpr int NBUF = DK == 64 && DV == 64 ? 1 : 2;
     static constexpr size_t oTab = oB + NBUF * szB;
     static constexpr size_t oBeta = oTab, oGam = oBeta + 4 * C, oCv = oGam + 4 * C, oPl = oCv + 4 * C; // v_i . dv_i;  third term of dbeta, per 32 tokens j
@@ -247,8 +247,10 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
             if (GATED) rh.gm = p.gam[tp.tile * 2 * C + lane];
         };
         // The compiler does not know of the transfers, and takes a wait for a register load that was made before some of them for one that lets only
-        // later loads and stores be under way: it would wait for the transfers too.  So loads are made and waited for at points where no transfer
-        // is to be under way, and their registers marked as written there.
+        // later loads and stores be under way: it would wait for the transfers too.  So the registers loaded in a chunk's first block are marked as
+        // written in its second one, before that requests anything.  Not covered: the position of the next tile (in the loop its loads go through the vector
+        // memory, and where the paths of the two layouts meet the compiler waits for everything), the first use of K and Q in a chunk, and with one
+        // block per chunk V.  As compiled each of them waits for all that is under way, so a chunk begins with nothing on its way.
         auto settle = [&](uint4 &x) __attribute__((always_inline)) { asm volatile("" : "+v"(x.x), "+v"(x.y), "+v"(x.z), "+v"(x.w)); };
         auto settle_all = [&]() __attribute__((always_inline)) {
             settle(rv[0]); settle(rv[1]);
@@ -418,13 +420,14 @@ __device__ __forceinline__ void bwd_local_bf16(SeqMap sm, int H, Ptrs p, int chu
             auto block = [&](int vb) __attribute__((always_inline)) {
                 const int buf = SM::NBUF == 1 ? 0 : NB == 1 ? par : vb & 1;
                 unsigned char *blk = smem + SM::oB + buf * SM::szB;
-                // (chunk's first block: its successor, on its way too, and the stores of the chunk before come after it)
+                // Requests after a first block's transfers: the chunk's second block, if there is one, and the stores of the chunk before, at the least (masked
+                // rows, dbeta and the gate's gradient store more).  The waits named at settle stand ahead of this one and are the ones that bind.
                 if (vb > 0) wait_dma<0>();
                 else wait_dma<NST + (NB > 1 ? NDMA : 0)>();
                 lds_barrier(); fresh();
                 if (vb > 0) settle_all();
                 // every wave is done with the other buffer: the next chunk's first block travels while this one is worked on (a second block has been
-                // on its way since the chunk before was done with its own)
+                // requested when the chunk before was done with its own, and has arrived by the first block of its own chunk)
                 if (vb + 1 == NB && SM::NBUF == 2 && np.ok) fetch_blk(np, 0, buf ^ 1);
                 if (masked) { masked_rows(blk, blk + SM::bDV, vb); fresh(); }
                 // v_i . dv_i

@@ -59,7 +59,7 @@ static inline int launch_offsets(const Problem &pb) {
 // chain waves of the widest scan workgroup: 64 state columns
 template <typename T, int DV> constexpr int kMostChainWaves = sizeof(T) == 4 ? 2 : DV < 64 ? DV / 16 : 4; // (fp32: 32 columns)
 
-// Which chunk kernel: in bf16 up to d_k = 128 the one whose tiles travel straight to the LDS; fp32, and d_k = 256, where the masked rows'
+// Which chunk kernel: in bf16 up to d_k = 128 the one whose tiles travel straight to the LDS (both sides' times at every head size: dn_chunk_bf16.hpp); fp32, and d_k = 256, where the masked rows'
 // extra work per block of 32 state columns costs that kernel more than it gains (16 384 tokens of 8 heads, none / a tenth / padding masked: tiles
 // through registers 215, 250, 247 us, straight to the LDS 204, 326, 305), keep the one that holds them in registers.
 template <typename T, int DK> constexpr bool kDmaChunk = sizeof(T) == 2 && DK <= 128;

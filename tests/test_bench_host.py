@@ -25,8 +25,10 @@ def test_byte_and_flop_models_of_the_kernels():
     # the reverse scan reads Q, K, dO, T (64x64), beta and writes dV and dS'; the pair adds K, V, T in and Ut, S out
     assert bench.kernel_bytes_per_chunk_head("k_scan_bwd", 128) == 4 * tile + cc + st + 64 * 2
     assert bench.kernel_bytes_per_chunk_head("k_scan_pair", 128) == 7 * tile + 2 * cc + 2 * st + 64 * 2
-    # its products: four of 64x128 with 128x128 or across d_k = 128, six of 64x64 with 64x128
-    assert bench.kernel_flops_per_chunk_head("k_bwd_local", 128) == 4 * (2 * 64 * 128 * 128) + 6 * (2 * 64 * 64 * 128) == 14680064
+    # the chunk kernel's products: three of 64x128 with 128x128, three of 64x64 across 128, four of a 64x64 triangle (three of its four
+    # 32x32 blocks) with 64x128; at d = 256 four, and six that count the whole square
+    assert bench.kernel_flops_per_chunk_head("k_bwd_local", 128) == 3 * (2 * 64 * 128 * 128) + 3 * (2 * 64 * 64 * 128) + 4 * 3 * (2 * 32 * 32 * 128) == 12582912
+    assert bench.kernel_flops_per_chunk_head("k_bwd_local", 256) == 4 * (2 * 64 * 256 * 256) + 6 * (2 * 64 * 64 * 256)
     # the specific scan names must not fall through to the plain forward scan's model
     names = ["k_scan_fwd_save", "k_scan_bwd", "k_scan_pair", "k_scan_fwd"]
     assert len({bench.kernel_bytes_per_chunk_head(n, 128) for n in names}) == 4
