@@ -491,7 +491,7 @@ __device__ __forceinline__ void scan_fwd_body(const SeqMap &sm, int H, const Ptr
         if (GATED) lds_barrier(); // (the chain waves read the tables before they hand over the state)
         auto step = [&](Set &nx, Set &cu, TabRegs<T, GATED> &nt, int ic) __attribute__((always_inline)) { // nx, nt: of chunk ic + 1
             fresh();
-            store_tab(nt, ic + 1);
+            store_tab(nt, ic + 1); // (bf16 up to d = 128: as compiled, every second step waits here for all that is under way, not only for the table)
             fetch_tab(nt, ic + 3);
             if (SETS == 2) fetch(cu, ic + 2); // (here rather than in B, where the LDS takes the next chunk)
             f32x4 o[NCW]; // O^T: lane = token, rows = 16 columns of the state per chain wave
